@@ -186,8 +186,11 @@ __device__ __forceinline__ void gather(const float4* __restrict__ sx, float4 xi,
 // (positions first) starts at address 0 (checked on the host) and an entry word can carry
 // ready-made byte addresses.
 typedef float lds_vec4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ lds_vec4 lds_v4(uint32_t byte) {
+    return *(const __attribute__((address_space(3))) lds_vec4*)(size_t)byte;
+}
 __device__ __forceinline__ float4 lds_f4(uint32_t byte) {
-    const lds_vec4 v = *(const __attribute__((address_space(3))) lds_vec4*)(size_t)byte;
+    const lds_vec4 v = lds_v4(byte);
     return make_float4(v.x, v.y, v.z, v.w);
 }
 __device__ __forceinline__ float lds_f1(uint32_t byte) {
@@ -647,51 +650,121 @@ __global__ void __launch_bounds__(1024) step_kernel(StepArgs a, StepParams p) {
 // of cross-lane exchanges (the same value in every lane of the group).  More wavefronts for
 // the same masses, each with a shorter dependent chain: for bodies too small to fill the chip.
 // The sum is grouped differently from the one-lane form, so the two agree to rounding only.
-template <bool ACT, int EX, int LPM, bool NARROW>
-__device__ __forceinline__ void gather_lanes(uint32_t tbase, const float* __restrict__ sf, float4 xi, int s, int sub,
-                                             int nslice, const int32_t* __restrict__ slice_ptr,
-                                             const uint32_t* __restrict__ packed, const uint16_t* __restrict__ narrow,
-                                             int tb, float& fx, float& fy, float& fz) {
-    fx = fy = fz = 0.0f;
-    s = __builtin_amdgcn_readfirstlane(s);
-    if (s < nslice) {
-        const int lane = ((int)threadIdx.x / LPM) & 63;
+//
+// Such a step is a chain of latencies (the 12.7k-mass quadruped: under one wavefront per SIMD,
+// 3% of the VALU's issue slots), so each lane loads its entries before the workgroup's barrier,
+// beside the halo's index -> position chain, and reads all its neighbours from LDS before the
+// first spring's arithmetic: 5.4 -> 4.8 us per step (two rows at a time after the barrier: a
+// memory, an LDS and an arithmetic latency for each pair).
+constexpr int kLaneGroup = 8;   // rows whose LDS reads are in flight together
+// rows of a lane held in registers: all of a voxel node's 26 (4 lanes: 7, 2 lanes: 13)
+template <int LPM>
+constexpr int kLanePre = LPM == 2 ? 2 * kLaneGroup : kLaneGroup;
+typedef uint32_t lane_rows_vec __attribute__((ext_vector_type(2 * kLaneGroup)));   // a vector, never an array in memory
+
+template <int LPM, bool NARROW>
+struct LaneRows {
+    const uint32_t* __restrict__ packed;
+    const uint16_t* __restrict__ narrow;
+    int e;       // this lane's entry of incidence row 0 (row r: 64 r further)
+    int w;       // incidence rows of the slice
+    int count;   // rows per lane, counting a last one that some lanes of a group may lack
+    lane_rows_vec q;
+
+    // the lane's k-th entry; a lane without one gets an entry of its own mass (used with factor 0)
+    __device__ __forceinline__ uint32_t row(int k, int sub, bool& ok) const {
+        ok = k * LPM + sub < w;
+        const int r = ok ? k * LPM + sub : k > 0 ? (k - 1) * LPM + sub : 0;
+        return NARROW ? (uint32_t)narrow[e + r * 64] : packed[e + r * 64];
+    }
+    __device__ __forceinline__ void load(int s, int lane, int sub, int nslice, const int32_t* __restrict__ slice_ptr) {
+        s = __builtin_amdgcn_readfirstlane(s);
+        e = w = count = 0;
+        if (s >= nslice) return;
         const int e0 = __builtin_amdgcn_readfirstlane(slice_ptr[s]);
-        const int w = __builtin_amdgcn_readfirstlane((slice_ptr[s + 1] - e0) >> 6);
-        const int rows = (w + LPM - 1) / LPM;
-        const uint32_t tmask = (1u << tb) - 1u;
-        auto one = [&](uint32_t q) {
-            uint32_t xa, ca, gi = 0;
-            if (NARROW) {
-                xa = (q >> tb) << 4;
-                ca = ((q & tmask) << 4) | tbase;
-            } else {
-                decode_entry<ACT>(q, tbase, xa, ca, gi);
-            }
-            const float4 xj = lds_f4(xa);
-            const float4 c = lds_f4(ca);
-            const float g = ACT ? sf[gi] : 1.0f;
-            float dx, dy, dz;
-            const float fac = hooke_fac_tab<ACT, EX>(xi, xj, c, g, dx, dy, dz);
-            fx = __builtin_fmaf(fac, dx, fx);
-            fy = __builtin_fmaf(fac, dy, fy);
-            fz = __builtin_fmaf(fac, dz, fz);
-        };
-        constexpr int B = 2;
-        for (int k = 0; k < rows; k += B) {
-            uint32_t q[B];
-            bool ok[B];
+        w = __builtin_amdgcn_readfirstlane((slice_ptr[s + 1] - e0) >> 6);
+        e = e0 + lane;
+        count = (w + LPM - 1) / LPM;
+        if (count == 0) return;
+        bool ok;
 #pragma unroll
-            for (int u = 0; u < B; ++u) {
-                const int r = (k + u) * LPM + sub;
-                ok[u] = r < w;
-                const int e = e0 + r * 64 + lane;
-                q[u] = ok[u] ? (NARROW ? (uint32_t)narrow[e] : packed[e]) : 0u;
-            }
+        for (int u = 0; u < kLanePre<LPM>; ++u) q[u] = row(min(u, count - 1), sub, ok);   // stays inside the slice
+    }
+};
+
+// N rows of the lane from their entries q[BASE ...]: every LDS read first, then the springs in row
+// order.  Only the slice's last row can be missing in some lanes (ok_last).
+template <bool ACT, int EX, bool NARROW, int BASE, int N>
+__device__ __forceinline__ void lane_springs(uint32_t tbase, const float* __restrict__ sf, float4 xi, int tb,
+                                             const lane_rows_vec& q, bool ok_last, float& fx, float& fy, float& fz) {
+    const uint32_t tmask = (1u << tb) - 1u;
+    lds_vec4 xj[N], c[N];
+    float g[N];
 #pragma unroll
-            for (int u = 0; u < B; ++u)
-                if (ok[u]) one(q[u]);
+    for (int u = 0; u < N; ++u) {
+        uint32_t xa, ca, gi = 0;
+        if (NARROW) {
+            xa = (q[BASE + u] >> tb) << 4;
+            ca = ((q[BASE + u] & tmask) << 4) | tbase;
+        } else {
+            decode_entry<ACT>(q[BASE + u], tbase, xa, ca, gi);
         }
+        xj[u] = lds_v4(xa);
+        c[u] = lds_v4(ca);
+        g[u] = ACT ? sf[gi] : 1.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        float dx, dy, dz;
+        float fac = hooke_fac_tab<ACT, EX>(xi, make_float4(xj[u].x, xj[u].y, xj[u].z, xj[u].w),
+                                           make_float4(c[u].x, c[u].y, c[u].z, c[u].w), g[u], dx, dy, dz);
+        if (u == N - 1) fac = ok_last ? fac : 0.0f;
+        fx = __builtin_fmaf(fac, dx, fx);
+        fy = __builtin_fmaf(fac, dy, fy);
+        fz = __builtin_fmaf(fac, dz, fz);
+    }
+}
+
+// The first `count` (at most kLaneGroup) rows of q[BASE ...]; count is uniform over the wavefront.
+template <bool ACT, int EX, bool NARROW, int BASE>
+__device__ __forceinline__ void lane_group(int count, uint32_t tbase, const float* __restrict__ sf, float4 xi, int tb,
+                                           const lane_rows_vec& q, bool ok_last, float& fx, float& fy, float& fz) {
+    switch (count) {
+#define CRONOS_ROWS(N) \
+    case N: lane_springs<ACT, EX, NARROW, BASE, N>(tbase, sf, xi, tb, q, ok_last, fx, fy, fz); break;
+        CRONOS_ROWS(1)
+        CRONOS_ROWS(2)
+        CRONOS_ROWS(3)
+        CRONOS_ROWS(4)
+        CRONOS_ROWS(5)
+        CRONOS_ROWS(6)
+        CRONOS_ROWS(7)
+        CRONOS_ROWS(8)
+#undef CRONOS_ROWS
+        default: break;
+    }
+}
+
+template <bool ACT, int EX, int LPM, bool NARROW>
+__device__ __forceinline__ void gather_lanes(uint32_t tbase, const float* __restrict__ sf, float4 xi, int sub, int tb,
+                                             const LaneRows<LPM, NARROW>& rows, float& fx, float& fy, float& fz) {
+    fx = fy = fz = 0.0f;
+    const bool ok_last = (rows.count - 1) * LPM + sub < rows.w;
+    auto ok = [&](int end) { return end < rows.count || ok_last; };   // of a group that ends before row `end`
+    const int n0 = min(rows.count, kLaneGroup);
+    lane_group<ACT, EX, NARROW, 0>(n0, tbase, sf, xi, tb, rows.q, ok(n0), fx, fy, fz);
+    if (kLanePre<LPM> > kLaneGroup && rows.count > kLaneGroup) {
+        const int n1 = min(rows.count - kLaneGroup, kLaneGroup);
+        lane_group<ACT, EX, NARROW, kLanePre<LPM> - kLaneGroup>(n1, tbase, sf, xi, tb, rows.q, ok(kLaneGroup + n1), fx, fy,
+                                                               fz);
+    }
+    for (int k = kLanePre<LPM>; k < rows.count; k += 4) {   // bodies of higher degree
+        lane_rows_vec q;
+        bool have;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[u] = rows.row(min(k + u, rows.count - 1), sub, have);
+        const int n = min(rows.count - k, 4);
+        lane_group<ACT, EX, NARROW, 0>(n, tbase, sf, xi, tb, q, ok(k + n), fx, fy, fz);
     }
 #pragma unroll
     for (int o = 1; o < LPM; o <<= 1) {
@@ -707,6 +780,11 @@ __device__ __forceinline__ void gather_lanes(uint32_t tbase, const float* __rest
 template <bool ACT, bool EXACT, int LPM, bool NARROW>
 __global__ void __launch_bounds__(1024) step_lanes_kernel(StepArgs a, StepParams p) {
     extern __shared__ float4 sx[];
+    // the arguments that the first loads need, fetched together (one scalar-cache latency, not
+    // one for each use)
+    asm volatile("" ::"s"(a.xin), "s"(a.vin), "s"(a.slice_ptr), "s"(a.halo_ptr), "s"(a.halo_idx), "s"(a.lane_mass),
+                 "s"(NARROW ? (const void*)a.narrow : (const void*)a.packed), "s"(a.table), "s"(a.n), "s"(a.nblk),
+                 "s"(a.nslice), "s"(a.block), "s"(a.n_table), "s"(a.lds_slots));
     const int b = logical_block(a.nblk);
     const long long n_step = ACT && a.fuse ? *a.step_in : 0;
     if (ACT && a.fuse) advance_step(a, n_step);
@@ -714,9 +792,29 @@ __global__ void __launch_bounds__(1024) step_lanes_kernel(StepArgs a, StepParams
     const int t = (int)threadIdx.x, nt = (int)blockDim.x;
     const int m = t / LPM, sub = t % LPM;
     const int base = b * a.block;
+    // every load that depends on nothing staged is issued here: the first halo index, this
+    // lane's mass, its own position, its entries, then what hangs on those
+    const int h0 = a.halo_ptr[b], h1 = a.halo_ptr[b + 1];
+    const int own = a.lane_mass[base + m];
+    const int hj = h0 + t < h1 ? a.halo_idx[h0 + t] : -1;
+    float4 xt = make_float4(0.f, 0.f, 0.f, 0.f), xh = xt;
+    if (t < a.block && base + t < a.n) xt = a.xin[base + t];
+    LaneRows<LPM, NARROW> rows;
+    rows.packed = a.packed;
+    rows.narrow = a.narrow;
+    rows.load((base + m) >> 6, m & 63, sub, a.nslice, a.slice_ptr);
     const uint32_t tbase = table_base(a.lds_slots);
     float4* st = reinterpret_cast<float4*>(reinterpret_cast<char*>(sx) + tbase);
     float* sf = reinterpret_cast<float*>(st + a.n_table);
+    if (hj >= 0) xh = a.xin[hj];
+    const int i = base + own;
+    const bool mine = sub == 0 && i < a.n;
+    float vx = 0.0f, vy = 0.0f, vz = 0.0f;
+    if (mine) {
+        vx = a.vin[3 * i + 0];
+        vy = a.vin[3 * i + 1];
+        vz = a.vin[3 * i + 2];
+    }
     for (int q = t; q < a.n_table; q += nt) st[q] = a.table[q];
     if (ACT) {
         const int2 bg = a.blk_groups[b];
@@ -728,27 +826,20 @@ __global__ void __launch_bounds__(1024) step_lanes_kernel(StepArgs a, StepParams
             for (int q = t; q <= bg.y; q += nt) sf[q] = q ? a.factor[bg.x + q - 1] : 1.0f;
         }
     }
-    for (int q = t; q < a.block; q += nt) sx[q] = base + q < a.n ? a.xin[base + q] : make_float4(0.f, 0.f, 0.f, 0.f);
-    const int h0 = a.halo_ptr[b], h1 = a.halo_ptr[b + 1];
-    for (int h = h0 + t; h < h1; h += nt) sx[a.block + (h - h0)] = a.xin[a.halo_idx[h]];
+    if (t < a.block) sx[t] = xt;   // block * LPM threads: one round
+    if (hj >= 0) sx[a.block + t] = xh;
+    for (int h = h0 + t + nt; h < h1; h += nt) sx[a.block + (h - h0)] = a.xin[a.halo_idx[h]];
     __syncthreads();
-    const int own = a.lane_mass[base + m];
     const float4 xi = sx[own];
-    const int s = (base + m) >> 6;
     float fx, fy, fz;
     const int mode = EXACT ? difference_mode(xi, p.safe) : kPlain;
     if (mode == kPlain)
-        gather_lanes<ACT, kPlain, LPM, NARROW>(tbase, sf, xi, s, sub, a.nslice, a.slice_ptr, a.packed, a.narrow,
-                                               a.narrow_tb, fx, fy, fz);
+        gather_lanes<ACT, kPlain, LPM, NARROW>(tbase, sf, xi, sub, a.narrow_tb, rows, fx, fy, fz);
     else if (mode == kExactZ)
-        gather_lanes<ACT, kExactZ, LPM, NARROW>(tbase, sf, xi, s, sub, a.nslice, a.slice_ptr, a.packed, a.narrow,
-                                                a.narrow_tb, fx, fy, fz);
+        gather_lanes<ACT, kExactZ, LPM, NARROW>(tbase, sf, xi, sub, a.narrow_tb, rows, fx, fy, fz);
     else
-        gather_lanes<ACT, kExactAll, LPM, NARROW>(tbase, sf, xi, s, sub, a.nslice, a.slice_ptr, a.packed, a.narrow,
-                                                  a.narrow_tb, fx, fy, fz);
-    const int i = base + own;
-    if (sub != 0 || i >= a.n) return;
-    float vx = a.vin[3 * i + 0], vy = a.vin[3 * i + 1], vz = a.vin[3 * i + 2];
+        gather_lanes<ACT, kExactAll, LPM, NARROW>(tbase, sf, xi, sub, a.narrow_tb, rows, fx, fy, fz);
+    if (!mine) return;
     float4 xo;
     integrate(p, p.dtv, xi, fx, fy, fz, a.fext ? a.fext + 3 * i : nullptr, vx, vy, vz, xo,
               a.vstar_out ? a.vstar_out + 3 * i : nullptr);
