@@ -146,20 +146,27 @@ hipError_t launch_actuation_steps(const DeviceArrays& d, unsigned long long cycl
 hipError_t launch_forces(const DeviceArrays& d, int cur, const StepParams& p, hipStream_t st);
 
 // Lanczos iterations for the natural frequencies (modes.hip), FP64.
+constexpr int kModesNormParts = 512;     // doubles held for the vector kernels' partial norms
 struct ModesBuffers {
     double* ism = nullptr;               // [n] M^-1/2 (0 for fixed masses)
-    double* q[2] = {nullptr, nullptr};   // [3n] Lanczos vectors, alternating roles
-    double* y = nullptr;                 // [3n] A q
-    double* part_a = nullptr;            // [nblk] partial q . A q
-    double* part_u = nullptr;            // [ceil(n / 256)] partial squared norms
+    double* q[2] = {nullptr, nullptr};   // [3n] unnormalised Lanczos vectors, alternating roles (16-byte aligned)
+    double* y = nullptr;                 // [3n] A q (16-byte aligned)
+    double* part_a = nullptr;            // [modes_apply_parts] partial q . A q
+    double* part_u = nullptr;            // [kModesNormParts] partial squared norms
     double* alpha = nullptr;             // [max_iter] diagonal of the tridiagonal matrix
     double* beta = nullptr;              // [max_iter] off-diagonal (beta[k] follows step k)
+    double* inv = nullptr;               // [2] 1 / norm of the two vectors
+    int cus = 0;                         // the device's compute units (set by launch_modes_init)
 };
-// Random start vector q_0 (normalised, in q[1]; q[0] cleared to zeros) and M^-1/2.
+// Partials that an apply launch writes, at most.
+int64_t modes_apply_parts(const DeviceArrays& d);
+// Random start vector (unnormalised, in q[1]; q[0] cleared to zeros) and M^-1/2.
 hipError_t launch_modes_init(const DeviceArrays& d, int cur, ModesBuffers& m, unsigned long long seed, hipStream_t st);
-// Lanczos step k: alpha[k], beta[k] and q_{k+1} from q_k and q_{k-1}.
+// Lanczos step k: alpha[k], beta[k - 1] and the unnormalised q_{k+1} from q_k and q_{k-1}.
 hipError_t launch_modes_iteration(const DeviceArrays& d, int cur, const StepParams& p, ModesBuffers& m, int k,
                                   hipStream_t st);
+// beta[k - 1] after steps 0 .. k - 1 (step k writes the same value again).
+hipError_t launch_modes_beta(const DeviceArrays& d, ModesBuffers& m, int k, hipStream_t st);
 // Fixed FP64 workspace of the allocation-free frequency entry point: a file-scope device
 // array of this many doubles (64 MiB) on every GPU the library runs on, held until the process
 // ends.  modes_scratch returns its address on `device` (which must be current), looked up

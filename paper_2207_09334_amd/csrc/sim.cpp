@@ -1424,6 +1424,7 @@ cronos_status lanczos_frequencies(cronos_sim sim, cronos::ModesBuffers& m, int32
     std::vector<double> best;
     while (true) {
         for (; k < next; ++k) HIP_TRY(cronos::launch_modes_iteration(sim->d, sim->cur, sim->p, m, k, sim->stream));
+        HIP_TRY(cronos::launch_modes_beta(sim->d, m, k, sim->stream));
         HIP_TRY(hipMemcpyAsync(ha.data(), m.alpha, k * sizeof(double), hipMemcpyDeviceToHost, sim->stream));
         HIP_TRY(hipMemcpyAsync(hb.data(), m.beta, k * sizeof(double), hipMemcpyDeviceToHost, sim->stream));
         HIP_TRY(hipStreamSynchronize(sim->stream));
@@ -1464,7 +1465,6 @@ extern "C" cronos_status cronos_natural_frequencies(cronos_sim sim, int32_t n_mo
     const int64_t n = sim->d.n;
     HIP_TRY(hipSetDevice(sim->device));
     cronos::ModesBuffers m;
-    const int64_t nu = (n + 255) / 256;
     std::vector<void*> owned;
     auto alloc = [&](double** p, size_t count) -> cronos_status {
         if (hipMalloc((void**)p, std::max<size_t>(count, 1) * sizeof(double)) != hipSuccess)
@@ -1477,8 +1477,9 @@ extern "C" cronos_status cronos_natural_frequencies(cronos_sim sim, int32_t n_mo
         TRY(alloc(&m.q[0], 3 * n));
         TRY(alloc(&m.q[1], 3 * n));
         TRY(alloc(&m.y, 3 * n));
-        TRY(alloc(&m.part_a, sim->d.nblk));
-        TRY(alloc(&m.part_u, nu));
+        TRY(alloc(&m.part_a, cronos::modes_apply_parts(sim->d)));
+        TRY(alloc(&m.part_u, cronos::kModesNormParts));
+        TRY(alloc(&m.inv, 2));
         TRY(alloc(&m.alpha, max_iter));
         TRY(alloc(&m.beta, max_iter));
         return lanczos_frequencies(sim, m, n_modes, max_iter, tol, seed, omega, n_found, iterations);
@@ -1499,9 +1500,10 @@ extern "C" cronos_status cronos_natural_frequencies_noalloc(cronos_sim sim, int3
     double* base = nullptr;
     HIP_TRY(cronos::modes_scratch(sim->device, &base));
     // carve the fixed workspace: every buffer starts on a 256-byte boundary
-    const int64_t counts[8] = {n, 3 * n, 3 * n, 3 * n, sim->d.nblk, (n + 255) / 256, max_iter, max_iter};
-    int64_t off[8], used = 0;
-    for (int b = 0; b < 8; ++b) {
+    const int64_t counts[9] = {n, 3 * n, 3 * n, 3 * n, cronos::modes_apply_parts(sim->d), cronos::kModesNormParts,
+                               max_iter, max_iter, 2};
+    int64_t off[9], used = 0;
+    for (int b = 0; b < 9; ++b) {
         off[b] = used;
         used += (std::max<int64_t>(counts[b], 1) + 31) / 32 * 32;
     }
@@ -1519,6 +1521,7 @@ extern "C" cronos_status cronos_natural_frequencies_noalloc(cronos_sim sim, int3
     m.part_u = base + off[5];
     m.alpha = base + off[6];
     m.beta = base + off[7];
+    m.inv = base + off[8];
     const cronos_status st = lanczos_frequencies(sim, m, n_modes, max_iter, tol, seed, omega, n_found, iterations);
     (void)hipStreamSynchronize(sim->stream);
     return st;
