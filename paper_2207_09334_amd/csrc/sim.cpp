@@ -1362,12 +1362,9 @@ std::vector<RitzCluster> ritz_clusters(const std::vector<double>& a, const std::
     const double tiny_count = 1e-300, tiny_solve = 1e-15 * std::max(norm, 1e-300);
     const double beta_k = b[k - 1];  // norm of the next Lanczos residual
     std::vector<double> th(count), r(count);
-    double lower = lo;
-    for (int64_t j = 0; j < count; ++j) {
-        th[j] = cronos::tridiag_eigenvalue(a.data(), b2.data(), k, j, lower, hi, tiny_count);
-        lower = std::max(lo, th[j] - 4e-16 * norm);
+    cronos::tridiag_smallest(a.data(), b2.data(), k, count, lo, hi, tiny_count, th.data());
+    for (int64_t j = 0; j < count; ++j)
         r[j] = std::fabs(beta_k) * cronos::eigvec_last_component(a.data(), b.data(), k, th[j], tiny_solve);
-    }
     std::vector<RitzCluster> out;
     std::vector<double> out_r;
     for (int64_t j = 0; j < count; ++j) {

@@ -7,20 +7,35 @@
 
 namespace cronos {
 
-// Number of eigenvalues of T below x (T: diagonal a[0..k), off-diagonal b[0..k-1), b2 = b^2).
-// The ratios of the LDL^T factorisation of T - x I count the negative pivots; a zero pivot
-// is replaced by a tiny one, which moves x by far less than the bisection tolerance.
-int64_t sturm_count(const double* a, const double* b2, int64_t k, double x, double tiny) {
-    int64_t count = 0;
-    double q = a[0] - x;
-    for (int64_t i = 0;; ++i) {
-        if (std::fabs(q) < tiny) q = -tiny;
-        if (q < 0.0) ++count;
-        if (i + 1 == k) break;
-        q = (a[i + 1] - x) - b2[i] / q;
+namespace {
+
+constexpr int kShifts = 16;   // shifts that one pass over T serves
+
+// Numbers of eigenvalues of T below each x[0..kShifts) (T: diagonal a[0..k), off-diagonal
+// b[0..k-1), b2 = b^2).  The ratios of the LDL^T factorisation of T - x I count the negative
+// pivots; a zero pivot is replaced by a tiny one, which moves x by far less than the bisection
+// tolerance.  One shift alone is a serial chain of divisions (a division latency per row); the
+// shifts' chains are independent, so together they run at the divider's throughput.
+void sturm_counts(const double* a, const double* b2, int64_t k, const double* x, double tiny, int64_t* count) {
+    double q[kShifts], c[kShifts], xs[kShifts];
+    for (int l = 0; l < kShifts; ++l) {
+        xs[l] = x[l];
+        q[l] = a[0] - xs[l];
+        c[l] = 0.0;
     }
-    return count;
+    for (int64_t i = 0;; ++i) {
+        for (int l = 0; l < kShifts; ++l) {
+            q[l] = std::fabs(q[l]) < tiny ? -tiny : q[l];
+            c[l] += q[l] < 0.0 ? 1.0 : 0.0;
+        }
+        if (i + 1 == k) break;
+        const double ai = a[i + 1], bi = b2[i];
+        for (int l = 0; l < kShifts; ++l) q[l] = (ai - xs[l]) - bi / q[l];
+    }
+    for (int l = 0; l < kShifts; ++l) count[l] = (int64_t)c[l];
 }
+
+}  // namespace
 
 // Gershgorin interval [lo, hi] holding every eigenvalue of T.
 void gershgorin(const double* a, const double* b, int64_t k, double* lo, double* hi) {
@@ -34,16 +49,40 @@ void gershgorin(const double* a, const double* b, int64_t k, double* lo, double*
     *hi = h;
 }
 
-// The index-th smallest eigenvalue (0-based) of T by bisection within [lo, hi].
-double tridiag_eigenvalue(const double* a, const double* b2, int64_t k, int64_t index, double lo, double hi,
-                          double tiny) {
-    for (int it = 0; it < 200; ++it) {
-        const double mid = 0.5 * (lo + hi);
-        if (mid <= lo || mid >= hi) break;  // interval at one ulp
-        if (sturm_count(a, b2, k, mid, tiny) > index) hi = mid;
-        else lo = mid;
+// The `count` smallest eigenvalues of T, ascending, by section of [lo, hi] down to one ulp: up to
+// kShifts of them at a time, each pass over T placing kShifts / m points inside each of m intervals.
+void tridiag_smallest(const double* a, const double* b2, int64_t k, int64_t count, double lo, double hi, double tiny,
+                      double* theta) {
+    for (int64_t j0 = 0; j0 < count; j0 += kShifts) {
+        const int m = (int)std::min<int64_t>(kShifts, count - j0), per = kShifts / m;
+        double l[kShifts], h[kShifts], x[kShifts];
+        int64_t below[kShifts];
+        for (int j = 0; j < kShifts; ++j) {
+            l[j] = lo;
+            h[j] = hi;
+            x[j] = hi;
+        }
+        for (int it = 0; it < 200; ++it) {
+            bool open = false;
+            for (int j = 0; j < m; ++j) {
+                const double mid = 0.5 * (l[j] + h[j]);
+                open = open || (mid > l[j] && mid < h[j]);   // else the interval is at one ulp
+                for (int p = 0; p < per; ++p) x[j * per + p] = l[j] + (h[j] - l[j]) * ((double)(p + 1) / (per + 1));
+            }
+            if (!open) break;
+            sturm_counts(a, b2, k, x, tiny, below);
+            for (int j = 0; j < m; ++j) {
+                const double l0 = l[j], h0 = h[j];
+                for (int p = 0; p < per; ++p) {
+                    const double xp = x[j * per + p];
+                    if (xp <= l0 || xp >= h0) continue;
+                    if (below[j * per + p] > j0 + j) h[j] = std::min(h[j], xp);
+                    else l[j] = std::max(l[j], xp);
+                }
+            }
+        }
+        for (int j = 0; j < m; ++j) theta[j0 + j] = 0.5 * (l[j] + h[j]);
     }
-    return 0.5 * (lo + hi);
 }
 
 // |last component| of the unit eigenvector of T for the eigenvalue approximation theta: two
@@ -117,10 +156,8 @@ extern "C" cronos_status cronos_tridiag_smallest(int64_t k, const double* a, con
     double lo, hi;
     cronos::gershgorin(a, bb, k, &lo, &hi);
     const double norm = std::max({std::fabs(lo), std::fabs(hi), 1e-300});
-    double lower = lo;
+    cronos::tridiag_smallest(a, b2.data(), k, count, lo, hi, 1e-300, theta);
     for (int64_t j = 0; j < count; ++j) {
-        theta[j] = cronos::tridiag_eigenvalue(a, b2.data(), k, j, lower, hi, 1e-300);
-        lower = std::max(lo, theta[j] - 4e-16 * norm);
         if (last) last[j] = cronos::eigvec_last_component(a, bb, k, theta[j], 1e-15 * norm);
     }
     return CRONOS_OK;

@@ -66,3 +66,17 @@ def test_bad_arguments():
         CR.cronos_tridiag_smallest(np.ones(3), np.ones(2), 4)
     with pytest.raises(CR.CronosError):
         CR.cronos_tridiag_smallest(np.array([1.0, np.nan]), np.ones(1), 1)
+
+
+@pytest.mark.parametrize("count", [1, 2, 5, 8, 15, 16, 17, 33, 40])
+def test_sections_of_any_count_agree(count):
+    """Eigenvalues are found several at a time, each interval cut at one to sixteen points a pass:
+    however many are asked for, the same doubles come out (each the one at which the count of
+    smaller eigenvalues changes), within a few eps of the norm of LAPACK's."""
+    rng = np.random.default_rng(count)
+    a, b = rng.uniform(0.0, 4.0, 40), rng.uniform(0.1, 2.0, 39)
+    every, _ = CR.cronos_tridiag_smallest(a, b, 40)
+    some, _ = CR.cronos_tridiag_smallest(a, b, count)
+    assert np.array_equal(some, every[:count])
+    ref = np.linalg.eigvalsh(np.diag(a) + np.diag(b, 1) + np.diag(b, -1))
+    assert np.abs(every - ref).max() <= 40 * np.finfo(float).eps * np.abs(ref).max()
