@@ -45,6 +45,19 @@ __device__ __forceinline__ int logical_block(int nblk) {
 // Coordinate-difference modes of the spring arithmetic (see hooke_fac).
 enum : int { kPlain = 0, kExactZ = 1, kExactAll = 2 };
 
+// Added to |d|^2 as it is summed (an FP64 addend far below half an ulp of any real spring's, so no
+// bit of those changes): keeps a zero-length spring's denominator above zero, and its factor
+// finite, without an instruction of its own.
+constexpr double kLengthFloor = 1e-37;
+
+// e^2 + kLengthFloor in one instruction: left to itself the compiler copies the constant into the
+// accumulator of a two-address multiply-add first (two more instructions per spring).
+__device__ __forceinline__ double square_above_floor(double e) {
+    double s;
+    asm("v_fma_f64 %0, %1, %1, %2" : "=v"(s) : "v"(e), "s"(kLengthFloor));
+    return s;
+}
+
 // Scalar factor of the Hooke force of eq. (2) for the spring from (xi, yi, zi) to (xj, yj, zj):
 // the force on the first end is fac * d with d = xj - xi; a zero-length spring gives 0 (its d
 // is 0 and fac stays finite).  Every step below is unchanged, bit for bit, when d changes sign,
@@ -74,13 +87,12 @@ __device__ __forceinline__ float hooke_fac(float xi, float yi, float zi, float x
         ey = (double)yj - (double)yi;
     }
     if (EX != kPlain) ez = (double)zj - (double)zi;
-    const double s = __builtin_fma(ex, ex, __builtin_fma(ey, ey, ez * ez));
+    const double s = __builtin_fma(ex, ex, __builtin_fma(ey, ey, square_above_floor(ez)));
     const float diff = (float)(s - q);
     const float s2 = (float)s;
     const float len = __builtin_amdgcn_sqrtf(s2);
-    // |d| (|d| + L0) = s2 + L0 |d| to within an ulp; the floor keeps a zero-length spring's
-    // factor finite (its force fac * d is then exactly 0) and is far below any real spring's
-    const float den = __builtin_fmaxf(__builtin_fmaf(l0, len, s2), 1e-30f);
+    // |d| (|d| + L0) = s2 + L0 |d| to within an ulp
+    const float den = __builtin_fmaf(l0, len, s2);
     return k * diff * __builtin_amdgcn_rcpf(den);
 }
 
