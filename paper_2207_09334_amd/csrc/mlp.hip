@@ -15,20 +15,27 @@
 // follows the weight in the parameter vector.  Widths are padded to multiples of 32 with zero
 // weights, so padded activations are exactly zero.
 //
-// Tiling: a workgroup of 4 wavefronts computes a 64 x 64 tile of C, each wavefront a 32 x 32
-// quarter as 2 x 2 MFMA tiles of 16 x 16, stepping K by 128 (or 64, 32) through two LDS buffers:
-// the next K-step's operands are loaded into registers while the matrix cores work on the
-// current one, then stored to the other buffer (one barrier per K-step).  The weight
-// gradients (K = the minibatch rows) split K into chunks of 512 rows computed by separate
+// Tiling: a workgroup of 8 wavefronts computes a 64 x 64 tile of C (128 x 128 for forward products of
+// many rows), each wavefront an eighth of it in MFMA tiles of 16 x 16, stepping K by 64 (or 32)
+// through a ring of four LDS stages.  A minibatch's product is a few hundred
+// tiles, one workgroup per CU or two, so nothing but its own wavefronts hides a latency: eight of them,
+// and the operands of three K-steps on their way at once, straight from memory into an LDS ring
+// (no registers, no store; one barrier per step).  1024 x 768 x 768 with GELU, its slope and
+// the transposed output: 11.5 -> 8.2 us; the paired backward products 16.2 -> 10.4 us (four
+// wavefronts, one step of 128 ahead in registers, both GELU and slope by erf per element).  The
+// weight gradients (K = the minibatch rows) split K into chunks of 512 rows computed by separate
 // workgroups into FP32 partials, laid out like the parameters, that Adam adds in a fixed
-// order (or one more kernel, when the gradient itself is asked for).  Operand layouts
-// of the 16x16x32 BF16 MFMA: lane l supplies A[l % 16][8 (l / 16) + j] and B[8 (l / 16) + j]
-// [l % 16], j = 0..7, and receives C[4 (l / 16) + r][l % 16], r = 0..3.
+// order (or one more kernel, when the gradient itself is asked for).  Every element of C sums K in
+// ascending steps of 32, whatever the tile and the K-step, so those do not change a bit of it.
+// Operand layouts of the 16x16x32 BF16 MFMA: lane l supplies A[l % 16][8 (l / 16) + j] and
+// B[8 (l / 16) + j][l % 16], j = 0..7, and receives C[4 (l / 16) + r][l % 16], r = 0..3.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -38,8 +45,11 @@ namespace {
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kBM = 64, kBN = 64;   // workgroup tile
+constexpr int kTile = 64;           // workgroup tile (rows and columns); 128 where launch_forward takes it
+constexpr int kThreads = 512;       // of a product's workgroup: 8 wavefronts, 2 across the tile's rows, 4 across its columns
+constexpr int kStages = 4;          // K-steps of operands held in LDS, three of them in flight
 constexpr int kWidthPad = 32;       // widths are padded to multiples of this (the MFMA's K)
 constexpr int kSplitRows = 512;     // K chunk of the weight-gradient products
 
@@ -54,18 +64,20 @@ struct GemmArgs {
     int k_chunk;          // K range of workgroup z: [z k_chunk, (z + 1) k_chunk)
     int n_real;           // columns below n_real get the bias, the transposed and FP32 outputs
     const float* bias;    // [n_real] (forward epilogues)
-    float* Cf;            // FP32 output: Cf[m * ldcf + n] (+ z * part_stride for partials)
+    float* Cf;            // FP32 output: Cf[m * ldcf + n] (+ z * part_stride for partials); the forward's are
+                          // the activation's slopes gelu'(Z), for the backward (null: left out, and with
+                          // them the transposed output)
     long ldcf, part_stride;
     bf16* Cb;             // BF16 row-major output: Cb[m * ldcb + n], n < N
     long ldcb;
     bf16* Ct;             // BF16 transposed output: Ct[n * ldct + m], n < n_real
     long ldct;
-    const float* Z;       // pre-activation Z[m * ldz + n] (backward GELU)
-    long ldz;
+    const float* S;       // the activation's slopes S[m * lds + n] (backward GELU)
+    long lds;
     int nbx, nby, tiles;  // column tiles, row tiles and their product with the K-splits
     // linear output with the loss (T non-null): dY = 2 (Y - T) / (rows n_real) as BF16, row-major
     // dY[m * lddy + n] for n < N (zero beyond n_real and below M beyond `rows`) and transposed
-    // dYt[n * lddyt + m] for n < n_real; the sum of squares of Y - T per row tile in loss_part
+    // dYt[n * lddyt + m] for n < n_real; the sum of squares of Y - T per tile in loss_part
     const float* T;       // targets T[m * n_real + n], m < rows
     bf16* dY;
     long lddy;
@@ -75,107 +87,304 @@ struct GemmArgs {
     int rows;
 };
 
-__device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
+constexpr float kRsqrt2 = 0.70710678118654752f;
 
-__device__ __forceinline__ float gelu_grad(float z) {
-    return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
+// GELU and its slope at z, given e = erf(z / sqrt 2).
+__device__ __forceinline__ float gelu(float z, float e) { return 0.5f * z * (1.0f + e); }
+
+__device__ __forceinline__ float gelu_grad(float z, float e) {
+    return 0.5f * (1.0f + e) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
+}
+
+// e[i] = erff(x[i]) for N values per lane.  erff takes a short polynomial below 1 and a much longer way
+// above; of 64 normally distributed pre-activations a few always lie above, so a wavefront that
+// evaluates value after value takes both ways every time (155 instructions per GELU and slope,
+// half of a product's time).  Here the values from 1 on (a sixth) are queued in LDS without gaps
+// and evaluated 64 at a time.  The results are erff's own either way.  queue: 64 (N + 1) floats of this
+// wavefront's, used by no other.
+template <int N>
+__device__ __forceinline__ void erf_values(const float (&x)[N], float (&e)[N], float* queue) {
+    // a value's place in the queue; one evaluated here writes to and reads from the lane's spare place
+    uint32_t place[N];
+    bool wide[N];
+    const uint32_t spare = 64 * N + (threadIdx.x & 63);
+    int queued = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        wide[i] = !(fabsf(x[i]) < 1.0f);
+        const unsigned long long who = __builtin_amdgcn_ballot_w64(wide[i]);
+        const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)who, (uint32_t)queued));
+        place[i] = wide[i] ? at : spare;
+        queue[place[i]] = x[i];
+        queued += __builtin_popcountll(who);
+        // no branch here either: the values' polynomials overlap
+        float near = wide[i] ? 0.0f : x[i];
+        asm("" : "+v"(near));   // (the compiler does not see that it is below 1 through the selection)
+        __builtin_assume(__builtin_fabsf(near) < 1.0f);
+        e[i] = erff(near);
+    }
+    // one wavefront's LDS accesses execute in order; the compiler is held to it as well
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+    for (int q = (int)(threadIdx.x & 63); q < queued; q += 64) queue[q] = erff(queue[q]);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const float far = queue[place[i]];
+        e[i] = wide[i] ? far : e[i];
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
 }
 
 __device__ __forceinline__ uint32_t pack2(bf16 lo, bf16 hi) {
     return (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
 }
 
-constexpr int kMaxBK = 128;
+// Elements of one operand's LDS: a ring of kStages K-steps of T rows of BK; later, for the GELU epilogues,
+// the tile's FP32 sums at a pitch of T + 4 (A's), its transposed BF16 outputs at a pitch of T + 8 and four
+// wavefronts' queues of erf_values (B's).
+constexpr int kErfPieces = 2;
+template <int BK, int T>
+constexpr int kLdsElems = std::max({kStages * T * BK, 2 * T * (T + 4), T * (T + 8) + kThreads * (4 * kErfPieces + 1) * 2});
 
-// One workgroup's 64 x 64 tile (column tile bx, row tile by, K-split bz) of the product g,
-// staged through As / Bs (two buffers of 64 rows of BK + 8 elements each, at least).
-template <int EPI, int BK>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int bz, bf16* __restrict__ As,
-                                          bf16* __restrict__ Bs) {
-    constexpr int LDK = BK + 8;               // LDS row pitch in elements (16-byte reads stay conflict-free)
+// 16 bytes per lane from global memory (byte offset `from` of `src`) straight into LDS, at byte address
+// lds + AT + 16 * lane; src and lds are uniform over the wavefront.  Counted by vmcnt like any
+// load, in order; no register is written.
+template <int AT>
+__device__ __forceinline__ void load_to_lds(const bf16* src, uint32_t from, uint32_t lds) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(lds), "v"(from), "s"(src), "n"(AT)
+                 : "m0", "scc", "memory");
+}
+
+// Waits until at most `newer` of this wavefront's later loads are still on their way.
+template <int NEWER>
+__device__ __forceinline__ void wait_loads() {
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(NEWER) : "memory");
+}
+
+// One workgroup's T x T tile (column tile bx, row tile by, K-split bz) of the product g, staged
+// through As / Bs (kLdsElems each, at least).
+template <int EPI, int BK, int T>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int bz, bf16* As,
+                                          bf16* Bs) {
     constexpr int CPR = BK / 8;               // 16-byte chunks per tile row
-    constexpr int LOADS = kBM * CPR / 256;    // 16-byte loads per thread per operand per K-step
-    constexpr int BUF = kBM * LDK;            // elements of one buffer
-    static_assert(BK <= kMaxBK, "K-step deeper than the LDS buffers");
+    constexpr int CHUNKS = T * CPR;           // 16-byte pieces of an operand's K-step
+    // loads per thread per K-step: of both operands, or (half a workgroup's worth each) of one
+    constexpr bool SHARED = CHUNKS < kThreads;
+    constexpr int PER = SHARED ? 1 : CHUNKS / kThreads, LOADS = SHARED ? 1 : 2 * PER;
+    constexpr int BUF = T * BK;               // elements of one stage
+    constexpr int FM = T / 32, FN = T / 64;   // MFMA tiles of a wavefront along the rows and the columns
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int m0 = by * kBM, n0 = bx * kBN;
+    const int m0 = by * T, n0 = bx * T;
     const int kbeg = bz * g.k_chunk;
     const int kend = min(g.K, kbeg + g.k_chunk);
     const int nk = (kend - kbeg) / BK;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    const int wm = (wave >> 2) * (T / 2), wn = (wave & 3) * (T / 4);
+    // A direct load writes a wavefront's 64 chunks one after the other, so rows cannot be padded; row
+    // r's chunk c lies in place c ^ turn(r) instead, and the 16 rows that the MFMA operand reads
+    // take together (the same chunk of each) fall into different banks.
+    auto turn = [](int row) { return (row / (16 / CPR)) & (CPR - 1); };
 
-    uint4 ra[LOADS], rb[LOADS];
-    auto gload = [&](int kb) {
+    // rows past the operand's last repeat it: they reach only rows and columns of C that are not stored
+    const bool does_a = !SHARED || wave < kThreads / 128, does_b = !SHARED || !does_a;
+    const int t0 = SHARED ? t & (kThreads / 2 - 1) : t;
+    static_assert(!SHARED || CHUNKS == kThreads / 2, "an operand's K-step is half a workgroup's loads or whole ones");
+    uint32_t oa[PER], ob[PER];   // byte offsets from the tile's first element
 #pragma unroll
-        for (int i = 0; i < LOADS; ++i) {
-            const int c = t + 256 * i, row = c / CPR, kc = (c % CPR) * 8;
-            const int m = m0 + row, n = n0 + row;
-            ra[i] = m < g.M ? *reinterpret_cast<const uint4*>(g.A + (long)m * g.lda + kb + kc) : uint4{0u, 0u, 0u, 0u};
-            rb[i] = n < g.N ? *reinterpret_cast<const uint4*>(g.B + (long)n * g.ldb + kb + kc) : uint4{0u, 0u, 0u, 0u};
+    for (int i = 0; i < PER; ++i) {
+        const int c = t0 + kThreads * i, row = c / CPR, kc = ((c % CPR) ^ turn(row)) * 8;
+        oa[i] = (uint32_t)(min(row, g.M - 1 - m0) * g.lda + kc) * 2u;
+        ob[i] = (uint32_t)(min(row, g.N - 1 - n0) * g.ldb + kc) * 2u;
+    }
+    const bf16* const ga = g.A + (long)m0 * g.lda + kbeg;
+    const bf16* const gb = g.B + (long)n0 * g.ldb + kbeg;
+    const uint32_t la = __builtin_amdgcn_readfirstlane(
+        (uint32_t)(size_t)(__attribute__((address_space(3))) bf16*)As + (uint32_t)((t0 >> 6) * 1024));
+    const uint32_t lb = __builtin_amdgcn_readfirstlane(
+        (uint32_t)(size_t)(__attribute__((address_space(3))) bf16*)Bs + (uint32_t)((t0 >> 6) * 1024));
+    auto gload = [&](auto stage, int it) {
+        constexpr int off = decltype(stage)::value * BUF * 2, more = kThreads * 16;
+        const bf16 *sa = ga + it * BK, *sb = gb + it * BK;
+        if (does_a) load_to_lds<off>(sa, oa[0], la);
+        if (does_b) load_to_lds<off>(sb, ob[0], lb);
+        if constexpr (PER == 2) {
+            load_to_lds<off + more>(sa, oa[1], la);
+            load_to_lds<off + more>(sb, ob[1], lb);
         }
     };
-    auto sstore = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < LOADS; ++i) {
-            const int c = t + 256 * i, row = c / CPR, kc = (c % CPR) * 8;
-            *reinterpret_cast<uint4*>(&As[buf * BUF + row * LDK + kc]) = ra[i];
-            *reinterpret_cast<uint4*>(&Bs[buf * BUF + row * LDK + kc]) = rb[i];
-        }
-    };
+    static_assert(PER <= 2, "loads of a K-step");
 
-    f32x4 acc[2][2];
+    f32x4 acc[FM][FN];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int r16 = lane & 15, k8 = (lane >> 4) * 8;
-    // linear output with the loss: the targets this thread's outputs meet, loaded before the
-    // K-loop so that their latency hides behind it
-    float tgt[2][2][4] = {};
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int r16 = lane & 15, k8 = lane >> 4;
+    // what the epilogue reads beside the sums, loaded before the K-loop, which hides its latency: the
+    // targets of a linear output with the loss (in the MFMA's output layout); for the GELU epilogues,
+    // which work on four adjacent columns of a row at a time, the bias or the activation's slopes
+    constexpr int Q4 = T / 4, ROWS = kThreads / Q4, PASSES = T / ROWS;
+    const int qrow = t / Q4, qcol = t % Q4 * 4;   // this thread's first piece; further ones ROWS rows on
+    float side[FM][FN][4] = {};
+    f32x4 bias4 = f32x4{0.f, 0.f, 0.f, 0.f}, slope4[EPI == kBwdGelu ? PASSES : 1];
     if (EPI == kLinear && g.T) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < FN; ++j) {
                 const int mb = m0 + wm + i * 16 + (lane >> 4) * 4, n = n0 + wn + j * 16 + (lane & 15);
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    if (n < g.n_real && mb + r < g.rows) tgt[i][j][r] = g.T[(long)(mb + r) * g.n_real + n];
+                    if (n < g.n_real && mb + r < g.rows) side[i][j][r] = g.T[(long)(mb + r) * g.n_real + n];
             }
     }
-
-    if (nk > 0) {
-        gload(kbeg);
-        sstore(0);
+    if (EPI == kFwdGelu) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (n0 + qcol + c < g.n_real) bias4[c] = g.bias[n0 + qcol + c];
     }
-    __syncthreads();
-    for (int it = 0; it < nk; ++it) {
-        const int cur = it & 1;
-        if (it + 1 < nk) gload(kbeg + (it + 1) * BK);
+    if constexpr (EPI == kBwdGelu) {
 #pragma unroll
-        for (int ks = 0; ks < BK; ks += 32) {
-            bf16x8 a[2], b[2];
+        for (int q = 0; q < PASSES; ++q) {
+            const int m = min(m0 + qrow + q * ROWS, g.M - 1), n = min(n0 + qcol, g.N - 4);   // outside: unused
+            slope4[q] = *reinterpret_cast<const f32x4*>(g.S + (long)m * g.lds + n);
+        }
+    }
+
+    // operand places in a stage: row r of 16 i + r16 turns alike for every i
+    const int ra = (wm + r16) * BK, rb = (wn + r16) * BK, tn = turn(r16);
+    static_assert(BK * 16 % 128 == 0, "rows 16 apart turn alike");
+    auto step = [&](auto stage, int it) {
+        constexpr int u = decltype(stage)::value;
+        // this wavefront's part of step `it` has arrived once only the newer steps' loads remain ...
+        const int newer = min(nk - 1 - it, kStages - 2);
+        if (newer == 2) wait_loads<2 * LOADS>();
+        else if (newer == 1) wait_loads<LOADS>();
+        else wait_loads<0>();
+        // ... and the others' after the barrier, which also frees the stage of step it - 1
+        __syncthreads();
+        if (it + kStages - 1 < nk) gload(std::integral_constant<int, (u + kStages - 1) % kStages>{}, it + kStages - 1);
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-                a[i] = *reinterpret_cast<const bf16x8*>(&As[cur * BUF + (wm + i * 16 + r16) * LDK + ks + k8]);
+        for (int ks = 0; ks < CPR; ks += 4) {
+            bf16x8 a[FM], b[FN];
+            const int kc = ((ks + k8) ^ tn) * 8;
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                b[j] = *reinterpret_cast<const bf16x8*>(&Bs[cur * BUF + (wn + j * 16 + r16) * LDK + ks + k8]);
+            for (int i = 0; i < FM; ++i)
+                a[i] = *reinterpret_cast<const bf16x8*>(As + ra + kc + (u * BUF + i * 16 * BK));
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int j = 0; j < FN; ++j)
+                b[j] = *reinterpret_cast<const bf16x8*>(Bs + rb + kc + (u * BUF + j * 16 * BK));
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
         }
-        if (it + 1 < nk) sstore(cur ^ 1);
-        __syncthreads();
+    };
+    using S0 = std::integral_constant<int, 0>;
+    using S1 = std::integral_constant<int, 1>;
+    using S2 = std::integral_constant<int, 2>;
+    using S3 = std::integral_constant<int, 3>;
+    if (0 < nk) gload(S0{}, 0);
+    if (1 < nk) gload(S1{}, 1);
+    if (2 < nk) gload(S2{}, 2);
+    for (int it = 0; it < nk; it += kStages) {
+        step(S0{}, it);
+        if (it + 1 < nk) step(S1{}, it + 1);
+        if (it + 2 < nk) step(S2{}, it + 2);
+        if (it + 3 < nk) step(S3{}, it + 3);
     }
+    static_assert(kStages == 4, "the waits and stages above are of a ring of four");
+    __syncthreads();   // the buffers are free
 
+    if constexpr (EPI == kFwdGelu || EPI == kBwdGelu) {
+        // The sums go through LDS, so that a thread has four adjacent columns of a row: every output
+        // leaves in 8- or 16-byte pieces of rows (the transposed ones through LDS once more), and the
+        // activation's code is a short loop (fully unrolled over the MFMA's output layout it was 1,900
+        // instructions executed once: half of the product's time).  M is a multiple of 64, N of 32 (padded
+        // minibatch rows and widths).
+        constexpr int LDC = T + 4, LDT = T + 8;
+        float* const c32 = reinterpret_cast<float*>(As);
+        float* const queue = reinterpret_cast<float*>(Bs + T * LDT) + wave * (64 * (4 * kErfPieces + 1));
+        const bool transposed = EPI == kBwdGelu || g.Cf;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    c32[(wm + i * 16 + (lane >> 4) * 4 + r) * LDC + wn + j * 16 + r16] = acc[i][j][r];
+        __syncthreads();
+        auto put = [&](int q, const bf16 (&h)[4]) {   // piece q's outputs
+            const int row = qrow + q * ROWS, m = m0 + row, n = n0 + qcol;
+            if (m < g.M && n < g.N)
+                *reinterpret_cast<uint2*>(g.Cb + (long)m * g.ldcb + n) = uint2{pack2(h[0], h[1]), pack2(h[2], h[3])};
+            if (transposed) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) Bs[(qcol + c) * LDT + row] = h[c];
+            }
+        };
+        if constexpr (EPI == kBwdGelu) {
+#pragma unroll
+            for (int q = 0; q < PASSES; ++q) {
+                const f32x4 sum = *reinterpret_cast<const f32x4*>(c32 + (qrow + q * ROWS) * LDC + qcol);
+                bf16 h[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) h[c] = (bf16)(sum[c] * slope4[q][c]);
+                put(q, h);
+            }
+        } else {
+            constexpr int G = kErfPieces;   // pieces whose values go through erf_values together
+#pragma unroll 1
+            for (int q0 = 0; q0 < PASSES; q0 += G) {
+                float z[4 * G], x[4 * G], e[4 * G];
+#pragma unroll
+                for (int q = 0; q < G; ++q) {
+                    const f32x4 sum = *reinterpret_cast<const f32x4*>(c32 + (qrow + (q0 + q) * ROWS) * LDC + qcol);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        z[4 * q + c] = sum[c] + bias4[c];
+                        x[4 * q + c] = z[4 * q + c] * kRsqrt2;
+                    }
+                }
+                erf_values(x, e, queue);
+#pragma unroll
+                for (int q = 0; q < G; ++q) {
+                    bf16 h[4];
+                    f32x4 s;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) h[c] = (bf16)gelu(z[4 * q + c], e[4 * q + c]);
+                    put(q0 + q, h);
+                    const int m = m0 + qrow + (q0 + q) * ROWS, n = n0 + qcol;
+                    if (!g.Cf) continue;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) s[c] = gelu_grad(z[4 * q + c], e[4 * q + c]);
+                    if (m < g.M && n < g.N) *reinterpret_cast<f32x4*>(g.Cf + (long)m * g.ldcf + n) = s;
+                }
+            }
+        }
+        if (!transposed) return;
+        __syncthreads();
+        constexpr int CPT = T / 8;
+#pragma unroll
+        for (int q = 0; q < T * CPT / kThreads; ++q) {
+            const int c = t + kThreads * q, row = c / CPT, col = (c % CPT) * 8;
+            if (n0 + row < g.n_real && m0 + col < g.M)
+                *reinterpret_cast<u32x4*>(g.Ct + (long)(n0 + row) * g.ldct + m0 + col) =
+                    *reinterpret_cast<const u32x4*>(&Bs[row * LDT + col]);
+        }
+        return;
+    }
     double lsum = 0.0;   // linear output with the loss: this thread's squares of Y - T
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < FN; ++j) {
             const int mb = m0 + wm + i * 16 + (lane >> 4) * 4;   // rows mb .. mb + 3
             const int n = n0 + wn + j * 16 + (lane & 15);
             if (n >= g.N) continue;
@@ -185,72 +394,120 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     if (mb + r < g.M) out[(long)(mb + r) * g.ldcf + n] = acc[i][j][r];
-            } else if (EPI == kLinear) {
-                if (!g.T) {
-                    if (n >= g.n_real) continue;
+            } else if (!g.T) {
+                if (n >= g.n_real) continue;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (mb + r < g.M) g.Cf[(long)(mb + r) * g.ldcf + n] = acc[i][j][r] + g.bias[n];
-                } else {
-                    // M is a multiple of 64 here (padded minibatch rows)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int row = mb + r;
-                        float d = 0.0f;
-                        if (n < g.n_real) {
-                            const float y = acc[i][j][r] + g.bias[n];
-                            g.Cf[(long)row * g.ldcf + n] = y;
-                            if (row < g.rows) {
-                                d = y - tgt[i][j][r];
-                                lsum += (double)d * (double)d;
-                            }
-                        }
-                        // rows * n_real formed in float (one rounding of the exact product, as the
-                        // integer product's conversion would give) cannot overflow 32 bits
-                        const bf16 v = (bf16)(2.0f * d / ((float)g.rows * (float)g.n_real));
-                        g.dY[(long)row * g.lddy + n] = v;
-                        if (n < g.n_real) g.dYt[(long)n * g.lddyt + row] = v;
-                    }
-                }
+                for (int r = 0; r < 4; ++r)
+                    if (mb + r < g.M) g.Cf[(long)(mb + r) * g.ldcf + n] = acc[i][j][r] + g.bias[n];
             } else {
-                // forward / backward GELU: M is a multiple of 64 (padded minibatch rows)
-                bf16 hv[4];
-                const float bn = (EPI == kFwdGelu && n < g.n_real) ? g.bias[n] : 0.0f;
+                // M is a multiple of 64 here (padded minibatch rows)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const long o = (long)(mb + r) * g.ldcb + n;
-                    if (EPI == kFwdGelu) {
-                        const float z = acc[i][j][r] + bn;
-                        g.Cf[(long)(mb + r) * g.ldcf + n] = z;
-                        hv[r] = (bf16)gelu(z);
-                    } else {
-                        hv[r] = (bf16)(acc[i][j][r] * gelu_grad(g.Z[(long)(mb + r) * g.ldz + n]));
+                    const int row = mb + r;
+                    float d = 0.0f;
+                    if (n < g.n_real) {
+                        const float y = acc[i][j][r] + g.bias[n];
+                        g.Cf[(long)row * g.ldcf + n] = y;
+                        if (row < g.rows) {
+                            d = y - side[i][j][r];
+                            lsum += (double)d * (double)d;
+                        }
                     }
-                    g.Cb[o] = hv[r];
+                    // rows * n_real formed in float (one rounding of the exact product, as the
+                    // integer product's conversion would give) cannot overflow 32 bits
+                    const bf16 v = (bf16)(2.0f * d / ((float)g.rows * (float)g.n_real));
+                    g.dY[(long)row * g.lddy + n] = v;
+                    if (n < g.n_real) g.dYt[(long)n * g.lddyt + row] = v;
                 }
-                if (n < g.n_real)
-                    *reinterpret_cast<uint2*>(g.Ct + (long)n * g.ldct + mb) = uint2{pack2(hv[0], hv[1]), pack2(hv[2], hv[3])};
             }
         }
     if (EPI == kLinear && g.T) {
-        // the row tile's loss partial, summed over the workgroup in a fixed order (the K-loop
+        // the tile's loss partial, summed over the workgroup in a fixed order (the K-loop
         // ended with a barrier, so As is free)
         double* red = reinterpret_cast<double*>(As);
         red[t] = lsum;
         __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
+        for (int w = kThreads / 2; w > 0; w >>= 1) {
             if (t < w) red[t] += red[t + w];
             __syncthreads();
         }
-        if (t == 0) g.loss_part[by] = red[0];
+        if (t == 0) g.loss_part[by * g.nbx + bx] = red[0];
     }
 }
 
-template <int EPI, int BK>
-__global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
-    __shared__ __attribute__((aligned(16))) bf16 As[2 * kBM * (BK + 8)];
-    __shared__ __attribute__((aligned(16))) bf16 Bs[2 * kBN * (BK + 8)];
-    gemm_tile<EPI, BK>(g, blockIdx.x, blockIdx.y, blockIdx.z, As, Bs);
+template <int EPI, int BK, int T>
+__global__ void __launch_bounds__(kThreads) gemm_kernel(GemmArgs g) {
+    __shared__ __attribute__((aligned(16))) bf16 As[kLdsElems<BK, T>];
+    __shared__ __attribute__((aligned(16))) bf16 Bs[kLdsElems<BK, T>];
+    gemm_tile<EPI, BK, T>(g, blockIdx.x, blockIdx.y, blockIdx.z, As, Bs);
+}
+
+// The output layer, of at most 16 columns: a wavefront per 16 rows, which loads its operands straight
+// into the MFMA's registers, kThinStages groups of 8 K-steps ahead.  A 64 x 64 tile would be 1/21
+// used and leave a workgroup alone with its loads on 16 of 256 CUs (1024 rows: 11.2 -> 5.2 us).
+// The epilogue is gemm_tile's linear one, a loss partial per 16 rows.
+constexpr int kThinStages = 3;
+
+__global__ void __launch_bounds__(64) thin_linear_kernel(GemmArgs g) {
+    const int lane = threadIdx.x, r16 = lane & 15, k8 = (lane >> 4) * 8;
+    const int m0 = blockIdx.x * 16, mb = m0 + (lane >> 4) * 4, n = r16;
+    const bf16* pa = g.A + (long)(m0 + r16) * g.lda + k8;   // M is a multiple of 64, N of 32
+    const bf16* pb = g.B + (long)r16 * g.ldb + k8;
+    const int nk = g.K / 32, groups = (nk + 7) / 8;
+    bf16x8 a[kThinStages][8], b[kThinStages][8];
+    auto load = [&](int slot, int group) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int k = min(group * 8 + u, nk - 1) * 32;   // past the last step: that one again, unused
+            a[slot][u] = *reinterpret_cast<const bf16x8*>(pa + k);
+            b[slot][u] = *reinterpret_cast<const bf16x8*>(pb + k);
+        }
+    };
+    const float bias = n < g.n_real ? g.bias[n] : 0.0f;
+    float tgt[4] = {};
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (g.T && n < g.n_real && mb + r < g.rows) tgt[r] = g.T[(long)(mb + r) * g.n_real + n];
+#pragma unroll
+    for (int d = 0; d < kThinStages; ++d)
+        if (d < groups) load(d, d);
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int g0 = 0; g0 < groups; g0 += kThinStages)
+#pragma unroll
+        for (int d = 0; d < kThinStages; ++d) {
+            if (g0 + d >= groups) break;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if ((g0 + d) * 8 + u < nk) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[d][u], b[d][u], acc, 0, 0, 0);
+            if (g0 + d + kThinStages < groups) load(d, g0 + d + kThinStages);
+        }
+    if (!g.T) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (n < g.n_real) g.Cf[(long)(mb + r) * g.ldcf + n] = acc[r] + bias;
+        return;
+    }
+    double lsum = 0.0;
+    bf16 v[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = mb + r;
+        float d = 0.0f;
+        if (n < g.n_real) {
+            const float y = acc[r] + bias;
+            g.Cf[(long)row * g.ldcf + n] = y;
+            if (row < g.rows) {
+                d = y - tgt[r];
+                lsum += (double)d * (double)d;
+            }
+        }
+        v[r] = (bf16)(2.0f * d / ((float)g.rows * (float)g.n_real));
+        for (int c = n; c < g.N; c += 16) g.dY[(long)row * g.lddy + c] = c == n ? v[r] : (bf16)0.0f;
+    }
+    if (n < g.n_real)
+        *reinterpret_cast<uint2*>(g.dYt + (long)n * g.lddyt + mb) = uint2{pack2(v[0], v[1]), pack2(v[2], v[3])};
+    for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, 64);
+    if (lane == 0) g.loss_part[blockIdx.x] = lsum;
 }
 
 // Two independent products in one launch (the backward's weight gradient of a layer and the
@@ -258,16 +515,16 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
 // take g1's tiles, the rest g2's, so both run side by side on the chip without a second
 // stream.  Tiles are numbered column fastest, then row, then split.
 template <int E1, int BK1, int E2, int BK2>
-__global__ void __launch_bounds__(256) gemm_pair_kernel(GemmArgs g1, GemmArgs g2) {
+__global__ void __launch_bounds__(kThreads) gemm_pair_kernel(GemmArgs g1, GemmArgs g2) {
     constexpr int BK = BK1 > BK2 ? BK1 : BK2;
-    __shared__ __attribute__((aligned(16))) bf16 As[2 * kBM * (BK + 8)];
-    __shared__ __attribute__((aligned(16))) bf16 Bs[2 * kBN * (BK + 8)];
+    __shared__ __attribute__((aligned(16))) bf16 As[kLdsElems<BK, kTile>];
+    __shared__ __attribute__((aligned(16))) bf16 Bs[kLdsElems<BK, kTile>];
     int tile = blockIdx.x;
     if (tile < g1.tiles) {
-        gemm_tile<E1, BK1>(g1, tile % g1.nbx, (tile / g1.nbx) % g1.nby, tile / (g1.nbx * g1.nby), As, Bs);
+        gemm_tile<E1, BK1, kTile>(g1, tile % g1.nbx, (tile / g1.nbx) % g1.nby, tile / (g1.nbx * g1.nby), As, Bs);
     } else {
         tile -= g1.tiles;
-        gemm_tile<E2, BK2>(g2, tile % g2.nbx, (tile / g2.nbx) % g2.nby, tile / (g2.nbx * g2.nby), As, Bs);
+        gemm_tile<E2, BK2, kTile>(g2, tile % g2.nbx, (tile / g2.nbx) % g2.nby, tile / (g2.nbx * g2.nby), As, Bs);
     }
 }
 
@@ -379,7 +636,7 @@ struct cronos_mlp_t {
     float* xin = nullptr;              // [rows][sizes[0]] FP32 staging of uploaded inputs
     bf16* x = nullptr;                 // [rows][wp[0]]
     bf16* xt = nullptr;                // [sizes[0] + 1][max_rows], last row ones
-    float* z[3] = {};                  // [rows][wp[l+1]]
+    float* slope[3] = {};              // [rows][wp[l+1]] gelu'(Z_l), kept by the forward for the backward
     bf16* h[3] = {};
     bf16* ht[3] = {};                  // [sizes[l+1] + 1][max_rows], last row ones
     float* y = nullptr;                // [rows][sizes[4]]
@@ -391,6 +648,7 @@ struct cronos_mlp_t {
     float* part_w = nullptr;           // [splits][n_params] split-K partials of the weight gradients
     int grad_splits = 1;               // partials Adam adds (1: the gradient is in grad)
     double* part = nullptr;            // loss partials
+    int loss_parts = 0;                // how many the last forward with the loss left
     // training data
     float* data_x = nullptr;
     float* data_t = nullptr;
@@ -400,49 +658,66 @@ struct cronos_mlp_t {
 
 namespace {
 
-// Tile counts of g over `splits` K-chunks, and the K-step it takes (128, 64 or 32: the
-// deepest that divides K and the chunk).
-int prepare(GemmArgs& g, int splits) {
-    g.nbx = (g.N + kBN - 1) / kBN;
-    g.nby = (g.M + kBM - 1) / kBM;
+// Tile counts of g over `splits` K-chunks, and the K-step it takes (64 or 32: the deeper that
+// divides K and the chunk).
+int prepare(GemmArgs& g, int splits, int tile = kTile) {
+    g.nbx = (g.N + tile - 1) / tile;
+    g.nby = (g.M + tile - 1) / tile;
     g.tiles = g.nbx * g.nby * splits;
     if (splits == 1) g.k_chunk = g.K;
-    if (g.K % 128 == 0 && g.k_chunk % 128 == 0) return 128;
-    if (g.K % 64 == 0 && g.k_chunk % 64 == 0) return 64;
-    return 32;
+    return g.K % 64 == 0 && g.k_chunk % 64 == 0 ? 64 : 32;
 }
 
 template <int EPI>
 hipError_t gemm(hipStream_t st, GemmArgs g, int splits = 1) {
     const int bk = prepare(g, splits);
     const dim3 grid(g.nbx, g.nby, splits);
-    if (bk == 128)
-        hipLaunchKernelGGL((gemm_kernel<EPI, 128>), grid, dim3(256), 0, st, g);
-    else if (bk == 64)
-        hipLaunchKernelGGL((gemm_kernel<EPI, 64>), grid, dim3(256), 0, st, g);
+    if (bk == 64)
+        hipLaunchKernelGGL((gemm_kernel<EPI, 64, kTile>), grid, dim3(kThreads), 0, st, g);
     else
-        hipLaunchKernelGGL((gemm_kernel<EPI, 32>), grid, dim3(256), 0, st, g);
+        hipLaunchKernelGGL((gemm_kernel<EPI, 32, kTile>), grid, dim3(kThreads), 0, st, g);
+    return hipGetLastError();
+}
+
+// A hidden layer's forward product.  A 128 x 128 tile does four times the arithmetic for twice the
+// operand bytes of a 64 x 64 one, but leaves a CU one workgroup where two small ones share it: it pays
+// from about two rounds of small tiles on.  Measured, small / wide (us): 2048 x 768 (384 small tiles)
+// 10.3 / 12.9, 4096 x 768 (768) 14.0 / 14.1, 8192 x 512 (1024) 15.5 / 12.6.
+constexpr int kWideTiles = 1000;
+
+hipError_t launch_forward(hipStream_t st, GemmArgs g) {
+    if (prepare(g, 1) < 64 || g.tiles < kWideTiles) return gemm<kFwdGelu>(st, g);
+    prepare(g, 1, 128);
+    hipLaunchKernelGGL((gemm_kernel<kFwdGelu, 64, 128>), dim3(g.nbx, g.nby), dim3(kThreads), 0, st, g);
+    return hipGetLastError();
+}
+
+// The output layer's product; loss_parts: the loss partials it leaves.
+hipError_t launch_output(hipStream_t st, GemmArgs g, int* loss_parts) {
+    if (g.n_real > 16) {
+        prepare(g, 1);
+        *loss_parts = g.nbx * g.nby;
+        return gemm<kLinear>(st, g);
+    }
+    *loss_parts = g.M / 16;
+    hipLaunchKernelGGL(thin_linear_kernel, dim3(g.M / 16), dim3(64), 0, st, g);
     return hipGetLastError();
 }
 
 template <int E1, int BK1, int E2>
 void launch_pair2(hipStream_t st, const GemmArgs& g1, const GemmArgs& g2, int bk2) {
     const dim3 grid((unsigned)(g1.tiles + g2.tiles));
-    if (bk2 == 128)
-        hipLaunchKernelGGL((gemm_pair_kernel<E1, BK1, E2, 128>), grid, dim3(256), 0, st, g1, g2);
-    else if (bk2 == 64)
-        hipLaunchKernelGGL((gemm_pair_kernel<E1, BK1, E2, 64>), grid, dim3(256), 0, st, g1, g2);
+    if (bk2 == 64)
+        hipLaunchKernelGGL((gemm_pair_kernel<E1, BK1, E2, 64>), grid, dim3(kThreads), 0, st, g1, g2);
     else
-        hipLaunchKernelGGL((gemm_pair_kernel<E1, BK1, E2, 32>), grid, dim3(256), 0, st, g1, g2);
+        hipLaunchKernelGGL((gemm_pair_kernel<E1, BK1, E2, 32>), grid, dim3(kThreads), 0, st, g1, g2);
 }
 
 // g1 over splits1 K-chunks and g2 (one chunk) in one launch.
 template <int E1, int E2>
 hipError_t gemm_pair(hipStream_t st, GemmArgs g1, int splits1, GemmArgs g2) {
     const int bk1 = prepare(g1, splits1), bk2 = prepare(g2, 1);
-    if (bk1 == 128)
-        launch_pair2<E1, 128, E2>(st, g1, g2, bk2);
-    else if (bk1 == 64)
+    if (bk1 == 64)
         launch_pair2<E1, 64, E2>(st, g1, g2, bk2);
     else
         launch_pair2<E1, 32, E2>(st, g1, g2, bk2);
@@ -457,7 +732,7 @@ void free_mlp(cronos_mlp_t* q) {
         ptrs.push_back(q->wt[l]);
     }
     for (int l = 0; l < 3; ++l) {
-        ptrs.push_back(q->z[l]);
+        ptrs.push_back(q->slope[l]);
         ptrs.push_back(q->h[l]);
         ptrs.push_back(q->ht[l]);
         ptrs.push_back(q->dz[l]);
@@ -469,7 +744,8 @@ void free_mlp(cronos_mlp_t* q) {
 }
 
 // Forward over `rows` (<= max_rows, padded to 64) rows already in q->x; with_loss: the output
-// product's epilogue also forms the loss partials and dY from the targets in q->t.
+// product's epilogue also forms the loss partials and dY from the targets in q->t, and the hidden
+// layers keep what the backward products read (the activation's slopes, transposed activations).
 cronos_status forward_dev(cronos_mlp_t* q, int rows, bool with_loss) {
     const int P = (rows + 63) / 64 * 64;
     const long R = q->max_rows;
@@ -485,13 +761,13 @@ cronos_status forward_dev(cronos_mlp_t* q, int rows, bool with_loss) {
         g.K = q->wp[l];
         g.n_real = q->sizes[l + 1];
         g.bias = q->p + q->off_b[l];
-        g.Cf = q->z[l];
+        g.Cf = with_loss ? q->slope[l] : nullptr;
         g.ldcf = q->wp[l + 1];
         g.Cb = q->h[l];
         g.ldcb = q->wp[l + 1];
         g.Ct = q->ht[l];
         g.ldct = R;
-        HIP_TRY(gemm<kFwdGelu>(q->stream, g));
+        HIP_TRY(launch_forward(q->stream, g));
         in = q->h[l];
     }
     GemmArgs g{};
@@ -515,7 +791,7 @@ cronos_status forward_dev(cronos_mlp_t* q, int rows, bool with_loss) {
         g.loss_part = q->part;
         g.rows = rows;
     }
-    HIP_TRY(gemm<kLinear>(q->stream, g));
+    HIP_TRY(launch_output(q->stream, g, &q->loss_parts));
     return CRONOS_OK;
 }
 
@@ -550,7 +826,7 @@ cronos_status backward_dev(cronos_mlp_t* q, int rows, bool sum_grads) {
         }
         if (l == 0) HIP_TRY(gemm<kPartial>(q->stream, g, splits));
         if (l) {
-            // dZ_{l-1} = (dZ_l W_l^T) * gelu'(Z_{l-1}) : (P x wp[l+1]) (wp[l+1] x wp[l])
+            // dZ_{l-1} = (dZ_l W_l^T) * gelu'(Z_{l-1}), the slopes as the forward left them : (P x wp[l+1]) (wp[l+1] x wp[l])
             GemmArgs d{};
             d.A = dnext;
             d.lda = q->wp[l + 1];
@@ -564,8 +840,8 @@ cronos_status backward_dev(cronos_mlp_t* q, int rows, bool sum_grads) {
             d.ldcb = q->wp[l];
             d.Ct = q->dzt[l - 1];
             d.ldct = R;
-            d.Z = q->z[l - 1];
-            d.ldz = q->wp[l];
+            d.S = q->slope[l - 1];
+            d.lds = q->wp[l];
             // both read dZ_l only: one launch for the pair
             HIP_TRY((gemm_pair<kPartial, kBwdGelu>(q->stream, g, splits, d)));
             dnext = q->dz[l - 1];
@@ -611,7 +887,7 @@ cronos_status adam_dev(cronos_mlp_t* q, double lr, double b1, double b2, double 
 }
 
 double loss_from_parts(cronos_mlp_t* q, int rows, cronos_status* st) {
-    const int nb = (rows + 63) / 64;   // one partial per 64-row tile of the output product
+    const int nb = q->loss_parts;
     std::vector<double> h(nb);
     *st = CRONOS_OK;
     if (hipMemcpyAsync(h.data(), q->part, nb * sizeof(double), hipMemcpyDeviceToHost, q->stream) != hipSuccess ||
@@ -685,7 +961,7 @@ extern "C" cronos_status cronos_mlp_create(const int32_t* sizes, const double* p
         HIP_TRY(dmalloc(&q->x, R * q->wp[0]));
         HIP_TRY(dmalloc(&q->xt, (sizes[0] + 1) * R));
         for (int l = 0; l < 3; ++l) {
-            HIP_TRY(dmalloc(&q->z[l], R * q->wp[l + 1]));
+            HIP_TRY(dmalloc(&q->slope[l], R * q->wp[l + 1]));
             HIP_TRY(dmalloc(&q->h[l], R * q->wp[l + 1]));
             HIP_TRY(dmalloc(&q->ht[l], (sizes[l + 1] + 1) * R));
             HIP_TRY(dmalloc(&q->dz[l], R * q->wp[l + 1]));
