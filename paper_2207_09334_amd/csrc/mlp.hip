@@ -558,20 +558,83 @@ __device__ __forceinline__ void write_shadow(const ShadowMap& s, long i, float v
 
 // Adam on the FP32 master copy; refreshes the BF16 shadows of the weight entries.  The
 // gradient is the sum of `splits` partial gradients laid out like the parameters, `stride`
-// apart, added in split order (the order splitk_sum_kernel uses).
-__global__ void adam_kernel(float* p, float* m, float* v, const float* grad, int splits, long stride, ShadowMap sm,
-                            long n, float lr, float b1, float b2, float eps, float c1, float c2) {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float gi = grad[i];
-    for (int z = 1; z < splits; ++z) gi += grad[z * stride + i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-    p[i] = pi;
-    write_shadow(sm, i, pi);
+// apart, added in split order (the order splitk_sum_kernel uses).  A workgroup takes 32 rows by 64
+// columns of one layer's weights, so that both shadows are written along their rows (the transposed one through
+// LDS), or, after the tiles, one layer's biases.  Memory-bound: 36 B a parameter with two
+// splits; 1.26 M parameters 15.9 -> 13.3 us (one thread per parameter, a 64-bit division for its row
+// and column and a transposed shadow scattered 2 bytes at a time).
+struct AdamMap {
+    ShadowMap s;
+    int first[5];   // first workgroup of each layer's tiles; first[4]: of the biases
+};
+
+__global__ void __launch_bounds__(256)
+adam_kernel(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v, const float* __restrict__ grad,
+            int splits, long stride, AdamMap a, float lr, float b1, float b2, float eps, float c1, float c2) {
+    constexpr int TK = 32, PER = TK * 64 / 256;
+    __shared__ __attribute__((aligned(16))) bf16 tile[64][TK + 8];   // [n][k]
+    const int t = threadIdx.x;
+    int blk = blockIdx.x;
+    auto update = [&](long i, float gi, float mi, float vi, float pi) {
+        mi = b1 * mi + (1.0f - b1) * gi;
+        vi = b2 * vi + (1.0f - b2) * gi * gi;
+        m[i] = mi;
+        v[i] = vi;
+        pi = pi - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+        p[i] = pi;
+        return pi;
+    };
+    if (blk >= a.first[4]) {
+        const int l = blk - a.first[4];
+        for (int n = t; n < a.s.N[l]; n += 256) {
+            const long i = a.s.off_b[l] + n;
+            float gi = grad[i];
+            for (int z = 1; z < splits; ++z) gi += grad[z * stride + i];
+            update(i, gi, m[i], v[i], p[i]);
+        }
+        return;
+    }
+    int l = 0;
+    while (l < 3 && blk >= a.first[l + 1]) ++l;
+    blk -= a.first[l];
+    const int K = a.s.K[l], N = a.s.N[l], Kp = a.s.Kp[l], Np = a.s.Np[l];
+    const int tn = (N + 63) / 64, k0 = blk / tn * TK, n0 = blk % tn * 64;
+    const int nl = t & 63, n = n0 + nl;
+    // every load first: a thread's elements would otherwise wait for memory one after the other
+    float gi[PER], mi[PER], vi[PER], pi[PER];
+    const long i0 = a.s.off_w[l] + (long)(k0 + (t >> 6)) * N + n, di = 4l * N;
+    const int have = n < N ? (min(K - k0, TK) - (t >> 6) + 3) / 4 : 0;   // this thread's rows: t / 64, + 4, ...
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (u < have) {
+            const long i = i0 + u * di;
+            gi[u] = grad[i];
+            mi[u] = m[i];
+            vi[u] = v[i];
+            pi[u] = p[i];
+        }
+    for (int z = 1; z < splits; ++z)
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (u < have) gi[u] += grad[z * stride + i0 + u * di];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int kl = (t >> 6) + 4 * u;
+        bf16 w = (bf16)0.0f;
+        if (u < have) {
+            w = (bf16)update(i0 + u * di, gi[u], mi[u], vi[u], pi[u]);
+            a.s.w[l][(long)(k0 + kl) * Np + n] = w;
+        }
+        tile[nl][kl] = w;
+    }
+    __syncthreads();
+    // 16-byte pieces of the transposed tile's rows
+    const int r = t >> 2, c = (t & 3) * 8;
+    bf16* const to = a.s.wt[l] + (long)(n0 + r) * Kp + k0 + c;
+    if (n0 + r >= N) return;
+    if (k0 + c + 8 <= K) *reinterpret_cast<u32x4*>(to) = *reinterpret_cast<const u32x4*>(&tile[r][c]);
+    else
+        for (int u = 0; u < 8 && k0 + c + u < K; ++u) to[u] = tile[r][c + u];
 }
 
 __global__ void shadow_kernel(const float* p, ShadowMap sm, long n) {
@@ -580,19 +643,34 @@ __global__ void shadow_kernel(const float* p, ShadowMap sm, long n) {
 }
 
 // Minibatch rows r < padded_rows: X_b[r][c] = bf16(X[src][c]) (zero beyond n_in and beyond
-// `rows`), X_t[c][r] for c < n_in, T_b[r] = T[src]; src = idx[r], or r when idx is NULL.
-__global__ void gather_kernel(const float* X, const float* T, const int* idx, bf16* Xb, long ldx, bf16* Xt, long ldt,
-                              float* Tb, int rows, int padded_rows, int n_in, int n_out) {
-    const int r = blockIdx.x;
-    if (r >= padded_rows) return;
-    const long src = r < rows ? (idx ? (long)idx[r] : (long)r) : -1;
-    for (int c = threadIdx.x; c < ldx; c += blockDim.x) {
-        const bf16 v = (src >= 0 && c < n_in) ? (bf16)X[src * n_in + c] : (bf16)0.0f;
-        Xb[(long)r * ldx + c] = v;
-        if (c < n_in) Xt[(long)c * ldt + r] = v;
-    }
-    if (T)
-        for (int c = threadIdx.x; c < n_out; c += blockDim.x) Tb[(long)r * n_out + c] = src >= 0 ? T[src * n_out + c] : 0.0f;
+// `rows`), X_t[c][r] for c < n_in (X_t null: left out), T_b[r] = T[src]; src = idx[r], or r when idx is
+// NULL.  A workgroup takes 16 rows (padded_rows is a multiple of 64) and 64 columns and turns them
+// in LDS.
+__global__ void __launch_bounds__(256)
+gather_kernel(const float* __restrict__ X, const float* __restrict__ T, const int* __restrict__ idx,
+              bf16* __restrict__ Xb, int ldx, bf16* __restrict__ Xt, long ldt, float* __restrict__ Tb, int rows,
+              int n_in, int n_out) {
+    __shared__ __attribute__((aligned(16))) bf16 turned[64][24];
+    const int t = threadIdx.x, r0 = blockIdx.x * 16, rl = t >> 4, r = r0 + rl;
+    auto from = [&](int row) { return row < rows ? (idx ? (long)idx[row] : (long)row) : -1; };
+    const long src = from(r);
+    const int cl = (t & 15) * 4, c0 = blockIdx.y * 64, c = c0 + cl;
+    bf16 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = (src >= 0 && c + u < n_in) ? (bf16)X[src * n_in + c + u] : (bf16)0.0f;
+    if (c < ldx) *reinterpret_cast<uint2*>(Xb + (long)r * ldx + c) = uint2{pack2(v[0], v[1]), pack2(v[2], v[3])};
+    if (T && blockIdx.y == 0)
+        for (int q = t; q < 16 * n_out; q += 256) {
+            const long s = from(r0 + q / n_out);
+            Tb[(long)r0 * n_out + q] = s >= 0 ? T[s * n_out + q % n_out] : 0.0f;
+        }
+    if (!Xt) return;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) turned[cl + u][rl] = v[u];
+    __syncthreads();
+    const int cc = t >> 1, h = (t & 1) * 8;
+    if (t < 128 && c0 + cc < n_in)
+        *reinterpret_cast<u32x4*>(Xt + (long)(c0 + cc) * ldt + r0 + h) = *reinterpret_cast<const u32x4*>(&turned[cc][h]);
 }
 
 __global__ void fill_kernel(bf16* p, long n, float v) {
@@ -654,6 +732,8 @@ struct cronos_mlp_t {
     float* data_t = nullptr;
     int* idx = nullptr;
     long data_rows = 0;
+    double* epoch_part = nullptr;      // loss partials of the last epoch's minibatches
+    size_t epoch_part_cap = 0;
 };
 
 namespace {
@@ -726,7 +806,7 @@ hipError_t gemm_pair(hipStream_t st, GemmArgs g1, int splits1, GemmArgs g2) {
 
 void free_mlp(cronos_mlp_t* q) {
     std::vector<void*> ptrs = {q->p, q->m, q->v, q->grad, q->xin, q->x, q->xt, q->y, q->t, q->dy, q->dyt, q->part_w,
-                               q->part, q->data_x, q->data_t, q->idx};
+                               q->part, q->data_x, q->data_t, q->idx, q->epoch_part};
     for (int l = 0; l < 4; ++l) {
         ptrs.push_back(q->w[l]);
         ptrs.push_back(q->wt[l]);
@@ -746,7 +826,8 @@ void free_mlp(cronos_mlp_t* q) {
 // Forward over `rows` (<= max_rows, padded to 64) rows already in q->x; with_loss: the output
 // product's epilogue also forms the loss partials and dY from the targets in q->t, and the hidden
 // layers keep what the backward products read (the activation's slopes, transposed activations).
-cronos_status forward_dev(cronos_mlp_t* q, int rows, bool with_loss) {
+// loss_part: where the loss partials go (q->loss_parts of them).
+cronos_status forward_dev(cronos_mlp_t* q, int rows, bool with_loss, double* loss_part) {
     const int P = (rows + 63) / 64 * 64;
     const long R = q->max_rows;
     const bf16* in = q->x;
@@ -788,7 +869,7 @@ cronos_status forward_dev(cronos_mlp_t* q, int rows, bool with_loss) {
         g.lddy = q->wp[4];
         g.dYt = q->dyt;
         g.lddyt = R;
-        g.loss_part = q->part;
+        g.loss_part = loss_part;
         g.rows = rows;
     }
     HIP_TRY(launch_output(q->stream, g, &q->loss_parts));
@@ -859,10 +940,11 @@ cronos_status backward_dev(cronos_mlp_t* q, int rows, bool sum_grads) {
 }
 
 // Rows of the minibatch from device arrays (idx == nullptr: the first `rows` rows in order).
-cronos_status gather_rows(cronos_mlp_t* q, const float* X, const float* T, const int* idx, int rows) {
+// backward: the transposed rows as well, which only the backward reads.
+cronos_status gather_rows(cronos_mlp_t* q, const float* X, const float* T, const int* idx, int rows, bool backward) {
     const int P = (rows + 63) / 64 * 64;
-    hipLaunchKernelGGL(gather_kernel, dim3(P), dim3(128), 0, q->stream, X, T, idx, q->x, (long)q->wp[0], q->xt,
-                       (long)q->max_rows, q->t, rows, P, q->sizes[0], q->sizes[4]);
+    hipLaunchKernelGGL(gather_kernel, dim3(P / 16, (q->wp[0] + 63) / 64), dim3(256), 0, q->stream, X, T, idx, q->x, q->wp[0],
+                       backward ? q->xt : nullptr, (long)q->max_rows, q->t, rows, q->sizes[0], q->sizes[4]);
     HIP_TRY(hipGetLastError());
     return CRONOS_OK;
 }
@@ -872,18 +954,27 @@ cronos_status upload_rows(cronos_mlp_t* q, const float* x, const float* t, int r
     HIP_TRY(hipMemcpyAsync(q->xin, x, (size_t)rows * n_in * sizeof(float), hipMemcpyHostToDevice, q->stream));
     // targets: the loss reads rows below `rows` only
     if (t) HIP_TRY(hipMemcpyAsync(q->t, t, (size_t)rows * n_out * sizeof(float), hipMemcpyHostToDevice, q->stream));
-    return gather_rows(q, q->xin, nullptr, nullptr, rows);
+    return gather_rows(q, q->xin, nullptr, nullptr, rows, t != nullptr);
 }
 
 cronos_status adam_dev(cronos_mlp_t* q, double lr, double b1, double b2, double eps) {
     q->step += 1;
     const float c1 = (float)(1.0 - std::pow(b1, q->step)), c2 = (float)(1.0 - std::pow(b2, q->step));
     const bool parts = q->grad_splits > 1;
-    hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((q->n_params + 255) / 256)), dim3(256), 0, q->stream, q->p, q->m,
-                       q->v, parts ? q->part_w : q->grad, parts ? q->grad_splits : 1, q->n_params, q->smap,
-                       q->n_params, (float)lr, (float)b1, (float)b2, (float)eps, c1, c2);
+    AdamMap a{q->smap, {}};
+    for (int l = 0; l < 4; ++l) a.first[l + 1] = a.first[l] + (q->sizes[l] + 31) / 32 * ((q->sizes[l + 1] + 63) / 64);
+    hipLaunchKernelGGL(adam_kernel, dim3((unsigned)(a.first[4] + 4)), dim3(256), 0, q->stream, q->p, q->m, q->v,
+                       parts ? q->part_w : q->grad, parts ? q->grad_splits : 1, q->n_params, a, (float)lr, (float)b1,
+                       (float)b2, (float)eps, c1, c2);
     HIP_TRY(hipGetLastError());
     return CRONOS_OK;
+}
+
+// The loss of `rows` rows from its partials (host copies).
+double loss_of(const cronos_mlp_t* q, const double* parts, int count, int rows) {
+    double s = 0.0;
+    for (int k = 0; k < count; ++k) s += parts[k];
+    return s / ((double)rows * q->sizes[4]);
 }
 
 double loss_from_parts(cronos_mlp_t* q, int rows, cronos_status* st) {
@@ -895,9 +986,7 @@ double loss_from_parts(cronos_mlp_t* q, int rows, cronos_status* st) {
         *st = fail(CRONOS_EDEVICE, "mlp: loss read-back failed");
         return 0.0;
     }
-    double s = 0.0;
-    for (double v : h) s += v;
-    return s / ((double)rows * q->sizes[4]);
+    return loss_of(q, h.data(), nb, rows);
 }
 
 }  // namespace
@@ -1030,7 +1119,7 @@ extern "C" cronos_status cronos_mlp_forward(cronos_mlp q, const float* x, int64_
         const int r = (int)std::min<int64_t>(q->max_rows, rows - r0);
         cronos_status st = upload_rows(q, x + r0 * q->sizes[0], nullptr, r);
         if (st != CRONOS_OK) return st;
-        st = forward_dev(q, r, false);
+        st = forward_dev(q, r, false, nullptr);
         if (st != CRONOS_OK) return st;
         HIP_TRY(hipMemcpyAsync(y + r0 * n_out, q->y, (size_t)r * n_out * sizeof(float), hipMemcpyDeviceToHost, q->stream));
         HIP_TRY(hipStreamSynchronize(q->stream));
@@ -1044,7 +1133,7 @@ extern "C" cronos_status cronos_mlp_loss_grad(cronos_mlp q, const float* x, cons
     if (!q || !x || !t || rows < 1 || rows > q->max_rows) return fail(CRONOS_EINVAL, "mlp_loss_grad: bad arguments");
     HIP_TRY(hipSetDevice(q->device));
     cronos_status st = upload_rows(q, x, t, rows);
-    if (st == CRONOS_OK) st = forward_dev(q, rows, true);
+    if (st == CRONOS_OK) st = forward_dev(q, rows, true, q->part);
     if (st == CRONOS_OK) st = backward_dev(q, rows, true);
     if (st != CRONOS_OK) return st;
     const double l = loss_from_parts(q, rows, &st);
@@ -1092,37 +1181,63 @@ extern "C" cronos_status cronos_mlp_train(cronos_mlp q, const float* x, const fl
     }
     HIP_TRY(hipMemcpyAsync(q->data_x, x, (size_t)rows * n_in * sizeof(float), hipMemcpyHostToDevice, q->stream));
     HIP_TRY(hipMemcpyAsync(q->data_t, t, (size_t)rows * n_out * sizeof(float), hipMemcpyHostToDevice, q->stream));
-    std::vector<int> perm(rows);
     // learning rate: cosine from lr to lr_final over all minibatch steps (constant if equal)
     const int64_t per_epoch = (rows + batch - 1) / batch, last = std::max<int64_t>(1, per_epoch * epochs - 1);
+    // loss partials of the last epoch, read back once at its end (at most one per 16 padded rows)
+    const size_t parts_cap = (size_t)per_epoch * (size_t)((std::min<int64_t>(batch, rows) + 63) / 64 * 4);
+    if (q->epoch_part_cap < parts_cap) {
+        if (q->epoch_part) (void)hipFree(q->epoch_part);
+        q->epoch_part = nullptr;
+        q->epoch_part_cap = 0;
+        HIP_TRY(hipMalloc((void**)&q->epoch_part, parts_cap * sizeof(double)));
+        q->epoch_part_cap = parts_cap;
+    }
+    // epoch order: Fisher-Yates driven by SplitMix64(seed, epoch, i); the next epoch's is drawn while the
+    // device works on this one
+    std::vector<int> perm[2];
+    auto draw_order = [&](int e) {
+        std::vector<int>& o = perm[e & 1];
+        o.resize(rows);
+        for (int64_t i = 0; i < rows; ++i) o[i] = (int)i;
+        const uint64_t base = splitmix64(seed ^ (0x5851F42D4C957F2Dull * (uint64_t)(e + 1)));
+        for (int64_t i = rows - 1; i > 0; --i) std::swap(o[i], o[(int64_t)(splitmix64(base ^ (uint64_t)i) % (uint64_t)(i + 1))]);
+    };
+    if (epochs > 0) draw_order(0);
     int64_t step = 0;
     for (int e = 0; e < epochs; ++e) {
-        // epoch order: Fisher-Yates driven by SplitMix64(seed, epoch, i)
-        for (int64_t i = 0; i < rows; ++i) perm[i] = (int)i;
-        for (int64_t i = rows - 1; i > 0; --i) {
-            const uint64_t r = splitmix64(splitmix64(seed ^ (0x5851F42D4C957F2Dull * (uint64_t)(e + 1))) ^ (uint64_t)i);
-            std::swap(perm[i], perm[(int64_t)(r % (uint64_t)(i + 1))]);
-        }
-        HIP_TRY(hipMemcpyAsync(q->idx, perm.data(), rows * sizeof(int), hipMemcpyHostToDevice, q->stream));
-        double sum = 0.0;
-        int64_t seen = 0;
+        const bool final_epoch = e == epochs - 1;
+        HIP_TRY(hipMemcpyAsync(q->idx, perm[e & 1].data(), rows * sizeof(int), hipMemcpyHostToDevice, q->stream));
+        std::vector<int> counts;   // loss partials of each of the last epoch's minibatches
+        size_t parts = 0;
         for (int64_t b0 = 0; b0 < rows; b0 += batch) {
             const int r = (int)std::min<int64_t>(batch, rows - b0);
-            cronos_status st = gather_rows(q, q->data_x, q->data_t, q->idx + b0, r);
-            if (st == CRONOS_OK) st = forward_dev(q, r, true);
+            cronos_status st = gather_rows(q, q->data_x, q->data_t, q->idx + b0, r, true);
+            if (st == CRONOS_OK) st = forward_dev(q, r, true, final_epoch ? q->epoch_part + parts : q->part);
             if (st == CRONOS_OK) st = backward_dev(q, r, false);
             const double lr_t = lr_final + 0.5 * (lr - lr_final) * (1.0 + std::cos(M_PI * (double)step++ / (double)last));
             if (st == CRONOS_OK) st = adam_dev(q, lr_t, 0.9, 0.999, 1e-8);
             if (st != CRONOS_OK) return st;
-            if (e == epochs - 1) {
-                const double l = loss_from_parts(q, r, &st);
-                if (st != CRONOS_OK) return st;
-                sum += l * r;
-                seen += r;
+            if (final_epoch) {
+                counts.push_back(q->loss_parts);
+                parts += (size_t)q->loss_parts;
             }
         }
-        HIP_TRY(hipStreamSynchronize(q->stream));   // perm is rewritten next epoch
-        if (e == epochs - 1 && epoch_loss) *epoch_loss = seen ? sum / seen : 0.0;
+        if (!final_epoch) {
+            draw_order(e + 1);
+            HIP_TRY(hipStreamSynchronize(q->stream));   // this epoch's order is rewritten after the next
+            continue;
+        }
+        std::vector<double> h(parts);
+        HIP_TRY(hipMemcpyAsync(h.data(), q->epoch_part, parts * sizeof(double), hipMemcpyDeviceToHost, q->stream));
+        HIP_TRY(hipStreamSynchronize(q->stream));
+        double sum = 0.0;
+        size_t at = 0;
+        for (int64_t b = 0; b < per_epoch; ++b) {
+            const int r = (int)std::min<int64_t>(batch, rows - b * batch);
+            sum += loss_of(q, h.data() + at, counts[b], r) * r;
+            at += (size_t)counts[b];
+        }
+        if (epoch_loss) *epoch_loss = sum / (double)rows;
     }
     return CRONOS_OK;
 }
