@@ -71,6 +71,7 @@ struct DeviceArrays {
     double* chunk_part = nullptr;        // [n_chunks][kDiagFields]
     double* body_out = nullptr;          // [nb][kDiagFields]
     float* fout = nullptr;               // [n][3] force output
+    int32_t* inv = nullptr;              // [n] caller's mass index -> device's
     // structured-box form (see step_grid_kernel): blocks are aligned 8 x 8 x 8 cubes of a full box
     int32_t grid = 0;
     int32_t grid_dim[3] = {0, 0, 0};
@@ -144,6 +145,15 @@ hipError_t launch_adj_group_sums(const double2* sens, const int32_t* grp_ptr, co
 hipError_t launch_actuation_steps(const DeviceArrays& d, unsigned long long cycles, long long n0, int steps,
                                   float* out, long long stride, hipStream_t st);
 hipError_t launch_forces(const DeviceArrays& d, int cur, const StepParams& p, hipStream_t st);
+// State in the caller's mass order, masses [o0, o0 + count), between device arrays and pinned host arrays
+// (three floats a mass, 16-byte aligned): positions and / or a 3-vector array out (unpack) and in
+// (pack, into xo and / or vo; 1/m from `now`, v = 0 for fixed masses).  inv: caller's index -> device's.
+hipError_t launch_unpack(const float4* x, const float* v, const int32_t* inv, float* host_x, float* host_v, int o0,
+                         int count, hipStream_t st);
+hipError_t launch_pack(const float* host_x, const float* host_v, const int32_t* inv, const float4* now, float4* xo,
+                       float* vo, int o0, int count, hipStream_t st);
+// The positions and / or velocities packed into buffer set cur ^ 1 become set cur's, at step `step`.
+hipError_t launch_commit_state(const DeviceArrays& d, int cur, bool x, bool v, long long step, hipStream_t st);
 
 // Lanczos iterations for the natural frequencies (modes.hip), FP64.
 constexpr int kModesNormParts = 512;     // doubles held for the vector kernels' partial norms

@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <fstream>
+#include <limits>
 #include <map>
 #include <mutex>
 #include <new>
@@ -106,15 +107,16 @@ struct cronos_sim_t {
     bool verlet = false;                 // integrator of eqs. (5)-(6): first step kicks dt / 2
     bool half_kick = false;              // the next step is Verlet's first
     hipGraphExec_t graph[2][kGraphLevels] = {};   // [parity][level]: 2^level steps
-    std::vector<float> inv_m;            // new order
     std::vector<uint16_t> h_grp;         // per entry factor index (actuated sims), for the adjoint reduction
     std::vector<double> h_phase, h_amp;  // actuation parameters last set
     double origin[3] = {0.0, 0.0, 0.0};  // absolute position = device position + origin
     double rest_max = 0.0;               // longest nominal rest length
     RolloutBuffers ro;
-    float4* h_x = nullptr;               // pinned staging
-    float* h_v = nullptr;
-    float* h_f = nullptr;
+    // pinned staging of the state's way to and from the host: two buffers of io_masses masses (positions,
+    // then velocities), each with an event
+    float* h_io[2] = {nullptr, nullptr};
+    hipEvent_t io_ev[2] = {nullptr, nullptr};
+    int64_t io_masses = 0;
     double* h_diag = nullptr;
 };
 
@@ -124,7 +126,7 @@ void free_device(cronos_sim_t* s) {
     cronos::DeviceArrays& d = s->d;
     void* ptrs[] = {d.narrow, d.packed, d.table, d.blk_groups, d.sp_rec, d.sp_grp, d.sp_ptr, d.x[0], d.x[1], d.v[0], d.v[1], d.mass, d.fext, d.lane_mass, d.slice_ptr, d.nbr, d.kl, d.grp, d.halo_ptr,
                     d.halo_idx, d.phase, d.amp, d.factor, d.step_ctr, d.chunks, d.body_chunk, d.chunk_part,
-                    d.body_out, d.fout, d.grid_halo, d.grid_org, d.grid_k, d.grid_tab};
+                    d.body_out, d.fout, d.grid_halo, d.grid_org, d.grid_k, d.grid_tab, d.inv};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     for (auto& per : s->graph)
@@ -139,9 +141,10 @@ void free_device(cronos_sim_t* s) {
                   r.xbl[0], r.xbl[1], r.sens, r.grp_ptr, r.grp_entries, r.gsum};
     for (void* p : rp)
         if (p) (void)hipFree(p);
-    if (s->h_x) (void)hipHostFree(s->h_x);
-    if (s->h_v) (void)hipHostFree(s->h_v);
-    if (s->h_f) (void)hipHostFree(s->h_f);
+    for (int b = 0; b < 2; ++b) {
+        if (s->io_ev[b]) (void)hipEventDestroy(s->io_ev[b]);
+        if (s->h_io[b]) (void)hipHostFree(s->h_io[b]);
+    }
     if (s->h_diag) (void)hipHostFree(s->h_diag);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
 }
@@ -755,11 +758,9 @@ extern "C" cronos_status cronos_create(const cronos_desc* d, cronos_sim* out) {
     }
     std::vector<float4> hx(n);
     std::vector<float> hv(3 * n, 0.0f), hm(n), hf;
-    sim->inv_m.resize(n);
     for (int64_t i = 0; i < n; ++i) {
         int32_t o = L.perm[i];
         float im = pin[i] ? 0.0f : (float)(1.0 / mn[i]);
-        sim->inv_m[i] = im;
         hx[i] = make_float4((float)(xn[3 * i] - sim->origin[0]), (float)(xn[3 * i + 1] - sim->origin[1]),
                             (float)(xn[3 * i + 2] - sim->origin[2]), im);
         if (d->v0 && !pin[i])
@@ -1119,6 +1120,7 @@ extern "C" cronos_status cronos_create(const cronos_desc* d, cronos_sim* out) {
         TRY(upload<double>(&D.chunk_part, nullptr, chunks.size() * cronos::kDiagFields));
         TRY(upload<double>(&D.body_out, nullptr, (size_t)sim->nb * cronos::kDiagFields));
         TRY(upload<float>(&D.fout, nullptr, 3 * n));
+        TRY(upload(&D.inv, L.inv.data(), n));
         if (use_grid) {
             TRY(upload(&D.grid_halo, gridh.halo.data(), gridh.halo.size()));
             TRY(upload(&D.grid_org, gridh.org.data(), gridh.org.size()));
@@ -1267,27 +1269,58 @@ extern "C" cronos_status cronos_step(cronos_sim sim, int64_t n_steps) {
     return CRONOS_OK;
 }
 
+namespace {
+
+// Masses per staging buffer: the device fills (or empties) one while the host converts the other.
+constexpr int64_t kIoChunk = 65536;
+
+cronos_status ensure_io(cronos_sim_t* s) {
+    s->io_masses = (std::min(s->d.n, kIoChunk) + 3) / 4 * 4;   // keeps both halves 16-byte aligned
+    for (int b = 0; b < 2; ++b) {
+        if (b == 1 && s->d.n <= s->io_masses) break;
+        if (!s->h_io[b]) HIP_TRY(hipHostMalloc((void**)&s->h_io[b], 6 * s->io_masses * sizeof(float), 0));
+        if (!s->io_ev[b]) HIP_TRY(hipEventCreateWithFlags(&s->io_ev[b], hipEventDisableTiming));
+    }
+    return CRONOS_OK;
+}
+
+// Device positions dx and a 3-vector array dv (with their host arrays; either pair may be null) to the
+// caller's order in FP64.
+cronos_status read_arrays(cronos_sim_t* s, const float4* dx, const float* dv, double* x, double* v) {
+    TRY(ensure_io(s));
+    const int64_t n = s->d.n, C = s->io_masses;
+    auto launch = [&](int64_t o0) -> cronos_status {
+        const int b = (int)(o0 / C & 1);
+        HIP_TRY(cronos::launch_unpack(dx, dv, s->d.inv, s->h_io[b], s->h_io[b] + 3 * C, (int)o0,
+                                      (int)std::min(C, n - o0), s->stream));
+        if (n > C) HIP_TRY(hipEventRecord(s->io_ev[b], s->stream));
+        return CRONOS_OK;
+    };
+    if (n > 0 && (dx || dv)) TRY(launch(0));
+    if (n > C && (dx || dv)) TRY(launch(C));
+    for (int64_t o0 = 0; o0 < n && (dx || dv); o0 += C) {
+        const int b = (int)(o0 / C & 1);
+        const int64_t m = std::min(C, n - o0);
+        HIP_TRY(n > C ? hipEventSynchronize(s->io_ev[b]) : hipStreamSynchronize(s->stream));
+        const float *hx = s->h_io[b], *hv = hx + 3 * C;
+        if (x)
+            for (int64_t i = 0; i < m; ++i)
+                for (int c = 0; c < 3; ++c) x[3 * (o0 + i) + c] = (double)hx[3 * i + c] + s->origin[c];
+        if (v)
+            for (int64_t i = 0; i < 3 * m; ++i) v[3 * o0 + i] = hv[i];
+        if (o0 + 2 * C < n) TRY(launch(o0 + 2 * C));
+    }
+    return CRONOS_OK;
+}
+
+}  // namespace
+
 extern "C" cronos_status cronos_read_state(cronos_sim sim, double* x, double* v, int64_t* step) {
     cronos::clear_error();
     if (!sim) return fail(CRONOS_EINVAL, "read_state: NULL handle");
-    const int64_t n = sim->d.n;
     HIP_TRY(hipSetDevice(sim->device));
-    if (!sim->h_x) HIP_TRY(hipHostMalloc((void**)&sim->h_x, n * sizeof(float4), 0));
-    if (!sim->h_v) HIP_TRY(hipHostMalloc((void**)&sim->h_v, 3 * n * sizeof(float), 0));
-    if (x) HIP_TRY(hipMemcpyAsync(sim->h_x, sim->d.x[sim->cur], n * sizeof(float4), hipMemcpyDeviceToHost, sim->stream));
-    if (v) HIP_TRY(hipMemcpyAsync(sim->h_v, sim->d.v[sim->cur], 3 * n * sizeof(float), hipMemcpyDeviceToHost, sim->stream));
-    HIP_TRY(hipStreamSynchronize(sim->stream));
-    const cronos::Layout& L = sim->lay;
-    for (int64_t i = 0; i < n; ++i) {
-        int32_t o = L.perm[i];
-        if (x) {
-            x[3 * o + 0] = (double)sim->h_x[i].x + sim->origin[0];
-            x[3 * o + 1] = (double)sim->h_x[i].y + sim->origin[1];
-            x[3 * o + 2] = (double)sim->h_x[i].z + sim->origin[2];
-        }
-        if (v)
-            for (int c = 0; c < 3; ++c) v[3 * o + c] = sim->h_v[3 * i + c];
-    }
+    TRY(read_arrays(sim, x ? sim->d.x[sim->cur] : nullptr, v ? sim->d.v[sim->cur] : nullptr, x, v));
+    if (!x && !v) HIP_TRY(hipStreamSynchronize(sim->stream));
     if (step) *step = sim->step;
     return CRONOS_OK;
 }
@@ -1296,31 +1329,39 @@ extern "C" cronos_status cronos_set_state(cronos_sim sim, const double* x, const
     cronos::clear_error();
     if (!sim) return fail(CRONOS_EINVAL, "set_state: NULL handle");
     if (step < 0) return fail(CRONOS_EINVAL, "set_state: step < 0");
-    const int64_t n = sim->d.n;
-    const cronos::Layout& L = sim->lay;
     HIP_TRY(hipSetDevice(sim->device));
     HIP_TRY(hipStreamSynchronize(sim->stream));
-    if (x) {
-        std::vector<float4> hx(n);
-        for (int64_t i = 0; i < n; ++i) {
-            int32_t o = L.perm[i];
-            for (int c = 0; c < 3; ++c)
-                if (!std::isfinite(x[3 * o + c])) return fail(CRONOS_EINVAL, "set_state: non-finite x");
-            hx[i] = make_float4((float)(x[3 * o] - sim->origin[0]), (float)(x[3 * o + 1] - sim->origin[1]),
-                                (float)(x[3 * o + 2] - sim->origin[2]), sim->inv_m[i]);
+    TRY(ensure_io(sim));
+    const int64_t n = sim->d.n, C = sim->io_masses;
+    cronos::DeviceArrays& D = sim->d;
+    // into the other buffer set first (the next step overwrites it anyway): a non-finite position found
+    // on the way leaves the state as it was
+    for (int64_t o0 = 0; o0 < n && (x || v); o0 += C) {
+        const int b = (int)(o0 / C & 1);
+        const int64_t m = std::min(C, n - o0);
+        if (o0 >= 2 * C) HIP_TRY(hipEventSynchronize(sim->io_ev[b]));
+        float *hx = sim->h_io[b], *hv = hx + 3 * C;
+        if (x) {
+            unsigned bad = 0;
+            for (int64_t i = 0; i < m; ++i)
+                for (int c = 0; c < 3; ++c) {
+                    const double w = x[3 * (o0 + i) + c];
+                    bad |= !(std::fabs(w) <= std::numeric_limits<double>::max());
+                    hx[3 * i + c] = (float)(w - sim->origin[c]);
+                }
+            if (bad) {
+                HIP_TRY(hipStreamSynchronize(sim->stream));
+                return fail(CRONOS_EINVAL, "set_state: non-finite x");
+            }
         }
-        HIP_TRY(hipMemcpy(sim->d.x[sim->cur], hx.data(), n * sizeof(float4), hipMemcpyHostToDevice));
+        if (v)
+            for (int64_t i = 0; i < 3 * m; ++i) hv[i] = (float)v[3 * o0 + i];
+        HIP_TRY(cronos::launch_pack(hx, hv, D.inv, D.x[sim->cur], x ? D.x[sim->cur ^ 1] : nullptr,
+                                    v ? D.v[sim->cur ^ 1] : nullptr, (int)o0, (int)m, sim->stream));
+        if (n > C) HIP_TRY(hipEventRecord(sim->io_ev[b], sim->stream));
     }
-    if (v) {
-        std::vector<float> hv(3 * n);
-        for (int64_t i = 0; i < n; ++i) {
-            int32_t o = L.perm[i];
-            for (int c = 0; c < 3; ++c) hv[3 * i + c] = sim->inv_m[i] == 0.0f ? 0.0f : (float)v[3 * o + c];
-        }
-        HIP_TRY(hipMemcpy(sim->d.v[sim->cur], hv.data(), 3 * n * sizeof(float), hipMemcpyHostToDevice));
-    }
-    long long ctr = step;
-    HIP_TRY(hipMemcpy(sim->d.step_ctr + sim->cur, &ctr, sizeof ctr, hipMemcpyHostToDevice));
+    HIP_TRY(cronos::launch_commit_state(D, sim->cur, x != nullptr, v != nullptr, step, sim->stream));
+    HIP_TRY(hipStreamSynchronize(sim->stream));
     sim->step = step;
     sim->half_kick = sim->verlet;   // Verlet restarts from (x_0, v_0): eq. (5)
     return CRONOS_OK;
@@ -1329,18 +1370,10 @@ extern "C" cronos_status cronos_set_state(cronos_sim sim, const double* x, const
 extern "C" cronos_status cronos_eval_forces(cronos_sim sim, double* f) {
     cronos::clear_error();
     if (!sim || !f) return fail(CRONOS_EINVAL, "eval_forces: NULL argument");
-    const int64_t n = sim->d.n;
     HIP_TRY(hipSetDevice(sim->device));
     if (sim->actuated) HIP_TRY(cronos::launch_actuation(sim->d, sim->cycles, 0, sim->stream, -1, nullptr, sim->cur));
     HIP_TRY(cronos::launch_forces(sim->d, sim->cur, sim->p, sim->stream));
-    if (!sim->h_f) HIP_TRY(hipHostMalloc((void**)&sim->h_f, 3 * n * sizeof(float), 0));
-    HIP_TRY(hipMemcpyAsync(sim->h_f, sim->d.fout, 3 * n * sizeof(float), hipMemcpyDeviceToHost, sim->stream));
-    HIP_TRY(hipStreamSynchronize(sim->stream));
-    for (int64_t i = 0; i < n; ++i) {
-        int32_t o = sim->lay.perm[i];
-        for (int c = 0; c < 3; ++c) f[3 * o + c] = sim->h_f[3 * i + c];
-    }
-    return CRONOS_OK;
+    return read_arrays(sim, nullptr, sim->d.fout, nullptr, f);
 }
 
 namespace {
