@@ -17,7 +17,16 @@ struct StepParams {
     float safe;          // a wavefront whose masses all have |x_c| >= safe on every axis takes
                          // the plain difference (Sterbenz-exact for springs shorter than safe/2)
     double ox, oy, oz;   // origin of the device coordinates: absolute x = device x + o
-    unsigned long long cycles = 0;   // actuation: frac(f dt) * 2^64, the period fraction per step
+};
+
+// What cronos_set_actuation changes besides phases and amplitudes, in device memory: a graph of
+// steps holds its launches' arguments, so a step that takes these from memory follows a new
+// actuation without being captured again (capturing the 16 graphs of the 12.7k-mass quadruped
+// anew cost 0.9 ms of every call; the call now takes 0.04 ms).
+struct ActuationState {
+    unsigned long long cycles;   // frac(f dt) * 2^64, the period fraction per step
+    float safe;                  // StepParams::safe for the longest rest length this actuation reaches
+    float unused;
 };
 
 // Device-resident layout and state of one simulation (all arrays in Morton order).
@@ -63,6 +72,7 @@ struct DeviceArrays {
     float* factor = nullptr;             // 1 + A sin(...) per (body, group), FP32
     long long* step_ctr = nullptr;       // [2] device step counter pair: slot cur holds the step
                                          // index of x[cur]; a launch reads slot cur, writes cur ^ 1
+    ActuationState* act = nullptr;       // follows the counter pair in its allocation
     // diagnostics
     int32_t n_chunks = 0;
     int32_t nb = 1;
@@ -118,7 +128,7 @@ hipError_t persistent_grid(const DeviceArrays& d, int exact, int* grid);
 // cur ^ 1 when advance != 0), or for the explicit step n_explicit >= 0 (counters untouched).
 // cycles = frac(f dt) * 2^64, the part of an actuation period that one step advances, in
 // 64-bit fixed point.  out (optional) receives the factors instead of the simulation's table.
-hipError_t launch_actuation(const DeviceArrays& d, unsigned long long cycles, int advance, hipStream_t st,
+hipError_t launch_actuation(const DeviceArrays& d, int advance, hipStream_t st,
                             long long n_explicit = -1, float* out = nullptr, int cur = 0);
 // Adjoint of one step (see kernels.hip).
 hipError_t launch_adj_local(const DeviceArrays& d, const float4* x, const float* vstar, const float* xb1,

@@ -431,7 +431,7 @@ struct StepArgs {
     const float* __restrict__ amp;
     const long long* step_in;
     long long* step_out;
-    unsigned long long cycles;
+    const ActuationState* act;
 };
 
 // Difference mode of a wavefront (uniform across it).  A coordinate at least `safe` away from
@@ -528,7 +528,7 @@ __device__ __forceinline__ void integrate(const StepParams& p, float dtv, float4
 // damping, symplectic Euler, fixed masses.
 template <bool ACT, bool EXACT, int BATCH, int MODE, bool STAGE = false>
 __device__ __forceinline__ void step_block(float4* __restrict__ sx, const StepArgs& a, const StepParams& p, int b,
-                                           long long n_step) {
+                                           float u, float safe) {
     constexpr bool TABLE = MODE != kExplicit;
     const int base = b * a.block;
     const uint32_t tbase = table_base(a.lds_slots);
@@ -540,7 +540,6 @@ __device__ __forceinline__ void step_block(float4* __restrict__ sx, const StepAr
         if (ACT) {
             const int2 bg = a.blk_groups[b];
             if (a.fuse) {   // the same formula as actuation_kernel, for this workgroup's factors only
-                const float u = period_fraction(n_step, a.cycles);
                 for (int q = threadIdx.x; q <= bg.y; q += a.block)
                     sf[q] = q ? actuation_factor(a.amp[bg.x + q - 1], a.phase[bg.x + q - 1], u) : 1.0f;
             } else {
@@ -565,12 +564,12 @@ __device__ __forceinline__ void step_block(float4* __restrict__ sx, const StepAr
         prefetch_entries(se, s, a.nslice, a.slice_ptr, a.packed);
         const int r0 = a.sp_ptr[b];
         spring_pass<ACT, EXACT, BATCH>(sx, tbase, sf, sfac, a.sp_rec + r0, ACT ? a.sp_grp + r0 : nullptr,
-                                       a.sp_ptr[b + 1] - r0, a.block, p.safe);
+                                       a.sp_ptr[b + 1] - r0, a.block, safe);
         __syncthreads();
         gather_split<BATCH>(tbase + (uint32_t)(reinterpret_cast<char*>(sfac) - reinterpret_cast<char*>(st)), xi, se,
                             fx, fy, fz);
     } else {
-        const int mode = EXACT ? difference_mode(xi, p.safe) : kPlain;
+        const int mode = EXACT ? difference_mode(xi, safe) : kPlain;
         if (MODE == kNarrow) {   // passive only (the host never picks it for actuation)
             if (mode == kPlain)
                 gather_narrow<kPlain, BATCH>(tbase, xi, s, a.nslice, a.slice_ptr, a.narrow, a.narrow_tb, fx, fy, fz);
@@ -642,9 +641,13 @@ __device__ __forceinline__ void step_block(float4* __restrict__ sx, const StepAr
 }
 
 // A fused-actuation launch hands the next one its step index through the other slot of the
-// counter pair (the next launch reads that slot; the kernel boundary orders the two).
-__device__ __forceinline__ void advance_step(const StepArgs& a, long long n_step) {
+// counter pair (the next launch reads that slot; the kernel boundary orders the two).  Returns
+// this step's fraction of an actuation period.
+__device__ __forceinline__ float advance_step(const StepArgs& a) {
+    const long long n_step = *a.step_in;
+    const unsigned long long cycles = a.act->cycles;   // both reads before the store: scalar loads
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.step_out = n_step + 1;
+    return period_fraction(n_step, cycles);
 }
 
 template <bool ACT, bool EXACT, int BATCH, int MODE, bool STAGE = false>
@@ -652,9 +655,9 @@ __global__ void __launch_bounds__(1024) step_kernel(StepArgs a, StepParams p) {
     extern __shared__ float4 sx[];
     constexpr bool FUSABLE = ACT && MODE != kExplicit;
     const int b = logical_block(a.nblk);
-    const long long n_step = FUSABLE && a.fuse ? *a.step_in : 0;
-    if (FUSABLE && a.fuse) advance_step(a, n_step);
-    if (b < a.nblk) step_block<ACT, EXACT, BATCH, MODE, STAGE>(sx, a, p, b, n_step);
+    const float safe = ACT ? a.act->safe : p.safe;
+    const float u = FUSABLE && a.fuse ? advance_step(a) : 0.0f;
+    if (b < a.nblk) step_block<ACT, EXACT, BATCH, MODE, STAGE>(sx, a, p, b, u, safe);
 }
 
 // Several lanes per mass (LPM = 2 or 4; compact table forms): lane j of a mass's group walks its
@@ -798,8 +801,8 @@ __global__ void __launch_bounds__(1024) step_lanes_kernel(StepArgs a, StepParams
                  "s"(NARROW ? (const void*)a.narrow : (const void*)a.packed), "s"(a.table), "s"(a.n), "s"(a.nblk),
                  "s"(a.nslice), "s"(a.block), "s"(a.n_table), "s"(a.lds_slots));
     const int b = logical_block(a.nblk);
-    const long long n_step = ACT && a.fuse ? *a.step_in : 0;
-    if (ACT && a.fuse) advance_step(a, n_step);
+    const float safe = ACT ? a.act->safe : p.safe;
+    const float u = ACT && a.fuse ? advance_step(a) : 0.0f;
     if (b >= a.nblk) return;
     const int t = (int)threadIdx.x, nt = (int)blockDim.x;
     const int m = t / LPM, sub = t % LPM;
@@ -831,7 +834,6 @@ __global__ void __launch_bounds__(1024) step_lanes_kernel(StepArgs a, StepParams
     if (ACT) {
         const int2 bg = a.blk_groups[b];
         if (a.fuse) {
-            const float u = period_fraction(n_step, a.cycles);
             for (int q = t; q <= bg.y; q += nt)
                 sf[q] = q ? actuation_factor(a.amp[bg.x + q - 1], a.phase[bg.x + q - 1], u) : 1.0f;
         } else {
@@ -844,7 +846,7 @@ __global__ void __launch_bounds__(1024) step_lanes_kernel(StepArgs a, StepParams
     __syncthreads();
     const float4 xi = sx[own];
     float fx, fy, fz;
-    const int mode = EXACT ? difference_mode(xi, p.safe) : kPlain;
+    const int mode = EXACT ? difference_mode(xi, safe) : kPlain;
     if (mode == kPlain)
         gather_lanes<ACT, kPlain, LPM, NARROW>(tbase, sf, xi, sub, a.narrow_tb, rows, fx, fy, fz);
     else if (mode == kExactZ)
@@ -870,12 +872,12 @@ __global__ void __launch_bounds__(1024) step_persistent(StepArgs a, StepParams p
     const int xcd = (int)(blockIdx.x & 7u);
     const int stride = (int)(gridDim.x >> 3);
     constexpr bool FUSABLE = ACT && MODE != kExplicit;
-    const long long n_step = FUSABLE && a.fuse ? *a.step_in : 0;
-    if (FUSABLE && a.fuse) advance_step(a, n_step);
+    const float safe = ACT ? a.act->safe : p.safe;
+    const float u = FUSABLE && a.fuse ? advance_step(a) : 0.0f;
     for (int j = (int)(blockIdx.x >> 3); j < per; j += stride) {
         const int b = xcd * per + j;
         if (b >= a.nblk) break;
-        step_block<ACT, EXACT, BATCH, MODE, STAGE>(sx, a, p, b, n_step);
+        step_block<ACT, EXACT, BATCH, MODE, STAGE>(sx, a, p, b, u, safe);
         __syncthreads();  // LDS is restaged for the next block
     }
 }
@@ -990,11 +992,11 @@ forces_kernel(const float4* __restrict__ xin, const float* __restrict__ mass, co
 // device counter *step_in; with `advance`, one thread stores n + 1 to *step_out, the other
 // slot of the counter pair, which the next launch reads.
 __global__ void __launch_bounds__(256)
-actuation_kernel(const float* __restrict__ phase, const float* __restrict__ amp, unsigned long long cycles,
+actuation_kernel(const float* __restrict__ phase, const float* __restrict__ amp, const ActuationState* __restrict__ act,
                  const long long* step_in, long long* step_out, float* __restrict__ factor, int n_factor, int advance,
                  long long n_explicit) {
     const long long n = n_explicit >= 0 ? n_explicit : *step_in;
-    const float u = period_fraction(n, cycles);
+    const float u = period_fraction(n, act->cycles);
     const int g = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (g < n_factor) factor[g] = actuation_factor(amp[g], phase[g], u);
     else if (g == n_factor) factor[g] = 1.0f;
@@ -1527,7 +1529,7 @@ hipError_t launch_step_io(const DeviceArrays& d, const float4* xin, const float*
     StepArgs a{xin, vin, xout, vout, d.slice_ptr, d.nbr, d.kl, d.grp, d.halo_ptr, d.halo_idx,
                d.lane_mass, factor ? factor : d.factor, d.fext, vstar, d.packed, d.narrow, d.table, d.blk_groups, d.sp_rec, d.sp_grp,
                d.sp_ptr, (int)d.n, (int)d.nblk, (int)d.nslice, d.block, d.n_table, d.lds_slots, d.max_local_groups,
-               d.narrow_tb, fuse, d.phase, d.amp, d.step_ctr + (cur & 1), d.step_ctr + ((cur & 1) ^ 1), p.cycles};
+               d.narrow_tb, fuse, d.phase, d.amp, d.step_ctr + (cur & 1), d.step_ctr + ((cur & 1) ^ 1), d.act};
     const size_t lds = step_lds_bytes(d);
     if (d.lanes > 1 && (mode == kTable || mode == kNarrow)) {
         const bool act = d.grp != nullptr, ex = p.exact != 0, nar = mode == kNarrow && !act;
@@ -1586,7 +1588,7 @@ hipError_t launch_resident(const DeviceArrays& d, int cur, const StepParams& p, 
     StepArgs a{d.x[cur], d.v[cur], d.x[cur ^ 1], d.v[cur ^ 1], d.slice_ptr, d.nbr, d.kl, d.grp, d.halo_ptr, d.halo_idx,
                d.lane_mass, d.factor, d.fext, nullptr, d.packed, d.narrow, d.table, d.blk_groups, d.sp_rec, d.sp_grp,
                d.sp_ptr, (int)d.n, (int)d.nblk, (int)d.nslice, d.block, d.n_table, d.lds_slots, d.max_local_groups,
-               d.narrow_tb, 0, d.phase, d.amp, d.step_ctr + (cur & 1), d.step_ctr + ((cur & 1) ^ 1), cycles};
+               d.narrow_tb, 0, d.phase, d.amp, d.step_ctr + (cur & 1), d.step_ctr + ((cur & 1) ^ 1), d.act};
     ResidentArgs r{d.phase, d.amp, cycles, d.step_ctr + (cur & 1), d.step_ctr + ((cur & 1) ^ 1), steps, dtv0,
                    d.resident_staged};
     const size_t lds = step_lds_bytes(d) + (size_t)d.resident_staged * sizeof(uint32_t);
@@ -1622,10 +1624,10 @@ hipError_t persistent_grid(const DeviceArrays& d, int exact, int* grid) {
     return hipSuccess;
 }
 
-hipError_t launch_actuation(const DeviceArrays& d, unsigned long long cycles, int advance, hipStream_t st,
+hipError_t launch_actuation(const DeviceArrays& d, int advance, hipStream_t st,
                             long long n_explicit, float* out, int cur) {
     const unsigned grid = (unsigned)((d.n_factor + 1 + 255) / 256);
-    hipLaunchKernelGGL(actuation_kernel, dim3(grid), dim3(256), 0, st, d.phase, d.amp, cycles, d.step_ctr + (cur & 1),
+    hipLaunchKernelGGL(actuation_kernel, dim3(grid), dim3(256), 0, st, d.phase, d.amp, d.act, d.step_ctr + (cur & 1),
                        d.step_ctr + ((cur & 1) ^ 1), out ? out : d.factor, d.n_factor, n_explicit >= 0 ? 0 : advance,
                        n_explicit);
     return hipGetLastError();

@@ -428,7 +428,7 @@ double omega_max(const cronos::Layout& L, const cronos_desc& d, const std::vecto
 // One step's launches from buffer set s->cur into the other one (s->cur is not flipped).
 cronos_status enqueue_one(cronos_sim_t* s) {
     if (s->actuated && !cronos::fused_actuation(s->d))
-        HIP_TRY(cronos::launch_actuation(s->d, s->cycles, 1, s->stream, -1, nullptr, s->cur));
+        HIP_TRY(cronos::launch_actuation(s->d, 1, s->stream, -1, nullptr, s->cur));
     HIP_TRY(cronos::launch_step(s->d, s->cur, s->p, s->stream));
     return CRONOS_OK;
 }
@@ -530,9 +530,9 @@ cronos_status ensure_graph(cronos_sim_t* s, int par, int level) {
     return CRONOS_OK;
 }
 
-// Every level's graph for both parities, built ahead of the first cronos_step (at creation and
-// whenever the parameters they capture change), so that no step call pays for capture and
-// instantiation.
+// Every level's graph for both parities, built at creation, ahead of the first cronos_step, so that
+// no step call pays for capture and instantiation.  What can change later is read from device
+// memory (phases, amplitudes, ActuationState), so they are captured once.
 cronos_status prepare_graphs(cronos_sim_t* s) {
     if (!s->use_graph || !s->stream || s->d.resident) return CRONOS_OK;
     for (int par = 0; par < 2; ++par)
@@ -540,13 +540,12 @@ cronos_status prepare_graphs(cronos_sim_t* s) {
     return CRONOS_OK;
 }
 
-void drop_graphs(cronos_sim_t* s) {
-    for (auto& per : s->graph)
-        for (auto& g : per)
-            if (g) {
-                (void)hipGraphExecDestroy(g);
-                g = nullptr;
-            }
+// The scalars of the current actuation, for the kernels that read them from device memory.
+cronos_status upload_actuation(cronos_sim_t* s) {
+    static_assert(sizeof(cronos::ActuationState) == 2 * sizeof(long long), "shares the counters' allocation");
+    const cronos::ActuationState act{s->cycles, s->p.safe, 0.0f};
+    HIP_TRY(hipMemcpy(s->d.act, &act, sizeof act, hipMemcpyHostToDevice));
+    return CRONOS_OK;
 }
 
 // ---- autotuner cache: (arch, log2 N, log2 S, actuated, contact) -> launch configuration
@@ -1113,8 +1112,9 @@ extern "C" cronos_status cronos_create(const cronos_desc* d, cronos_sim* out) {
         TRY(upload(&D.factor, ones.data(), ones.size()));
         TRY(upload(&D.phase, zeros.data(), zeros.size()));
         TRY(upload(&D.amp, zeros.data(), zeros.size()));
-        const long long zeros2[2] = {0, 0};
-        TRY(upload(&D.step_ctr, zeros2, 2));
+        const long long zeros4[4] = {0, 0, 0, 0};
+        TRY(upload(&D.step_ctr, zeros4, 4));
+        D.act = reinterpret_cast<cronos::ActuationState*>(D.step_ctr + 2);
         TRY(upload(&D.chunks, chunks.data(), chunks.size()));
         TRY(upload(&D.body_chunk, body_chunk.data(), body_chunk.size()));
         TRY(upload<double>(&D.chunk_part, nullptr, chunks.size() * cronos::kDiagFields));
@@ -1178,7 +1178,8 @@ extern "C" cronos_status cronos_create(const cronos_desc* d, cronos_sim* out) {
     sim->lay.nbr_local.shrink_to_fit();
     sim->lay.entry_csr.clear();
     sim->lay.entry_csr.shrink_to_fit();
-    if ((st = choose_launch_mode(sim, d->flags)) != CRONOS_OK || (st = prepare_graphs(sim)) != CRONOS_OK) {
+    if ((st = upload_actuation(sim)) != CRONOS_OK || (st = choose_launch_mode(sim, d->flags)) != CRONOS_OK ||
+        (st = prepare_graphs(sim)) != CRONOS_OK) {
         free_device(sim);
         delete sim;
         return st;
@@ -1212,16 +1213,14 @@ extern "C" cronos_status cronos_set_actuation(cronos_sim sim, const double* phas
     {
         const double c = freq_hz * sim->dt;
         sim->cycles = (unsigned long long)std::ldexp(c - std::floor(c), 64);
-        sim->p.cycles = sim->cycles;   // the fused step computes its factors from it
     }
     double amax = 0.0;
     for (size_t g = 0; g < m; ++g) amax = std::max(amax, std::fabs(amp[g]));
     sim->p.safe = (float)(4.0 * sim->rest_max * (1.0 + amax));
-    drop_graphs(sim);             // graphs captured the old parameters
-
+    TRY(upload_actuation(sim));
     sim->h_phase.assign(phase, phase + m);
     sim->h_amp.assign(amp, amp + m);
-    return prepare_graphs(sim);
+    return CRONOS_OK;
 }
 
 extern "C" cronos_status cronos_step(cronos_sim sim, int64_t n_steps) {
@@ -1371,7 +1370,7 @@ extern "C" cronos_status cronos_eval_forces(cronos_sim sim, double* f) {
     cronos::clear_error();
     if (!sim || !f) return fail(CRONOS_EINVAL, "eval_forces: NULL argument");
     HIP_TRY(hipSetDevice(sim->device));
-    if (sim->actuated) HIP_TRY(cronos::launch_actuation(sim->d, sim->cycles, 0, sim->stream, -1, nullptr, sim->cur));
+    if (sim->actuated) HIP_TRY(cronos::launch_actuation(sim->d, 0, sim->stream, -1, nullptr, sim->cur));
     HIP_TRY(cronos::launch_forces(sim->d, sim->cur, sim->p, sim->stream));
     return read_arrays(sim, nullptr, sim->d.fout, nullptr, f);
 }
@@ -1446,7 +1445,7 @@ cronos_status check_modes_args(cronos_sim sim, int32_t n_modes, int32_t max_iter
 cronos_status lanczos_frequencies(cronos_sim sim, cronos::ModesBuffers& m, int32_t n_modes, int32_t max_iter, double tol,
                                   uint64_t seed, double* omega, int32_t* n_found, int32_t* iterations) {
     const int64_t n = sim->d.n;
-    if (sim->actuated) HIP_TRY(cronos::launch_actuation(sim->d, sim->cycles, 0, sim->stream, -1, nullptr, sim->cur));
+    if (sim->actuated) HIP_TRY(cronos::launch_actuation(sim->d, 0, sim->stream, -1, nullptr, sim->cur));
     HIP_TRY(cronos::launch_modes_init(sim->d, sim->cur, m, seed, sim->stream));
     std::vector<double> ha(max_iter), hb(max_iter);
     int32_t k = 0, next = std::min<int32_t>(max_iter, std::max<int32_t>(64, 4 * n_modes + 16));
@@ -1562,7 +1561,7 @@ extern "C" cronos_status cronos_diagnostics(cronos_sim sim, cronos_diag* out) {
     if (!sim || !out) return fail(CRONOS_EINVAL, "diagnostics: NULL argument");
     HIP_TRY(hipSetDevice(sim->device));
     const int nb = sim->nb;
-    if (sim->actuated) HIP_TRY(cronos::launch_actuation(sim->d, sim->cycles, 0, sim->stream, -1, nullptr, sim->cur));
+    if (sim->actuated) HIP_TRY(cronos::launch_actuation(sim->d, 0, sim->stream, -1, nullptr, sim->cur));
     HIP_TRY(cronos::launch_diagnostics(sim->d, sim->cur, sim->p, sim->stream));
     if (!sim->h_diag) HIP_TRY(hipHostMalloc((void**)&sim->h_diag, (size_t)nb * cronos::kDiagFields * sizeof(double), 0));
     HIP_TRY(hipMemcpyAsync(sim->h_diag, sim->d.body_out, (size_t)nb * cronos::kDiagFields * sizeof(double),
