@@ -94,6 +94,10 @@ struct DeviceArrays {
     float grid_l0[3] = {};               // rest length per direction kind
 };
 
+// Entries allocated after the last slice of each entry array, so that a batch of up to eight rows
+// may be loaded across a slice's end (their values are not used).
+constexpr int kEntryPad = 8 * 64;
+
 constexpr int kDiagFields = 20;  // ke, pe_s, pe_g, pe_c, p3, mx3, mass, min3, max3, nonfinite
 
 // Byte address of the parameter table in a step workgroup's LDS: after the positions, rounded

@@ -149,9 +149,77 @@ __device__ __forceinline__ int stage_positions(float4* __restrict__ sx, const fl
     return own;
 }
 
+template <int EX, int BATCH>
+constexpr int kPart = EX == kExactAll && BATCH > 2 ? BATCH / 2 : BATCH;
+
+// A lane's entries, row after row of its slice (64 masses; the slice, and so the trip count, is
+// uniform across the wavefront), BATCH rows at a time: each batch is loaded while the one before
+// it is worked on, and the first before the workgroup's positions are staged, since entries depend
+// on nothing in LDS.  A step waits on memory more than it computes, and a slice's five to ten
+// batches were one full latency each when loaded as they were needed (655,000 masses of the
+// 64-robot population: 13.2 -> 11.4 us; the cantilever by 16-bit entries 18.3 -> 17.1, by 32-bit ones
+// 19.7 -> 18.3; the quadruped with one lane per mass 7.7 -> 6.8).
+// The springs are added in row order whatever BATCH is.
+template <class Rows, int BATCH>
+struct RowWalk {
+    Rows rows;
+    int w = 0;   // rows of the slice
+    typename Rows::Item q[BATCH];
+
+    // the first batch; rows past the slice's end are the next slice's or the arrays' padding
+    // (kEntryPad), and never used
+    __device__ __forceinline__ void start(int s, int nslice, const int32_t* __restrict__ slice_ptr) {
+        s = __builtin_amdgcn_readfirstlane(s);
+        if (s >= nslice) return;
+        const int e0 = __builtin_amdgcn_readfirstlane(slice_ptr[s]);
+        w = __builtin_amdgcn_readfirstlane((slice_ptr[s + 1] - e0) >> 6);
+        rows.at(e0 + (int)(threadIdx.x & 63u), w);
+        if (w > 0) fetch(0);
+    }
+    __device__ __forceinline__ void fetch(int r) {
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) q[u] = rows.load(r + u);
+    }
+    // one(item) for every row.  PART: rows whose LDS reads may be in flight together (the
+    // exact-difference loop holds more live values per row; half as many keep its registers, and
+    // so its occupancy, those of the plain one)
+    template <int PART, class One>
+    __device__ __forceinline__ void run(One one) {
+        int r = 0;
+        for (; r + BATCH <= w; r += BATCH) {
+            typename Rows::Item c[BATCH];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) c[u] = q[u];
+            if (r + BATCH < w) fetch(r + BATCH);
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                one(c[u]);
+                if (PART < BATCH && (u + 1) % PART == 0) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        tail<0, BATCH>(w - r, one);
+    }
+    // the last `left` < N rows, q[BASE ...], in straight runs of 4, 2 and 1
+    template <int BASE, int N, class One>
+    __device__ __forceinline__ void tail(int left, One one) {
+        if constexpr (N > 1) {
+            constexpr int H = N / 2;
+            if (left >= H) {
+#pragma unroll
+                for (int u = 0; u < H; ++u) one(q[BASE + u]);
+                tail<BASE + H, H>(left - H, one);
+            } else {
+                tail<BASE, H>(left, one);
+            }
+        }
+    }
+};
+
 // Sum of the spring forces on this lane's mass over its slice entries.  The slice (and so the
 // trip count) is uniform across the wavefront; entries are fetched in batches of BATCH so
 // that several loads are in flight before the first is consumed.
+// (Loading a batch ahead as RowWalk does, three registers a row here, lost: 640,000 masses 30.8 -> 31.5 us,
+// the quadruped's bodies 7.9 -> 8.7 us.)
 template <bool ACT, int EX, int BATCH>
 __device__ __forceinline__ void gather(const float4* __restrict__ sx, float4 xi, int s, int nslice,
                                        const int32_t* __restrict__ slice_ptr,
@@ -232,18 +300,32 @@ __device__ __forceinline__ void decode_entry(uint32_t q, uint32_t tbase, uint32_
     }
 }
 
-template <bool ACT, int EX, int BATCH>
-__device__ __forceinline__ void gather_table(uint32_t tbase, const float* __restrict__ sf, float4 xi, int s,
-                                             int nslice, const int32_t* __restrict__ slice_ptr,
-                                             const uint32_t* __restrict__ packed, float& fx, float& fy, float& fz) {
+template <class T>
+struct CompactRows {
+    const T* __restrict__ words;
+    typedef uint32_t Item;
+    __device__ __forceinline__ void at(int e, int) { words += e; }
+    __device__ __forceinline__ Item load(int r) const { return (uint32_t)words[r * 64]; }
+};
+
+// The same over entries held in LDS, which has no padding: rows past the end repeat the last one.
+struct ResidentRows {
+    const uint32_t* words;
+    int last;
+    typedef uint32_t Item;
+    __device__ __forceinline__ void at(int e, int w) {
+        words += e;
+        last = w - 1;
+    }
+    __device__ __forceinline__ Item load(int r) const { return words[min(r, last) * 64]; }
+};
+
+template <bool ACT, int EX, int BATCH, class Rows>
+__device__ __forceinline__ void gather_table(uint32_t tbase, const float* __restrict__ sf, float4 xi,
+                                             RowWalk<Rows, BATCH>& walk, float& fx, float& fy,
+                                             float& fz) {
     fx = fy = fz = 0.0f;
-    s = __builtin_amdgcn_readfirstlane(s);
-    if (s >= nslice) return;
-    const int lane = threadIdx.x & 63;
-    const int e0 = __builtin_amdgcn_readfirstlane(slice_ptr[s]);
-    const int w = __builtin_amdgcn_readfirstlane((slice_ptr[s + 1] - e0) >> 6);
-    const uint32_t* pp = packed + e0 + lane;
-    auto one = [&](uint32_t q) {
+    walk.template run<kPart<EX, BATCH>>([&](uint32_t q) {
         uint32_t xa, ca, gi;
         decode_entry<ACT>(q, tbase, xa, ca, gi);
         const float4 xj = lds_f4(xa);
@@ -254,35 +336,18 @@ __device__ __forceinline__ void gather_table(uint32_t tbase, const float* __rest
         fx = __builtin_fmaf(fac, dx, fx);
         fy = __builtin_fmaf(fac, dy, fy);
         fz = __builtin_fmaf(fac, dz, fz);
-    };
-    int r = 0;
-    for (; r + BATCH <= w; r += BATCH) {
-        uint32_t q[BATCH];
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) q[u] = pp[(r + u) * 64];
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) one(q[u]);
-    }
-    for (; r < w; ++r) one(pp[r * 64]);
+    });
 }
 
 // The same sum over 16-bit entries (passive simulations whose LDS slots and (k, L0) pairs fit
 // together in 16 bits): neighbour slot << tb | pair index.  Half the entry stream of the
 // 32-bit form, which is most of what a step reads from HBM.
 template <int EX, int BATCH>
-__device__ __forceinline__ void gather_narrow(uint32_t tbase, float4 xi, int s, int nslice,
-                                              const int32_t* __restrict__ slice_ptr,
-                                              const uint16_t* __restrict__ narrow, int tb, float& fx, float& fy,
-                                              float& fz) {
+__device__ __forceinline__ void gather_narrow(uint32_t tbase, float4 xi, RowWalk<CompactRows<uint16_t>, BATCH>& walk,
+                                              int tb, float& fx, float& fy, float& fz) {
     fx = fy = fz = 0.0f;
-    s = __builtin_amdgcn_readfirstlane(s);
-    if (s >= nslice) return;
-    const int lane = threadIdx.x & 63;
-    const int e0 = __builtin_amdgcn_readfirstlane(slice_ptr[s]);
-    const int w = __builtin_amdgcn_readfirstlane((slice_ptr[s + 1] - e0) >> 6);
-    const uint16_t* pp = narrow + e0 + lane;
     const uint32_t tmask = (1u << tb) - 1u;
-    auto one = [&](uint32_t q) {
+    walk.template run<kPart<EX, BATCH>>([&](uint32_t q) {
         const float4 xj = lds_f4((q >> tb) << 4);
         const float4 c = lds_f4(((q & tmask) << 4) | tbase);
         float dx, dy, dz;
@@ -290,16 +355,7 @@ __device__ __forceinline__ void gather_narrow(uint32_t tbase, float4 xi, int s, 
         fx = __builtin_fmaf(fac, dx, fx);
         fy = __builtin_fmaf(fac, dy, fy);
         fz = __builtin_fmaf(fac, dz, fz);
-    };
-    int r = 0;
-    for (; r + BATCH <= w; r += BATCH) {
-        uint32_t q[BATCH];
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) q[u] = pp[(r + u) * 64];
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) one(q[u]);
-    }
-    for (; r < w; ++r) one(pp[r * 64]);
+    });
 }
 
 // Split form of the same sum, in two passes over the workgroup's LDS.
@@ -530,38 +586,56 @@ template <bool ACT, bool EXACT, int BATCH, int MODE, bool STAGE = false>
 __device__ __forceinline__ void step_block(float4* __restrict__ sx, const StepArgs& a, const StepParams& p, int b,
                                            float u, float safe) {
     constexpr bool TABLE = MODE != kExplicit;
-    const int base = b * a.block;
+    const int t = (int)threadIdx.x, base = b * a.block;
     const uint32_t tbase = table_base(a.lds_slots);
     float4* st = reinterpret_cast<float4*>(reinterpret_cast<char*>(sx) + tbase);
     float* sf = reinterpret_cast<float*>(st + a.n_table);
     float* sfac = sf + a.max_local_groups + 1;
-    if (TABLE) {
-        for (int q = threadIdx.x; q < a.n_table; q += a.block) st[q] = a.table[q];
-        if (ACT) {
-            const int2 bg = a.blk_groups[b];
-            if (a.fuse) {   // the same formula as actuation_kernel, for this workgroup's factors only
-                for (int q = threadIdx.x; q <= bg.y; q += a.block)
-                    sf[q] = q ? actuation_factor(a.amp[bg.x + q - 1], a.phase[bg.x + q - 1], u) : 1.0f;
-            } else {
-                for (int q = threadIdx.x; q <= bg.y; q += a.block) sf[q] = q ? a.factor[bg.x + q - 1] : 1.0f;
-            }
-        }
-    }
+    // every load that depends on nothing staged is issued before the first is waited for: the
+    // lane's mass, the first halo index, positions, the first batch of entries, the table's
+    // first part, then what hangs on those
+    const int own = a.lane_mass[base + t];
+    const int h0 = a.halo_ptr[b], h1 = a.halo_ptr[b + 1];
+    const int hj = h0 + t < h1 ? a.halo_idx[h0 + t] : -1;
+    float4 xt = make_float4(0.f, 0.f, 0.f, 0.f), xh = xt, tab = xt;
+    if (base + t < a.n) xt = a.xin[base + t];
+    if (TABLE && t < a.n_table) tab = a.table[t];
+    const int2 bg = TABLE && ACT ? a.blk_groups[b] : make_int2(0, 0);
+    const int s = (base + t) >> 6;
+    SliceEntries se;
+    RowWalk<CompactRows<uint32_t>, BATCH> rt{{a.packed}};
+    RowWalk<CompactRows<uint16_t>, BATCH> rn{{a.narrow}};
+    if (MODE == kSplit) prefetch_entries(se, s, a.nslice, a.slice_ptr, a.packed);
+    else if (MODE == kNarrow) rn.start(s, a.nslice, a.slice_ptr);   // passive only (the host never picks it for actuation)
+    else if (TABLE) rt.start(s, a.nslice, a.slice_ptr);
+    if (hj >= 0) xh = a.xin[hj];
     // velocities read in mass order (one contiguous run), handed to each mass's lane through LDS below
     float vt0 = 0.0f, vt1 = 0.0f, vt2 = 0.0f;
-    if (STAGE && base + (int)threadIdx.x < a.n) {
-        const long q = 3 * (long)(base + (int)threadIdx.x);
+    if (STAGE && base + t < a.n) {
+        const long q = 3 * (long)(base + t);
         vt0 = a.vin[q + 0];
         vt1 = a.vin[q + 1];
         vt2 = a.vin[q + 2];
     }
-    const int own = stage_positions(sx, a.xin, a.halo_ptr, a.halo_idx, a.lane_mass, b, base, a.n, a.block);
+    if (TABLE && ACT) {
+        if (a.fuse) {   // the same formula as actuation_kernel, for this workgroup's factors only
+            for (int q = t; q <= bg.y; q += a.block)
+                sf[q] = q ? actuation_factor(a.amp[bg.x + q - 1], a.phase[bg.x + q - 1], u) : 1.0f;
+        } else {
+            for (int q = t; q <= bg.y; q += a.block) sf[q] = q ? a.factor[bg.x + q - 1] : 1.0f;
+        }
+    }
+    if (TABLE) {
+        if (t < a.n_table) st[t] = tab;
+        for (int q = t + a.block; q < a.n_table; q += a.block) st[q] = a.table[q];
+    }
+    sx[t] = xt;
+    if (hj >= 0) sx[a.block + t] = xh;
+    for (int h = h0 + t + a.block; h < h1; h += a.block) sx[a.block + (h - h0)] = a.xin[a.halo_idx[h]];
+    __syncthreads();
     const float4 xi = sx[own];
     float fx, fy, fz;
-    const int s = (base + (int)threadIdx.x) >> 6;
     if (MODE == kSplit) {
-        SliceEntries se;
-        prefetch_entries(se, s, a.nslice, a.slice_ptr, a.packed);
         const int r0 = a.sp_ptr[b];
         spring_pass<ACT, EXACT, BATCH>(sx, tbase, sf, sfac, a.sp_rec + r0, ACT ? a.sp_grp + r0 : nullptr,
                                        a.sp_ptr[b + 1] - r0, a.block, safe);
@@ -570,19 +644,14 @@ __device__ __forceinline__ void step_block(float4* __restrict__ sx, const StepAr
                             fx, fy, fz);
     } else {
         const int mode = EXACT ? difference_mode(xi, safe) : kPlain;
-        if (MODE == kNarrow) {   // passive only (the host never picks it for actuation)
-            if (mode == kPlain)
-                gather_narrow<kPlain, BATCH>(tbase, xi, s, a.nslice, a.slice_ptr, a.narrow, a.narrow_tb, fx, fy, fz);
-            else if (mode == kExactZ)
-                gather_narrow<kExactZ, BATCH>(tbase, xi, s, a.nslice, a.slice_ptr, a.narrow, a.narrow_tb, fx, fy, fz);
-            else
-                gather_narrow<kExactAll, kExactBatch<BATCH>>(tbase, xi, s, a.nslice, a.slice_ptr, a.narrow, a.narrow_tb,
-                                                             fx, fy, fz);
+        if (MODE == kNarrow) {
+            if (mode == kPlain) gather_narrow<kPlain, BATCH>(tbase, xi, rn, a.narrow_tb, fx, fy, fz);
+            else if (mode == kExactZ) gather_narrow<kExactZ, BATCH>(tbase, xi, rn, a.narrow_tb, fx, fy, fz);
+            else gather_narrow<kExactAll, BATCH>(tbase, xi, rn, a.narrow_tb, fx, fy, fz);
         } else if (TABLE) {
-            if (mode == kPlain) gather_table<ACT, kPlain, BATCH>(tbase, sf, xi, s, a.nslice, a.slice_ptr, a.packed, fx, fy, fz);
-            else if (mode == kExactZ)
-                gather_table<ACT, kExactZ, BATCH>(tbase, sf, xi, s, a.nslice, a.slice_ptr, a.packed, fx, fy, fz);
-            else gather_table<ACT, kExactAll, kExactBatch<BATCH>>(tbase, sf, xi, s, a.nslice, a.slice_ptr, a.packed, fx, fy, fz);
+            if (mode == kPlain) gather_table<ACT, kPlain, BATCH>(tbase, sf, xi, rt, fx, fy, fz);
+            else if (mode == kExactZ) gather_table<ACT, kExactZ, BATCH>(tbase, sf, xi, rt, fx, fy, fz);
+            else gather_table<ACT, kExactAll, BATCH>(tbase, sf, xi, rt, fx, fy, fz);
         } else {
             if (mode == kPlain) gather<ACT, kPlain, BATCH>(sx, xi, s, a.nslice, a.slice_ptr, a.nbr, a.kl, a.grp, a.factor, fx, fy, fz);
             else if (mode == kExactZ)
@@ -897,11 +966,12 @@ __global__ void __launch_bounds__(1024) step_resident(StepArgs a, StepParams p, 
     float* sf = reinterpret_cast<float*>(st + a.n_table);
     const int t = (int)threadIdx.x;
     for (int q = t; q < a.n_table; q += a.block) st[q] = a.table[q];
-    const uint32_t* pk = a.packed;
+    RowWalk<ResidentRows, BATCH> first{{a.packed, 0}};
+    first.start(t >> 6, a.nslice, a.slice_ptr);
     if (STAGED) {
         uint32_t* se = reinterpret_cast<uint32_t*>(sf + a.max_local_groups + 1);
         for (int q = t; q < r.staged; q += a.block) se[q] = a.packed[q];
-        pk = se;
+        first.rows.words = se + (first.rows.words - a.packed);
     }
     sx[t] = t < a.n ? a.xin[t] : make_float4(0.f, 0.f, 0.f, 0.f);
     const int own = a.lane_mass[t];
@@ -915,7 +985,6 @@ __global__ void __launch_bounds__(1024) step_resident(StepArgs a, StepParams p, 
     const long long n0 = *r.step_in;
     const int2 bg = ACT ? a.blk_groups[0] : make_int2(0, 0);
     const float* fext = a.fext && live ? a.fext + 3 * own : nullptr;
-    const int s = t >> 6;
     float4 xo = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int k = 0; k < r.steps; ++k) {
         if (ACT) {
@@ -927,9 +996,10 @@ __global__ void __launch_bounds__(1024) step_resident(StepArgs a, StepParams p, 
         const float4 xi = sx[own];
         float fx, fy, fz;
         const int mode = EXACT ? difference_mode(xi, p.safe) : kPlain;
-        if (mode == kPlain) gather_table<ACT, kPlain, BATCH>(tbase, sf, xi, s, a.nslice, a.slice_ptr, pk, fx, fy, fz);
-        else if (mode == kExactZ) gather_table<ACT, kExactZ, BATCH>(tbase, sf, xi, s, a.nslice, a.slice_ptr, pk, fx, fy, fz);
-        else gather_table<ACT, kExactAll, kExactBatch<BATCH>>(tbase, sf, xi, s, a.nslice, a.slice_ptr, pk, fx, fy, fz);
+        auto walk = first;
+        if (mode == kPlain) gather_table<ACT, kPlain, BATCH>(tbase, sf, xi, walk, fx, fy, fz);
+        else if (mode == kExactZ) gather_table<ACT, kExactZ, BATCH>(tbase, sf, xi, walk, fx, fy, fz);
+        else gather_table<ACT, kExactAll, BATCH>(tbase, sf, xi, walk, fx, fy, fz);
         integrate(p, k == 0 ? r.dtv0 : p.dtv, xi, fx, fy, fz, fext, vx, vy, vz, xo, nullptr);
         __syncthreads();  // every lane has read step k's positions
         if (live) sx[own] = xo;

@@ -149,11 +149,14 @@ void free_device(cronos_sim_t* s) {
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
 }
 
+// `pad` further zero elements follow the array.
 template <typename T>
-cronos_status upload(T** dst, const T* src, size_t count) {
+cronos_status upload(T** dst, const T* src, size_t count, size_t pad = 0) {
     if (count == 0) count = 1;
-    if (hipMalloc((void**)dst, count * sizeof(T)) != hipSuccess) return fail(CRONOS_ENOMEM, "device allocation of %zu bytes failed", count * sizeof(T));
+    const size_t bytes = (count + pad) * sizeof(T);
+    if (hipMalloc((void**)dst, bytes) != hipSuccess) return fail(CRONOS_ENOMEM, "device allocation of %zu bytes failed", bytes);
     if (src) HIP_TRY(hipMemcpy(*dst, src, count * sizeof(T), hipMemcpyHostToDevice));
+    if (pad) HIP_TRY(hipMemset(*dst + count, 0, pad * sizeof(T)));
     return CRONOS_OK;
 }
 
@@ -1078,8 +1081,8 @@ extern "C" cronos_status cronos_create(const cronos_desc* d, cronos_sim* out) {
                     D.narrow_tb = tb;
                 }
             }
-            if (!hnarrow.empty()) TRY(upload(&D.narrow, hnarrow.data(), entries));
-            else if (hsp_rec.empty()) TRY(upload(&D.packed, hpacked.data(), entries));
+            if (!hnarrow.empty()) TRY(upload(&D.narrow, hnarrow.data(), entries, cronos::kEntryPad));
+            else if (hsp_rec.empty()) TRY(upload(&D.packed, hpacked.data(), entries, cronos::kEntryPad));
             std::vector<float4> tab(htable.size());
             for (size_t q = 0; q < htable.size(); ++q) {
                 // (k, L0, L0^2 exactly, as an FP64 value in the last two words)
