@@ -1229,16 +1229,27 @@ __global__ void diag_body_kernel(const double* __restrict__ part, const int32_t*
 // spring sum; adj_gather adds the spring sum with the same LDS-staged incidence walk as the
 // step, and accumulates each actuated spring's sensitivity in FP64, half from each end.
 
-// adj_local for mass i, given its x_bar' (bx, by, bz) and v_bar' (vb1).
-__device__ __forceinline__ void adj_local_one(int i, const float4* __restrict__ x, const float* __restrict__ vstar,
-                                              float bx, float by, float bz, const float* __restrict__ vb1,
+// adj_local for mass i, given its x_bar' (bx, by, bz); v_bar', the position and v* are loaded apart,
+// so that a caller can do so early.
+struct AdjLocalIn {
+    float4 x;
+    float vb[3], vs[2];
+    __device__ __forceinline__ void load(int i, const float4* __restrict__ px, const float* __restrict__ vstar,
+                                         const float* __restrict__ vb1) {
+        x = px[i];
+        for (int c = 0; c < 3; ++c) vb[c] = vb1[3 * i + c];
+        for (int c = 0; c < 2; ++c) vs[c] = vstar[3 * i + c];
+    }
+};
+
+__device__ __forceinline__ void adj_local_one(int i, const AdjLocalIn& in, float bx, float by, float bz,
                                               float4* __restrict__ w, float* __restrict__ vb0,
                                               float* __restrict__ xbl, const StepParams& p) {
-    const float4 xi = x[i];
+    const float4 xi = in.x;
     const float inv_m = xi.w;
-    const float tx = __builtin_fmaf(p.dt, bx, vb1[3 * i + 0]);
-    const float ty = __builtin_fmaf(p.dt, by, vb1[3 * i + 1]);
-    const float tz = __builtin_fmaf(p.dt, bz, vb1[3 * i + 2]);
+    const float tx = __builtin_fmaf(p.dt, bx, in.vb[0]);
+    const float ty = __builtin_fmaf(p.dt, by, in.vb[1]);
+    const float tz = __builtin_fmaf(p.dt, bz, in.vb[2]);
     float gx = p.damp * tx, gy = p.damp * ty, gz = p.damp * tz;
     float zb = 0.0f;
     float wz_contact = 0.0f;
@@ -1255,7 +1266,7 @@ __device__ __forceinline__ void adj_local_one(int i, const float4* __restrict__ 
     if (touching) {
         const float fn = p.ground_k * pen;
         const float c = p.ground_mu * fn * p.dt * inv_m;
-        const float vx = vstar[3 * i + 0], vy = vstar[3 * i + 1];
+        const float vx = in.vs[0], vy = in.vs[1];
         const float sp = __builtin_sqrtf(vx * vx + vy * vy);
         if (sp > c) {
             const float ux = vx / sp, uy = vy / sp;
@@ -1285,122 +1296,251 @@ adj_local_kernel(const float4* __restrict__ x, const float* __restrict__ vstar, 
                  float* __restrict__ xbl, int n, StepParams p) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    adj_local_one(i, x, vstar, xb1[3 * i + 0], xb1[3 * i + 1], xb1[3 * i + 2], vb1, w, vb0, xbl, p);
+    AdjLocalIn in;
+    in.load(i, x, vstar, vb1);
+    adj_local_one(i, in, xb1[3 * i + 0], xb1[3 * i + 1], xb1[3 * i + 2], w, vb0, xbl, p);
 }
 
-// LPM lanes per mass (1, 2 or 4; the simulation's lanes per mass): with more than one, lane j
-// of a mass takes its incidence rows j, j + LPM, ... and the partial sums are combined by the
-// same fixed cross-lane pairing as the step's; each incidence's sensitivity is still
-// accumulated by exactly one lane.  With nx.x set, the mass's x_bar then feeds adj_local of
-// the step before (every input of which is the mass's own), so one launch per reversed step
-// remains; nx.w and nx.xbl must not be the w and xbl this launch reads.
-template <bool ACT, int LPM>
-__global__ void __launch_bounds__(1024)
-adj_gather_kernel(const float4* __restrict__ x, const float4* __restrict__ w, const float* __restrict__ xbl,
-                  float* __restrict__ xb0, const int32_t* __restrict__ slice_ptr, const uint16_t* __restrict__ nbr,
-                  const float2* __restrict__ kl, const uint16_t* __restrict__ grp,
-                  const int32_t* __restrict__ halo_ptr, const int32_t* __restrict__ halo_idx,
-                  const uint16_t* __restrict__ lane_mass, const float* __restrict__ factor,
-                  double2* __restrict__ sens, int n_factor, double cos_t, double sin_t, int n, int nblk, int nslice,
-                  int block, int lds_slots, int stage_factors, StepParams p, AdjNext nx) {
+struct AdjArgs {
+    const float4* __restrict__ x;
+    const float4* __restrict__ w;
+    const float* __restrict__ xbl;
+    float* __restrict__ xb0;
+    const int32_t* __restrict__ slice_ptr;
+    const uint16_t* __restrict__ nbr;
+    const float2* __restrict__ kl;
+    const uint16_t* __restrict__ grp;
+    const int32_t* __restrict__ halo_ptr;
+    const int32_t* __restrict__ halo_idx;
+    const uint16_t* __restrict__ lane_mass;
+    const float* __restrict__ factor;
+    double2* __restrict__ sens;
+    double cos_t, sin_t;
+    int n_factor, n, nblk, nslice, block, lds_slots;
+    int stage_factors;   // the factor table goes through LDS (small tables: no dependent global load)
+};
+
+// What an entry holds for the reverse step: neighbour slot, (k, L0), the index of its factor, and the
+// sensitivity summed so far.
+typedef float adj_pair __attribute__((ext_vector_type(2)));
+typedef double adj_sum __attribute__((ext_vector_type(2)));
+struct AdjEntry {
+    uint32_t slot, g;
+    adj_pair kl;
+    adj_sum acc;
+};
+
+template <bool ACT>
+__device__ __forceinline__ AdjEntry adj_entry(const AdjArgs& a, int e) {
+    AdjEntry q;
+    q.slot = a.nbr[e];
+    q.kl = reinterpret_cast<const adj_pair*>(a.kl)[e];
+    q.g = ACT ? (uint32_t)a.grp[e] : (uint32_t)a.n_factor;
+    if (ACT) q.acc = reinterpret_cast<const adj_sum*>(a.sens)[e];
+    return q;
+}
+
+// One incidence: the spring's tangent stiffness applied to w_j - w_i, and (actuated) the sensitivity
+// of the loss to its rest length, accumulated in FP64.
+template <bool ACT>
+__device__ __forceinline__ void adj_spring(const AdjArgs& a, int e, const AdjEntry& q, float f, float4 xi, float4 wi,
+                                           lds_vec4 xj, lds_vec4 wj, float& ax, float& ay, float& az) {
+    const float l0 = ACT ? q.kl.y * f : q.kl.y;
+    const float dx = xj.x - xi.x, dy = xj.y - xi.y, dz = xj.z - xi.z;
+    const float len2 = dx * dx + dy * dy + dz * dz;
+    if (len2 > 0.0f) {
+        const float len = __builtin_sqrtf(len2);
+        const float il = 1.0f / len;
+        const float nx = dx * il, ny = dy * il, nz = dz * il;
+        const float dwx = wj.x - wi.x, dwy = wj.y - wi.y, dwz = wj.z - wi.z;
+        const float ndw = nx * dwx + ny * dwy + nz * dwz;
+        const float tr = 1.0f - l0 * il;        // delta / l
+        const float k = q.kl.x;
+        ax += k * (nx * ndw + tr * (dwx - nx * ndw));
+        ay += k * (ny * ndw + tr * (dwy - ny * ndw));
+        az += k * (nz * ndw + tr * (dwz - nz * ndw));
+        if (ACT && q.g < (uint32_t)a.n_factor) {
+            const double s = 0.5 * (double)q.kl.y * (double)k * (double)ndw;
+            adj_sum acc = q.acc;
+            acc.x += a.cos_t * s;
+            acc.y += a.sin_t * s;
+            reinterpret_cast<adj_sum*>(a.sens)[e] = acc;
+        }
+    }
+}
+
+__device__ __forceinline__ lds_vec4 vec4_of(float4 v) {
+    const lds_vec4 r = {v.x, v.y, v.z, v.w};
+    return r;
+}
+
+// The step reversed, one lane per mass (bodies that fill the chip by themselves).  With nx.x set, the
+// mass's x_bar then feeds adj_local of the step before (every input of which is the mass's own), so
+// one launch per reversed step remains; nx.w and nx.xbl must not be the w and xbl this launch reads.
+// (x_bar itself is then needed by nobody else.)
+template <bool ACT>
+__global__ void __launch_bounds__(1024) adj_gather_kernel(AdjArgs a, StepParams p, AdjNext nx) {
     extern __shared__ float4 sx[];
-    float4* sw = sx + lds_slots;
-    float* sfac = reinterpret_cast<float*>(sw + lds_slots);   // the factor table, when staged
-    const int b = logical_block(nblk);
-    if (b >= nblk) return;
-    const int base = b * block;
-    const int t = threadIdx.x, nt = (int)blockDim.x;
-    const int m = t / LPM, sub = t % LPM;
-    const float* fac = factor;
-    if (ACT && stage_factors) {   // small tables: one LDS copy per workgroup, no dependent global load
-        for (int q = t; q <= n_factor; q += nt) sfac[q] = factor[q];
-        fac = sfac;   // visible after the barrier below
-    }
-    int own;
-    if constexpr (LPM == 1) {
-        float4 wt = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (base + t < n) wt = w[base + t];
-        sw[t] = wt;
-        const int h0 = halo_ptr[b], h1 = halo_ptr[b + 1];
-        for (int h = h0 + t; h < h1; h += block) sw[block + (h - h0)] = w[halo_idx[h]];
-        own = stage_positions(sx, x, halo_ptr, halo_idx, lane_mass, b, base, n, block);
-    } else {
-        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int q = t; q < block; q += nt) {
-            sx[q] = base + q < n ? x[base + q] : z;
-            sw[q] = base + q < n ? w[base + q] : z;
-        }
-        const int h0 = halo_ptr[b], h1 = halo_ptr[b + 1];
-        for (int h = h0 + t; h < h1; h += nt) {
-            const int j = halo_idx[h];
-            sx[block + (h - h0)] = x[j];
-            sw[block + (h - h0)] = w[j];
-        }
-        __syncthreads();
-        own = lane_mass[base + m];
-    }
+    float4* sw = sx + a.lds_slots;
+    float* sfac = reinterpret_cast<float*>(sw + a.lds_slots);   // the factor table, when staged
+    const int b = logical_block(a.nblk);
+    if (b >= a.nblk) return;
+    const int base = b * a.block, t = (int)threadIdx.x;
+    if (ACT && a.stage_factors)
+        for (int q = t; q <= a.n_factor; q += a.block) sfac[q] = a.factor[q];
+    float4 wt = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (base + t < a.n) wt = a.w[base + t];
+    sw[t] = wt;
+    const int h0 = a.halo_ptr[b], h1 = a.halo_ptr[b + 1];
+    for (int h = h0 + t; h < h1; h += a.block) sw[a.block + (h - h0)] = a.w[a.halo_idx[h]];
+    const int own = stage_positions(sx, a.x, a.halo_ptr, a.halo_idx, a.lane_mass, b, base, a.n, a.block);
     const float4 xi = sx[own];
     const float4 wi = sw[own];
     float ax = 0.f, ay = 0.f, az = 0.f;
-    // one incidence: the spring's tangent stiffness applied to w_j - w_i, and (actuated) the
-    // sensitivity of the loss to its rest length, accumulated in FP64
-    auto one = [&](int e, int slot, float2 c, int g, float f, double2 acc) {
-        const float l0 = ACT ? c.y * f : c.y;
-        const float4 xj = sx[slot];
-        const float4 wj = sw[slot];
-        const float dx = xj.x - xi.x, dy = xj.y - xi.y, dz = xj.z - xi.z;
-        const float len2 = dx * dx + dy * dy + dz * dz;
-        if (len2 > 0.0f) {
-            const float len = __builtin_sqrtf(len2);
-            const float il = 1.0f / len;
-            const float nx = dx * il, ny = dy * il, nz = dz * il;
-            const float dwx = wj.x - wi.x, dwy = wj.y - wi.y, dwz = wj.z - wi.z;
-            const float ndw = nx * dwx + ny * dwy + nz * dwz;
-            const float tr = 1.0f - l0 * il;        // delta / l
-            const float k = c.x;
-            ax += k * (nx * ndw + tr * (dwx - nx * ndw));
-            ay += k * (ny * ndw + tr * (dwy - ny * ndw));
-            az += k * (nz * ndw + tr * (dwz - nz * ndw));
-            if (ACT && g < n_factor) {
-                const double q = 0.5 * (double)c.y * (double)k * (double)ndw;
-                acc.x += cos_t * q;
-                acc.y += sin_t * q;
-                sens[e] = acc;
-            }
-        }
+    auto factor = [&](uint32_t g) {
+        if (!ACT) return 1.0f;
+        if (a.stage_factors) return sfac[g];   // LDS and global memory apart: one pointer to either is a flat load
+        return a.factor[g];
     };
-    const int s = __builtin_amdgcn_readfirstlane((base + (LPM == 1 ? t : m)) >> 6);
-    if (s < nslice) {
-        const int lane = (LPM == 1 ? t : m) & 63;
-        const int e0 = __builtin_amdgcn_readfirstlane(slice_ptr[s]);
-        const int wdt = __builtin_amdgcn_readfirstlane((slice_ptr[s + 1] - e0) >> 6);
-        constexpr int B = LPM == 1 ? 8 : 4;   // rows whose loads are in flight together
-        // this lane's rows: sub, sub + LPM, ... (all rows when LPM == 1)
-        const int rows = (wdt - sub + LPM - 1) / LPM;
+    const int s = __builtin_amdgcn_readfirstlane((base + t) >> 6);
+    if (s < a.nslice) {
+        const int e0 = __builtin_amdgcn_readfirstlane(a.slice_ptr[s]);
+        const int rows = __builtin_amdgcn_readfirstlane((a.slice_ptr[s + 1] - e0) >> 6);
+        const int e = e0 + (t & 63);
+        constexpr int B = 8;   // rows whose loads are in flight together
         int k = 0;
         for (; k + B <= rows; k += B) {
-            int slot[B], g[B];
-            float2 c[B];
+            AdjEntry q[B];
             float f[B];
-            double2 acc[B];
 #pragma unroll
-            for (int u = 0; u < B; ++u) {
-                const int e = e0 + ((k + u) * LPM + sub) * 64 + lane;
-                slot[u] = nbr[e];
-                c[u] = kl[e];
-                g[u] = ACT ? (int)grp[e] : n_factor;
-                if (ACT) acc[u] = sens[e];
-            }
+            for (int u = 0; u < B; ++u) q[u] = adj_entry<ACT>(a, e + (k + u) * 64);
 #pragma unroll
-            for (int u = 0; u < B; ++u) f[u] = ACT ? fac[g[u]] : 1.0f;
+            for (int u = 0; u < B; ++u) f[u] = factor(q[u].g);
 #pragma unroll
-            for (int u = 0; u < B; ++u) one(e0 + ((k + u) * LPM + sub) * 64 + lane, slot[u], c[u], g[u], f[u], acc[u]);
+            for (int u = 0; u < B; ++u)
+                adj_spring<ACT>(a, e + (k + u) * 64, q[u], f[u], xi, wi, vec4_of(sx[q[u].slot]), vec4_of(sw[q[u].slot]),
+                                ax, ay, az);
         }
         for (; k < rows; ++k) {
-            const int e = e0 + (k * LPM + sub) * 64 + lane;
-            const int g = ACT ? (int)grp[e] : n_factor;
-            one(e, nbr[e], kl[e], g, ACT ? fac[g] : 1.0f, ACT ? sens[e] : make_double2(0.0, 0.0));
+            const AdjEntry q = adj_entry<ACT>(a, e + k * 64);
+            adj_spring<ACT>(a, e + k * 64, q, factor(q.g), xi, wi, vec4_of(sx[q.slot]), vec4_of(sw[q.slot]), ax, ay, az);
         }
+    }
+    const int i = base + own;
+    if (i >= a.n) return;
+    const float bx = a.xbl[3 * i + 0] + ax, by = a.xbl[3 * i + 1] + ay, bz = a.xbl[3 * i + 2] + az;
+    if (nx.x) {
+        AdjLocalIn in;
+        in.load(i, nx.x, nx.vstar, nx.vb1);
+        adj_local_one(i, in, bx, by, bz, nx.w, nx.vb0, nx.xbl, p);
+        return;
+    }
+    a.xb0[3 * i + 0] = bx;
+    a.xb0[3 * i + 1] = by;
+    a.xb0[3 * i + 2] = bz;
+}
+
+// The same with LPM lanes per mass (2 or 4; the simulation's lanes per mass): lane j of a mass takes its
+// incidence rows j, j + LPM, ... and the partial sums are combined by the same fixed cross-lane
+// pairing as the step's; each incidence's sensitivity is still accumulated by exactly one lane.
+// Such a launch is a chain of latencies (the quadruped: under one wavefront per SIMD), so every load
+// is issued as early as it can be: the first kAdjPre rows of each lane (at four lanes all rows of a
+// full lattice's masses), the halo, and what adj_local needs, before anything is waited for.
+// The quadruped's launch: 9.7 -> 8.5 us beside the recomputed steps (7.8 -> 7.5 alone).
+constexpr int kAdjPre = 8, kAdjGroup = 4;
+
+template <bool ACT, int LPM>
+__global__ void __launch_bounds__(1024) adj_gather_lanes_kernel(AdjArgs a, StepParams p, AdjNext nx) {
+    extern __shared__ float4 sx[];
+    float4* sw = sx + a.lds_slots;
+    float* sfac = reinterpret_cast<float*>(sw + a.lds_slots);
+    const int b = logical_block(a.nblk);
+    if (b >= a.nblk) return;
+    const int t = (int)threadIdx.x, nt = (int)blockDim.x, base = b * a.block;
+    const int m = t / LPM, sub = t % LPM;
+    const int h0 = a.halo_ptr[b], h1 = a.halo_ptr[b + 1];
+    const int own = a.lane_mass[base + m];
+    const int hj = h0 + t < h1 ? a.halo_idx[h0 + t] : -1;
+    float4 xt = make_float4(0.f, 0.f, 0.f, 0.f), wt = xt, xh = xt, wh = xt;
+    if (t < a.block && base + t < a.n) {
+        xt = a.x[base + t];
+        wt = a.w[base + t];
+    }
+    // this lane's rows: sub, sub + LPM, ...; the slice's last row can be missing in some lanes of a group
+    const int s = __builtin_amdgcn_readfirstlane((base + m) >> 6);
+    int e = 0, rows = 0, count = 0;
+    if (s < a.nslice) {
+        const int e0 = __builtin_amdgcn_readfirstlane(a.slice_ptr[s]);
+        rows = __builtin_amdgcn_readfirstlane((a.slice_ptr[s + 1] - e0) >> 6);
+        count = (rows + LPM - 1) / LPM;
+        e = e0 + (m & 63);
+    }
+    auto at = [&](int k) { return e + min(k * LPM + sub, rows - 1) * 64; };   // past the end: the last row again
+    AdjEntry q[kAdjPre];
+    if (count > 0) {
+#pragma unroll
+        for (int u = 0; u < kAdjPre; ++u)
+            if (u < count) q[u] = adj_entry<ACT>(a, at(u));
+    }
+    if (hj >= 0) {
+        xh = a.x[hj];
+        wh = a.w[hj];
+    }
+    const int i = base + own;
+    const bool mine = sub == 0 && i < a.n;
+    AdjLocalIn in = {};
+    float xb[3] = {};
+    if (mine) {
+        for (int c = 0; c < 3; ++c) xb[c] = a.xbl[3 * i + c];
+        if (nx.x) in.load(i, nx.x, nx.vstar, nx.vb1);
+    }
+    if (ACT && a.stage_factors)
+        for (int r = t; r <= a.n_factor; r += nt) sfac[r] = a.factor[r];
+    if (t < a.block) {   // block * LPM threads: one round
+        sx[t] = xt;
+        sw[t] = wt;
+    }
+    if (hj >= 0) {
+        sx[a.block + t] = xh;
+        sw[a.block + t] = wh;
+    }
+    for (int h = h0 + t + nt; h < h1; h += nt) {
+        const int j = a.halo_idx[h];
+        sx[a.block + (h - h0)] = a.x[j];
+        sw[a.block + (h - h0)] = a.w[j];
+    }
+    __syncthreads();
+    const float4 xi = sx[own], wi = sw[own];
+    float ax = 0.f, ay = 0.f, az = 0.f;
+    // kAdjGroup rows from row k on, their LDS reads together
+    auto group = [&](const AdjEntry* g, int k) {
+        lds_vec4 xj[kAdjGroup], wj[kAdjGroup];
+        float f[kAdjGroup];
+#pragma unroll
+        for (int u = 0; u < kAdjGroup; ++u)
+            if (k + u < count) {
+                xj[u] = vec4_of(sx[g[u].slot]);
+                wj[u] = vec4_of(sw[g[u].slot]);
+                f[u] = 1.0f;
+                if (ACT) {
+                    if (a.stage_factors) f[u] = sfac[g[u].g];
+                    else f[u] = a.factor[g[u].g];
+                }
+            }
+#pragma unroll
+        for (int u = 0; u < kAdjGroup; ++u)
+            if (k + u < count && (k + u) * LPM + sub < rows)
+                adj_spring<ACT>(a, e + ((k + u) * LPM + sub) * 64, g[u], f[u], xi, wi, xj[u], wj[u], ax, ay, az);
+    };
+    int k = 0;
+#pragma unroll
+    for (int u = 0; u < kAdjPre; u += kAdjGroup)
+        if (u < count) group(q + u, u);
+    for (k = kAdjPre; k < count; k += kAdjGroup) {
+#pragma unroll
+        for (int u = 0; u < kAdjGroup; ++u)
+            if (k + u < count) q[u] = adj_entry<ACT>(a, at(k + u));
+        group(q, k);
     }
 #pragma unroll
     for (int o = 1; o < LPM; o <<= 1) {
@@ -1408,13 +1548,15 @@ adj_gather_kernel(const float4* __restrict__ x, const float4* __restrict__ w, co
         ay += __shfl_xor(ay, o, 64);
         az += __shfl_xor(az, o, 64);
     }
-    const int i = base + own;
-    if (sub != 0 || i >= n) return;
-    const float bx = xbl[3 * i + 0] + ax, by = xbl[3 * i + 1] + ay, bz = xbl[3 * i + 2] + az;
-    xb0[3 * i + 0] = bx;
-    xb0[3 * i + 1] = by;
-    xb0[3 * i + 2] = bz;
-    if (nx.x) adj_local_one(i, nx.x, nx.vstar, bx, by, bz, nx.vb1, nx.w, nx.vb0, nx.xbl, p);
+    if (!mine) return;
+    const float bx = xb[0] + ax, by = xb[1] + ay, bz = xb[2] + az;
+    if (nx.x) {
+        adj_local_one(i, in, bx, by, bz, nx.w, nx.vb0, nx.xbl, p);
+        return;
+    }
+    a.xb0[3 * i + 0] = bx;
+    a.xb0[3 * i + 1] = by;
+    a.xb0[3 * i + 2] = bz;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1762,19 +1904,17 @@ hipError_t launch_adj_gather(const DeviceArrays& d, const float4* x, const float
     const size_t lds = 2 * (size_t)d.lds_slots * sizeof(float4) + (stage ? (size_t)(d.n_factor + 1) * sizeof(float) : 0);
     const int lanes = d.lanes == 2 || d.lanes == 4 ? d.lanes : 1;
     const dim3 g(grid_for(d.nblk)), th((unsigned)(d.block * lanes));
-    auto go = [&](auto k) {
-        hipLaunchKernelGGL(k, g, th, lds, st, x, w, xbl, xb0, d.slice_ptr, d.nbr, d.kl, d.grp, d.halo_ptr, d.halo_idx,
-                           d.lane_mass, factor, sens, d.n_factor, cos_t, sin_t, (int)d.n, (int)d.nblk, (int)d.nslice,
-                           d.block, d.lds_slots, stage, p, next);
-    };
+    const AdjArgs a{x, w, xbl, xb0, d.slice_ptr, d.nbr, d.kl, d.grp, d.halo_ptr, d.halo_idx, d.lane_mass, factor, sens,
+                    cos_t, sin_t, d.n_factor, (int)d.n, (int)d.nblk, (int)d.nslice, d.block, d.lds_slots, stage};
+    auto go = [&](auto k) { hipLaunchKernelGGL(k, g, th, lds, st, a, p, next); };
     if (d.grp) {
-        if (lanes == 4) go(adj_gather_kernel<true, 4>);
-        else if (lanes == 2) go(adj_gather_kernel<true, 2>);
-        else go(adj_gather_kernel<true, 1>);
+        if (lanes == 4) go(adj_gather_lanes_kernel<true, 4>);
+        else if (lanes == 2) go(adj_gather_lanes_kernel<true, 2>);
+        else go(adj_gather_kernel<true>);
     } else {
-        if (lanes == 4) go(adj_gather_kernel<false, 4>);
-        else if (lanes == 2) go(adj_gather_kernel<false, 2>);
-        else go(adj_gather_kernel<false, 1>);
+        if (lanes == 4) go(adj_gather_lanes_kernel<false, 4>);
+        else if (lanes == 2) go(adj_gather_lanes_kernel<false, 2>);
+        else go(adj_gather_kernel<false>);
     }
     return hipGetLastError();
 }
