@@ -148,12 +148,16 @@ struct AdjNext {
     float* xbl = nullptr;
 };
 hipError_t launch_adj_gather(const DeviceArrays& d, const float4* x, const float4* w, const float* xbl, float* xb0,
-                             double2* sens, double cos_t, double sin_t, hipStream_t st, const float* factor,
-                             const StepParams& p, const AdjNext& next);
+                             double2* sens, const int4* range, int max_groups, double cos_t, double sin_t, hipStream_t st,
+                             const float* factor, const StepParams& p, const AdjNext& next);
+// Whether the workgroups of launch_adj_gather hold the sums of up to max_groups actuation groups each
+// in LDS (range then gives each block's, see AdjArgs); otherwise range is null and sens holds one
+// sum per entry.
+bool adj_block_sums(const DeviceArrays& d, int max_groups);
 // Per actuation group g: gsum[g] = the sum of the per-entry sensitivities sens[e] over the
-// group's entries grp_entries[grp_ptr[g] .. grp_ptr[g + 1]) (one workgroup per group, a
+// group's entries grp_sums[grp_ptr[g] .. grp_ptr[g + 1]) (one workgroup per group, a
 // fixed summation order).
-hipError_t launch_adj_group_sums(const double2* sens, const int32_t* grp_ptr, const int32_t* grp_entries, int n_groups,
+hipError_t launch_adj_group_sums(const double2* sens, const int32_t* grp_ptr, const int32_t* grp_sums, int n_groups,
                                  double2* gsum, hipStream_t st);
 // Actuation factors of steps n0 .. n0 + steps - 1 in one launch, row k at out + k * stride.
 hipError_t launch_actuation_steps(const DeviceArrays& d, unsigned long long cycles, long long n0, int steps,

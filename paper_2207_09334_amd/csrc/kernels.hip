@@ -1301,6 +1301,15 @@ adj_local_kernel(const float4* __restrict__ x, const float* __restrict__ vstar, 
     adj_local_one(i, in, xb1[3 * i + 0], xb1[3 * i + 1], xb1[3 * i + 2], w, vb0, xbl, p);
 }
 
+// Where the sensitivities of actuated springs (FP64) go.  kAdjBlockSums: every lane sums its springs'
+// in a column of LDS of its own, one row per actuation group of the workgroup's range; the columns
+// are then added in a fixed order and the workgroup's sums, not each entry's, cross the launches.
+// kAdjEntrySums (ranges too wide for that, see adj_block_sums): one sum per entry in memory, read and
+// written by every launch, 32 of the 44 bytes an entry then costs.  Block against entry sums: the
+// quadruped's launch 7.0 against 8.5 us and the sums at the end 2 against 48; 60 reversed steps of 32
+// robots (239k masses) 3.9 against 4.5 ms.
+enum : int { kAdjPassive = 0, kAdjEntrySums = 1, kAdjBlockSums = 2 };
+
 struct AdjArgs {
     const float4* __restrict__ x;
     const float4* __restrict__ w;
@@ -1315,58 +1324,151 @@ struct AdjArgs {
     const uint16_t* __restrict__ lane_mass;
     const float* __restrict__ factor;
     double2* __restrict__ sens;
+    const int4* __restrict__ range;   // kAdjBlockSums: (first group, groups, first sum) of each block
     double cos_t, sin_t;
     int n_factor, n, nblk, nslice, block, lds_slots;
-    int stage_factors;   // the factor table goes through LDS (small tables: no dependent global load)
+    int max_groups;      // kAdjBlockSums: of any block
+    int stage_factors;   // kAdjEntrySums: the factor table goes through LDS (small tables: no dependent global load)
 };
 
-// What an entry holds for the reverse step: neighbour slot, (k, L0), the index of its factor, and the
-// sensitivity summed so far.
+// What an entry holds for the reverse step: neighbour slot, (k, L0), the index of its factor and, with
+// kAdjEntrySums, the sensitivity summed so far.
 typedef float adj_pair __attribute__((ext_vector_type(2)));
 typedef double adj_sum __attribute__((ext_vector_type(2)));
+template <int MODE>
 struct AdjEntry {
     uint32_t slot, g;
     adj_pair kl;
     adj_sum acc;
 };
 
-template <bool ACT>
-__device__ __forceinline__ AdjEntry adj_entry(const AdjArgs& a, int e) {
-    AdjEntry q;
+template <int MODE>
+__device__ __forceinline__ AdjEntry<MODE> adj_entry(const AdjArgs& a, int e) {
+    AdjEntry<MODE> q;
     q.slot = a.nbr[e];
     q.kl = reinterpret_cast<const adj_pair*>(a.kl)[e];
-    q.g = ACT ? (uint32_t)a.grp[e] : (uint32_t)a.n_factor;
-    if (ACT) q.acc = reinterpret_cast<const adj_sum*>(a.sens)[e];
+    q.g = MODE != kAdjPassive ? (uint32_t)a.grp[e] : (uint32_t)a.n_factor;
+    if (MODE == kAdjEntrySums) q.acc = reinterpret_cast<const adj_sum*>(a.sens)[e];
     return q;
 }
 
-// One incidence: the spring's tangent stiffness applied to w_j - w_i, and (actuated) the sensitivity
-// of the loss to its rest length, accumulated in FP64.
-template <bool ACT>
-__device__ __forceinline__ void adj_spring(const AdjArgs& a, int e, const AdjEntry& q, float f, float4 xi, float4 wi,
-                                           lds_vec4 xj, lds_vec4 wj, float& ax, float& ay, float& az) {
-    const float l0 = ACT ? q.kl.y * f : q.kl.y;
-    const float dx = xj.x - xi.x, dy = xj.y - xi.y, dz = xj.z - xi.z;
-    const float len2 = dx * dx + dy * dy + dz * dz;
-    if (len2 > 0.0f) {
-        const float len = __builtin_sqrtf(len2);
-        const float il = 1.0f / len;
-        const float nx = dx * il, ny = dy * il, nz = dz * il;
-        const float dwx = wj.x - wi.x, dwy = wj.y - wi.y, dwz = wj.z - wi.z;
-        const float ndw = nx * dwx + ny * dwy + nz * dwz;
-        const float tr = 1.0f - l0 * il;        // delta / l
-        const float k = q.kl.x;
-        ax += k * (nx * ndw + tr * (dwx - nx * ndw));
-        ay += k * (ny * ndw + tr * (dwy - ny * ndw));
-        az += k * (nz * ndw + tr * (dwz - nz * ndw));
-        if (ACT && q.g < (uint32_t)a.n_factor) {
-            const double s = 0.5 * (double)q.kl.y * (double)k * (double)ndw;
-            adj_sum acc = q.acc;
+// The value of another lane of the same sixteen, by data-parallel primitive CTRL.
+template <int CTRL>
+__device__ __forceinline__ double dpp_double(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// A workgroup's actuation factors and sums, after its positions and adjoint forces in LDS.
+template <int MODE>
+struct AdjGroups {
+    double* column;   // kAdjBlockSums: this thread's, a row of `threads` apart per group
+    float* factor;
+    int first, count, slot, threads;
+    adj_sum old;      // the sum that this lane will add to
+    float early;
+
+    // Sixteen lanes add up a row, so that all rows of a usual range go at once; the first of them
+    // stores it.  (A wavefront per row, the rows one after the other, cost 1 us at the launch's end.)
+    __device__ __forceinline__ int pitch() const { return threads + 16; }   // rows apart in the banks
+    __device__ __forceinline__ void start(const AdjArgs& a, float4* lds, int b) {
+        threads = (int)blockDim.x;
+        if (MODE == kAdjEntrySums) factor = reinterpret_cast<float*>(lds);
+        if (MODE == kAdjBlockSums) {
+            const int4 r = a.range[b];
+            first = r.x;
+            count = r.y;
+            slot = r.z;
+            column = reinterpret_cast<double*>(lds) + threadIdx.x;
+            factor = reinterpret_cast<float*>(reinterpret_cast<double*>(lds) + (a.max_groups + 1) * pitch());
+            const int q = (int)threadIdx.x >> 4;
+            if ((threadIdx.x & 15u) == 0 && q < count) old = reinterpret_cast<const adj_sum*>(a.sens)[slot + q];
+            if ((int)threadIdx.x < count) early = a.factor[first + (int)threadIdx.x];
+        }
+    }
+    // what start loaded, into LDS
+    __device__ __forceinline__ void stage(const AdjArgs& a) {
+        if (MODE == kAdjBlockSums) {
+            if ((int)threadIdx.x < count) factor[threadIdx.x] = early;
+            for (int q = (int)threadIdx.x + threads; q < count; q += threads) factor[q] = a.factor[first + q];
+            for (int q = 0; q < count; ++q) column[q * pitch()] = 0.0;
+        } else if (MODE == kAdjEntrySums) {
+            if (a.stage_factors)
+                for (int q = (int)threadIdx.x; q <= a.n_factor; q += threads) factor[q] = a.factor[q];
+        }
+    }
+    // the factor of an entry's rest length (after the barrier)
+    __device__ __forceinline__ float of(const AdjArgs& a, uint32_t g) const {
+        if (MODE == kAdjPassive) return 1.0f;
+        if (MODE == kAdjBlockSums) return g < (uint32_t)a.n_factor ? factor[(int)g - first] : 1.0f;
+        if (a.stage_factors) return factor[g];   // LDS and global memory apart: one pointer to either is a flat load
+        return a.factor[g];
+    }
+    // s counts where `use` is set and the spring is actuated
+    __device__ __forceinline__ void add(const AdjArgs& a, int e, uint32_t g, adj_sum acc, bool use, double s) {
+        use = use && g < (uint32_t)a.n_factor;
+        if (MODE == kAdjBlockSums) {
+            // one lane per column, so the order is the lane's own; the row after the last takes what does not count
+            typedef __attribute__((address_space(3))) double* lds_double;
+            (void)__builtin_amdgcn_ds_atomic_fadd_f64((lds_double)(column + (use ? (int)g - first : count) * pitch()), s);
+        } else if (use) {
             acc.x += a.cos_t * s;
             acc.y += a.sin_t * s;
             reinterpret_cast<adj_sum*>(a.sens)[e] = acc;
         }
     }
+    // every thread of the workgroup
+    __device__ __forceinline__ void finish(const AdjArgs& a) {
+        if (MODE != kAdjBlockSums) return;
+        __syncthreads();
+        const int part = (int)(threadIdx.x & 15u), per = threads >> 4;
+        const double* rows = column - threadIdx.x;
+        for (int r0 = 0; r0 < count; r0 += per) {
+            const int r = r0 + ((int)threadIdx.x >> 4);
+            double v = 0.0;
+            if (r < count)
+                for (int c = part; c < threads; c += 16) v += rows[r * pitch() + c];
+            v += dpp_double<0xB1>(v);    // lane ^ 1
+            v += dpp_double<0x4E>(v);    // lane ^ 2
+            v += dpp_double<0x141>(v);   // the other half of eight
+            v += dpp_double<0x140>(v);   // the other half of sixteen
+            if (part == 0 && r < count) {
+                adj_sum* to = reinterpret_cast<adj_sum*>(a.sens) + slot + r;
+                adj_sum now = r0 ? *to : old;
+                now.x += a.cos_t * v;
+                now.y += a.sin_t * v;
+                *to = now;
+            }
+        }
+    }
+};
+
+// One incidence: the spring's tangent stiffness applied to w_j - w_i, and (actuated) the sensitivity
+// of the loss to its rest length, accumulated in FP64.
+template <int MODE>
+__device__ __forceinline__ void adj_spring(const AdjArgs& a, AdjGroups<MODE>& groups, int e, const AdjEntry<MODE>& q,
+                                           float f, bool ok, float4 xi, float4 wi, lds_vec4 xj, lds_vec4 wj, float& ax,
+                                           float& ay, float& az) {
+    const float l0 = MODE != kAdjPassive ? q.kl.y * f : q.kl.y;
+    const float dx = xj.x - xi.x, dy = xj.y - xi.y, dz = xj.z - xi.z;
+    const float len2 = dx * dx + dy * dy + dz * dz;
+    const bool use = ok && len2 > 0.0f;   // selects, not a branch: the rows of a lane then overlap
+    const float len = __builtin_sqrtf(use ? len2 : 1.0f);
+    const float il = 1.0f / len;
+    const float nx = dx * il, ny = dy * il, nz = dz * il;
+    const float dwx = wj.x - wi.x, dwy = wj.y - wi.y, dwz = wj.z - wi.z;
+    const float ndw = nx * dwx + ny * dwy + nz * dwz;
+    const float tr = 1.0f - l0 * il;        // delta / l
+    const float k = q.kl.x;
+    const float sx = ax + k * (nx * ndw + tr * (dwx - nx * ndw));
+    const float sy = ay + k * (ny * ndw + tr * (dwy - ny * ndw));
+    const float sz = az + k * (nz * ndw + tr * (dwz - nz * ndw));
+    ax = use ? sx : ax;
+    ay = use ? sy : ay;
+    az = use ? sz : az;
+    if (MODE != kAdjPassive) groups.add(a, e, q.g, q.acc, use, 0.5 * (double)q.kl.y * (double)k * (double)ndw);
 }
 
 __device__ __forceinline__ lds_vec4 vec4_of(float4 v) {
@@ -1378,16 +1480,16 @@ __device__ __forceinline__ lds_vec4 vec4_of(float4 v) {
 // mass's x_bar then feeds adj_local of the step before (every input of which is the mass's own), so
 // one launch per reversed step remains; nx.w and nx.xbl must not be the w and xbl this launch reads.
 // (x_bar itself is then needed by nobody else.)
-template <bool ACT>
+template <int MODE>
 __global__ void __launch_bounds__(1024) adj_gather_kernel(AdjArgs a, StepParams p, AdjNext nx) {
     extern __shared__ float4 sx[];
     float4* sw = sx + a.lds_slots;
-    float* sfac = reinterpret_cast<float*>(sw + a.lds_slots);   // the factor table, when staged
     const int b = logical_block(a.nblk);
     if (b >= a.nblk) return;
     const int base = b * a.block, t = (int)threadIdx.x;
-    if (ACT && a.stage_factors)
-        for (int q = t; q <= a.n_factor; q += a.block) sfac[q] = a.factor[q];
+    AdjGroups<MODE> groups;
+    groups.start(a, sw + a.lds_slots, b);
+    groups.stage(a);
     float4 wt = make_float4(0.f, 0.f, 0.f, 0.f);
     if (base + t < a.n) wt = a.w[base + t];
     sw[t] = wt;
@@ -1397,11 +1499,6 @@ __global__ void __launch_bounds__(1024) adj_gather_kernel(AdjArgs a, StepParams 
     const float4 xi = sx[own];
     const float4 wi = sw[own];
     float ax = 0.f, ay = 0.f, az = 0.f;
-    auto factor = [&](uint32_t g) {
-        if (!ACT) return 1.0f;
-        if (a.stage_factors) return sfac[g];   // LDS and global memory apart: one pointer to either is a flat load
-        return a.factor[g];
-    };
     const int s = __builtin_amdgcn_readfirstlane((base + t) >> 6);
     if (s < a.nslice) {
         const int e0 = __builtin_amdgcn_readfirstlane(a.slice_ptr[s]);
@@ -1410,34 +1507,37 @@ __global__ void __launch_bounds__(1024) adj_gather_kernel(AdjArgs a, StepParams 
         constexpr int B = 8;   // rows whose loads are in flight together
         int k = 0;
         for (; k + B <= rows; k += B) {
-            AdjEntry q[B];
+            AdjEntry<MODE> q[B];
             float f[B];
 #pragma unroll
-            for (int u = 0; u < B; ++u) q[u] = adj_entry<ACT>(a, e + (k + u) * 64);
+            for (int u = 0; u < B; ++u) q[u] = adj_entry<MODE>(a, e + (k + u) * 64);
 #pragma unroll
-            for (int u = 0; u < B; ++u) f[u] = factor(q[u].g);
+            for (int u = 0; u < B; ++u) f[u] = groups.of(a, q[u].g);
 #pragma unroll
             for (int u = 0; u < B; ++u)
-                adj_spring<ACT>(a, e + (k + u) * 64, q[u], f[u], xi, wi, vec4_of(sx[q[u].slot]), vec4_of(sw[q[u].slot]),
+                adj_spring<MODE>(a, groups, e + (k + u) * 64, q[u], f[u], true, xi, wi, vec4_of(sx[q[u].slot]), vec4_of(sw[q[u].slot]),
                                 ax, ay, az);
         }
         for (; k < rows; ++k) {
-            const AdjEntry q = adj_entry<ACT>(a, e + k * 64);
-            adj_spring<ACT>(a, e + k * 64, q, factor(q.g), xi, wi, vec4_of(sx[q.slot]), vec4_of(sw[q.slot]), ax, ay, az);
+            const AdjEntry<MODE> q = adj_entry<MODE>(a, e + k * 64);
+            adj_spring<MODE>(a, groups, e + k * 64, q, groups.of(a, q.g), true, xi, wi, vec4_of(sx[q.slot]),
+                             vec4_of(sw[q.slot]), ax, ay, az);
         }
     }
     const int i = base + own;
-    if (i >= a.n) return;
-    const float bx = a.xbl[3 * i + 0] + ax, by = a.xbl[3 * i + 1] + ay, bz = a.xbl[3 * i + 2] + az;
-    if (nx.x) {
-        AdjLocalIn in;
-        in.load(i, nx.x, nx.vstar, nx.vb1);
-        adj_local_one(i, in, bx, by, bz, nx.w, nx.vb0, nx.xbl, p);
-        return;
+    if (i < a.n) {
+        const float bx = a.xbl[3 * i + 0] + ax, by = a.xbl[3 * i + 1] + ay, bz = a.xbl[3 * i + 2] + az;
+        if (nx.x) {
+            AdjLocalIn in;
+            in.load(i, nx.x, nx.vstar, nx.vb1);
+            adj_local_one(i, in, bx, by, bz, nx.w, nx.vb0, nx.xbl, p);
+        } else {
+            a.xb0[3 * i + 0] = bx;
+            a.xb0[3 * i + 1] = by;
+            a.xb0[3 * i + 2] = bz;
+        }
     }
-    a.xb0[3 * i + 0] = bx;
-    a.xb0[3 * i + 1] = by;
-    a.xb0[3 * i + 2] = bz;
+    groups.finish(a);
 }
 
 // The same with LPM lanes per mass (2 or 4; the simulation's lanes per mass): lane j of a mass takes its
@@ -1446,14 +1546,13 @@ __global__ void __launch_bounds__(1024) adj_gather_kernel(AdjArgs a, StepParams 
 // Such a launch is a chain of latencies (the quadruped: under one wavefront per SIMD), so every load
 // is issued as early as it can be: the first kAdjPre rows of each lane (at four lanes all rows of a
 // full lattice's masses), the halo, and what adj_local needs, before anything is waited for.
-// The quadruped's launch: 9.7 -> 8.5 us beside the recomputed steps (7.8 -> 7.5 alone).
+// The quadruped's launch: 9.7 -> 7.0 us beside the recomputed steps (7.8 -> 6.0 alone).
 constexpr int kAdjPre = 8, kAdjGroup = 4;
 
-template <bool ACT, int LPM>
+template <int MODE, int LPM>
 __global__ void __launch_bounds__(1024) adj_gather_lanes_kernel(AdjArgs a, StepParams p, AdjNext nx) {
     extern __shared__ float4 sx[];
     float4* sw = sx + a.lds_slots;
-    float* sfac = reinterpret_cast<float*>(sw + a.lds_slots);
     const int b = logical_block(a.nblk);
     if (b >= a.nblk) return;
     const int t = (int)threadIdx.x, nt = (int)blockDim.x, base = b * a.block;
@@ -1461,11 +1560,11 @@ __global__ void __launch_bounds__(1024) adj_gather_lanes_kernel(AdjArgs a, StepP
     const int h0 = a.halo_ptr[b], h1 = a.halo_ptr[b + 1];
     const int own = a.lane_mass[base + m];
     const int hj = h0 + t < h1 ? a.halo_idx[h0 + t] : -1;
-    float4 xt = make_float4(0.f, 0.f, 0.f, 0.f), wt = xt, xh = xt, wh = xt;
-    if (t < a.block && base + t < a.n) {
-        xt = a.x[base + t];
-        wt = a.w[base + t];
-    }
+    // no condition around these loads, only clamped addresses: after a load that may be skipped, the next
+    // wait is for every load
+    const int it = min(base + min(t, a.block - 1), a.n - 1);
+    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 xt = a.x[it], wt = a.w[it], xh = z, wh = z;
     // this lane's rows: sub, sub + LPM, ...; the slice's last row can be missing in some lanes of a group
     const int s = __builtin_amdgcn_readfirstlane((base + m) >> 6);
     int e = 0, rows = 0, count = 0;
@@ -1475,17 +1574,17 @@ __global__ void __launch_bounds__(1024) adj_gather_lanes_kernel(AdjArgs a, StepP
         count = (rows + LPM - 1) / LPM;
         e = e0 + (m & 63);
     }
-    auto at = [&](int k) { return e + min(k * LPM + sub, rows - 1) * 64; };   // past the end: the last row again
-    AdjEntry q[kAdjPre];
-    if (count > 0) {
+    auto at = [&](int k) { return e + max(min(k * LPM + sub, rows - 1), 0) * 64; };   // past the end: the last row again
+    AdjEntry<MODE> q[kAdjPre];
 #pragma unroll
-        for (int u = 0; u < kAdjPre; ++u)
-            if (u < count) q[u] = adj_entry<ACT>(a, at(u));
-    }
+    for (int u = 0; u < kAdjPre; ++u) q[u] = adj_entry<MODE>(a, at(u));   // (an empty slice: the arrays' padding)
     if (hj >= 0) {
         xh = a.x[hj];
         wh = a.w[hj];
     }
+    AdjGroups<MODE> groups;
+    groups.start(a, sw + a.lds_slots, b);
+    if (base + t >= a.n) xt = wt = z;
     const int i = base + own;
     const bool mine = sub == 0 && i < a.n;
     AdjLocalIn in = {};
@@ -1494,8 +1593,7 @@ __global__ void __launch_bounds__(1024) adj_gather_lanes_kernel(AdjArgs a, StepP
         for (int c = 0; c < 3; ++c) xb[c] = a.xbl[3 * i + c];
         if (nx.x) in.load(i, nx.x, nx.vstar, nx.vb1);
     }
-    if (ACT && a.stage_factors)
-        for (int r = t; r <= a.n_factor; r += nt) sfac[r] = a.factor[r];
+    groups.stage(a);
     if (t < a.block) {   // block * LPM threads: one round
         sx[t] = xt;
         sw[t] = wt;
@@ -1512,34 +1610,37 @@ __global__ void __launch_bounds__(1024) adj_gather_lanes_kernel(AdjArgs a, StepP
     __syncthreads();
     const float4 xi = sx[own], wi = sw[own];
     float ax = 0.f, ay = 0.f, az = 0.f;
-    // kAdjGroup rows from row k on, their LDS reads together
-    auto group = [&](const AdjEntry* g, int k) {
-        lds_vec4 xj[kAdjGroup], wj[kAdjGroup];
-        float f[kAdjGroup];
+    // N rows from row k on, their LDS reads together
+    auto part = [&](auto rows_of, const AdjEntry<MODE>* g, int k) {
+        constexpr int N = decltype(rows_of)::value;
+        lds_vec4 xj[N], wj[N];
+        float f[N];
 #pragma unroll
-        for (int u = 0; u < kAdjGroup; ++u)
-            if (k + u < count) {
-                xj[u] = vec4_of(sx[g[u].slot]);
-                wj[u] = vec4_of(sw[g[u].slot]);
-                f[u] = 1.0f;
-                if (ACT) {
-                    if (a.stage_factors) f[u] = sfac[g[u].g];
-                    else f[u] = a.factor[g[u].g];
-                }
-            }
+        for (int u = 0; u < N; ++u) {
+            xj[u] = vec4_of(sx[g[u].slot]);
+            wj[u] = vec4_of(sw[g[u].slot]);
+            f[u] = groups.of(a, g[u].g);
+        }
 #pragma unroll
-        for (int u = 0; u < kAdjGroup; ++u)
-            if (k + u < count && (k + u) * LPM + sub < rows)
-                adj_spring<ACT>(a, e + ((k + u) * LPM + sub) * 64, g[u], f[u], xi, wi, xj[u], wj[u], ax, ay, az);
+        for (int u = 0; u < N; ++u)
+            adj_spring<MODE>(a, groups, e + ((k + u) * LPM + sub) * 64, g[u], f[u], (k + u) * LPM + sub < rows, xi, wi,
+                             xj[u], wj[u], ax, ay, az);
     };
-    int k = 0;
+    auto group = [&](const AdjEntry<MODE>* g, int k) {   // up to kAdjGroup rows; the count is uniform
+        switch (min(count - k, kAdjGroup)) {
+        case 1: part(std::integral_constant<int, 1>{}, g, k); break;
+        case 2: part(std::integral_constant<int, 2>{}, g, k); break;
+        case 3: part(std::integral_constant<int, 3>{}, g, k); break;
+        case 4: part(std::integral_constant<int, 4>{}, g, k); break;
+        }
+    };
+    static_assert(kAdjGroup == 4, "the cases above");
 #pragma unroll
     for (int u = 0; u < kAdjPre; u += kAdjGroup)
         if (u < count) group(q + u, u);
-    for (k = kAdjPre; k < count; k += kAdjGroup) {
+    for (int k = kAdjPre; k < count; k += kAdjGroup) {
 #pragma unroll
-        for (int u = 0; u < kAdjGroup; ++u)
-            if (k + u < count) q[u] = adj_entry<ACT>(a, at(k + u));
+        for (int u = 0; u < kAdjGroup; ++u) q[u] = adj_entry<MODE>(a, at(k + u));
         group(q, k);
     }
 #pragma unroll
@@ -1548,15 +1649,17 @@ __global__ void __launch_bounds__(1024) adj_gather_lanes_kernel(AdjArgs a, StepP
         ay += __shfl_xor(ay, o, 64);
         az += __shfl_xor(az, o, 64);
     }
-    if (!mine) return;
-    const float bx = xb[0] + ax, by = xb[1] + ay, bz = xb[2] + az;
-    if (nx.x) {
-        adj_local_one(i, in, bx, by, bz, nx.w, nx.vb0, nx.xbl, p);
-        return;
+    if (mine) {
+        const float bx = xb[0] + ax, by = xb[1] + ay, bz = xb[2] + az;
+        if (nx.x) {
+            adj_local_one(i, in, bx, by, bz, nx.w, nx.vb0, nx.xbl, p);
+        } else {
+            a.xb0[3 * i + 0] = bx;
+            a.xb0[3 * i + 1] = by;
+            a.xb0[3 * i + 2] = bz;
+        }
     }
-    a.xb0[3 * i + 0] = bx;
-    a.xb0[3 * i + 1] = by;
-    a.xb0[3 * i + 2] = bz;
+    groups.finish(a);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1671,6 +1774,10 @@ __global__ void __launch_bounds__(kGridThreads) step_grid_kernel(GridArgs a, Ste
 inline int grid_for(int64_t nblk) { return (int)(((nblk + 7) / 8) * 8); }
 
 constexpr int kAdjStagedFactors = 4096;
+
+// LDS that a workgroup may take for kAdjBlockSums: what a launch may have without asking for more, and two
+// workgroups a CU still fit.  Four lanes on 64 masses: up to 25 groups a block (the quadruped's 16 at most).
+constexpr size_t kAdjBlockLds = 64 * 1024;
 
 }  // namespace
 
@@ -1895,27 +2002,38 @@ hipError_t launch_actuation_steps(const DeviceArrays& d, unsigned long long cycl
     return hipGetLastError();
 }
 
+namespace {
+
+size_t adj_lds_bytes(const DeviceArrays& d, int groups) {
+    const size_t threads = (size_t)d.block * (d.lanes == 2 || d.lanes == 4 ? d.lanes : 1);
+    return 2 * (size_t)d.lds_slots * sizeof(float4) + (groups ? (size_t)(groups + 1) * ((threads + 16) * sizeof(double) + sizeof(float)) : 0);
+}
+
+}  // namespace
+
+bool adj_block_sums(const DeviceArrays& d, int max_groups) { return adj_lds_bytes(d, max_groups) <= kAdjBlockLds; }
+
 hipError_t launch_adj_gather(const DeviceArrays& d, const float4* x, const float4* w, const float* xbl, float* xb0,
-                             double2* sens, double cos_t, double sin_t, hipStream_t st, const float* factor,
-                             const StepParams& p, const AdjNext& next) {
+                             double2* sens, const int4* range, int max_groups, double cos_t, double sin_t, hipStream_t st,
+                             const float* factor, const StepParams& p, const AdjNext& next) {
     if (!factor) factor = d.factor;
-    // the factor table goes to LDS when small (kAdjStagedFactors entries at most)
-    const int stage = d.grp && d.n_factor + 1 <= kAdjStagedFactors ? 1 : 0;
-    const size_t lds = 2 * (size_t)d.lds_slots * sizeof(float4) + (stage ? (size_t)(d.n_factor + 1) * sizeof(float) : 0);
+    // kAdjEntrySums: the factor table goes to LDS when small (kAdjStagedFactors entries at most)
+    const int stage = d.grp && !range && d.n_factor + 1 <= kAdjStagedFactors ? 1 : 0;
+    const size_t lds = range ? adj_lds_bytes(d, max_groups)
+                             : adj_lds_bytes(d, 0) + (stage ? (size_t)(d.n_factor + 1) * sizeof(float) : 0);
     const int lanes = d.lanes == 2 || d.lanes == 4 ? d.lanes : 1;
     const dim3 g(grid_for(d.nblk)), th((unsigned)(d.block * lanes));
-    const AdjArgs a{x, w, xbl, xb0, d.slice_ptr, d.nbr, d.kl, d.grp, d.halo_ptr, d.halo_idx, d.lane_mass, factor, sens,
-                    cos_t, sin_t, d.n_factor, (int)d.n, (int)d.nblk, (int)d.nslice, d.block, d.lds_slots, stage};
-    auto go = [&](auto k) { hipLaunchKernelGGL(k, g, th, lds, st, a, p, next); };
-    if (d.grp) {
-        if (lanes == 4) go(adj_gather_lanes_kernel<true, 4>);
-        else if (lanes == 2) go(adj_gather_lanes_kernel<true, 2>);
-        else go(adj_gather_kernel<true>);
-    } else {
-        if (lanes == 4) go(adj_gather_lanes_kernel<false, 4>);
-        else if (lanes == 2) go(adj_gather_lanes_kernel<false, 2>);
-        else go(adj_gather_kernel<false>);
-    }
+    const AdjArgs a{x, w, xbl, xb0, d.slice_ptr, d.nbr, d.kl, d.grp, d.halo_ptr, d.halo_idx, d.lane_mass, factor, sens, range,
+                    cos_t, sin_t, d.n_factor, (int)d.n, (int)d.nblk, (int)d.nslice, d.block, d.lds_slots, max_groups, stage};
+    auto go = [&](auto one, auto two, auto four) {
+        const auto k = lanes == 4 ? four : lanes == 2 ? two : one;
+        hipLaunchKernelGGL(k, g, th, lds, st, a, p, next);
+    };
+#define CRONOS_ADJ(M) go(adj_gather_kernel<M>, adj_gather_lanes_kernel<M, 2>, adj_gather_lanes_kernel<M, 4>)
+    if (!d.grp) CRONOS_ADJ(kAdjPassive);
+    else if (range) CRONOS_ADJ(kAdjBlockSums);
+    else CRONOS_ADJ(kAdjEntrySums);
+#undef CRONOS_ADJ
     return hipGetLastError();
 }
 
@@ -2029,17 +2147,17 @@ hipError_t launch_commit_state(const DeviceArrays& d, int cur, bool x, bool v, l
 
 namespace {
 
-// One workgroup per actuation group: its entries' sums, each thread over a strided part of
-// the group's entry list in order, then the fixed-order workgroup tree.
+// One workgroup per actuation group: its sums (one per entry or per workgroup), each thread over a
+// strided part of the group's list in order, then the fixed-order workgroup tree.
 __global__ void __launch_bounds__(256) adj_group_sums_kernel(const double2* __restrict__ sens,
                                                              const int32_t* __restrict__ grp_ptr,
-                                                             const int32_t* __restrict__ grp_entries,
+                                                             const int32_t* __restrict__ grp_sums,
                                                              double2* __restrict__ gsum) {
     __shared__ double2 red[256];
     const int g = blockIdx.x, t = threadIdx.x;
     double2 s = make_double2(0.0, 0.0);
     for (int q = grp_ptr[g] + t; q < grp_ptr[g + 1]; q += 256) {
-        const double2 v = sens[grp_entries[q]];
+        const double2 v = sens[grp_sums[q]];
         s.x += v.x;
         s.y += v.y;
     }
@@ -2057,10 +2175,10 @@ __global__ void __launch_bounds__(256) adj_group_sums_kernel(const double2* __re
 
 }  // namespace
 
-hipError_t launch_adj_group_sums(const double2* sens, const int32_t* grp_ptr, const int32_t* grp_entries, int n_groups,
+hipError_t launch_adj_group_sums(const double2* sens, const int32_t* grp_ptr, const int32_t* grp_sums, int n_groups,
                                  double2* gsum, hipStream_t st) {
     if (n_groups < 1) return hipSuccess;
-    hipLaunchKernelGGL(adj_group_sums_kernel, dim3(n_groups), dim3(256), 0, st, sens, grp_ptr, grp_entries, gsum);
+    hipLaunchKernelGGL(adj_group_sums_kernel, dim3(n_groups), dim3(256), 0, st, sens, grp_ptr, grp_sums, gsum);
     return hipGetLastError();
 }
 

@@ -82,10 +82,15 @@ struct RolloutBuffers {
     float* xb[2] = {nullptr, nullptr};
     float* vb[2] = {nullptr, nullptr};
     float* xbl[2] = {nullptr, nullptr};   // [3N] x_bar before the spring sum, alternating as w
-    double2* sens = nullptr;  // [entries] each actuated entry's sensitivity, summed over the reversed steps
-    // the entries of each actuation group (CSR, entry order), for the per-group sums on the device
+    // actuation sensitivities summed over the reversed steps: one sum per block and group of its range,
+    // or (adj_range null) one per entry
+    double2* sens = nullptr;
+    int4* adj_range = nullptr;       // [nblk] (first group, groups, first sum, -)
+    int32_t adj_max_groups = 0;
+    size_t n_sens = 0;
+    // the sums of each actuation group (CSR, in order), added up on the device
     int32_t* grp_ptr = nullptr;      // [n_factor + 1]
-    int32_t* grp_entries = nullptr;  // [actuated entries]
+    int32_t* grp_sums = nullptr;
     double2* gsum = nullptr;         // [n_factor]
     size_t cap_seg = 0, cap_ck = 0;
 };
@@ -138,7 +143,7 @@ void free_device(cronos_sim_t* s) {
     if (r.side) (void)hipStreamDestroy(r.side);
     void* rp[] = {r.seg_f[0], r.seg_f[1], r.ck_x, r.ck_v, r.seg_x[0], r.seg_x[1], r.seg_v[0], r.seg_v[1], r.seg_vs[0],
                   r.seg_vs[1], r.lossw, r.w[0], r.w[1], r.xb[0], r.xb[1], r.vb[0], r.vb[1],
-                  r.xbl[0], r.xbl[1], r.sens, r.grp_ptr, r.grp_entries, r.gsum};
+                  r.xbl[0], r.xbl[1], r.sens, r.adj_range, r.grp_ptr, r.grp_sums, r.gsum};
     for (void* p : rp)
         if (p) (void)hipFree(p);
     for (int b = 0; b < 2; ++b) {
@@ -1052,8 +1057,8 @@ extern "C" cronos_status cronos_create(const cronos_desc* d, cronos_sim* out) {
         if (d->fext) TRY(upload(&D.fext, hf.data(), 3 * n));
         TRY(upload(&D.lane_mass, L.lane_mass.data(), L.lane_mass.size()));
         TRY(upload(&D.slice_ptr, L.slice_ptr.data(), L.slice_ptr.size()));
-        TRY(upload(&D.nbr, L.nbr_local.data(), entries));
-        TRY(upload(&D.kl, hkl.data(), entries));
+        TRY(upload(&D.nbr, L.nbr_local.data(), entries, cronos::kEntryPad));
+        TRY(upload(&D.kl, hkl.data(), entries, cronos::kEntryPad));
         if (!hsp_rec.empty()) {
             TRY(upload(&D.packed, hsplit.data(), entries));
             TRY(upload(&D.sp_rec, hsp_rec.data(), hsp_rec.size()));
@@ -1107,7 +1112,7 @@ extern "C" cronos_status cronos_create(const cronos_desc* d, cronos_sim* out) {
                     D.resident_staged = (int32_t)entries;
             }
         }
-        if (sim->actuated) TRY(upload(&D.grp, hg.data(), entries));
+        if (sim->actuated) TRY(upload(&D.grp, hg.data(), entries, cronos::kEntryPad));
         TRY(upload(&D.halo_ptr, L.halo_ptr.data(), L.halo_ptr.size()));
         TRY(upload(&D.halo_idx, L.halo_idx.data(), L.halo_idx.size()));
         std::vector<float> ones(n_factor + 1, 1.0f);
@@ -1625,22 +1630,53 @@ void release(T*& p) {
 
 namespace {
 
-// The actuated entries of each actuation group in entry order (CSR over groups), read by the
-// device's per-group sums of the adjoint's sensitivities.
+// Where the adjoint's sensitivities are summed, and the list of each actuation group's sums (CSR over
+// groups, in block or entry order) that the device adds up at the end.
 cronos_status build_group_lists(cronos_sim_t* sim) {
     RolloutBuffers& R = sim->ro;
+    const cronos::Layout& L = sim->lay;
     const int32_t G = sim->d.n_factor;
-    const int64_t entries = sim->lay.slice_ptr.back();
+    const int64_t entries = L.slice_ptr.back(), spb = sim->d.block / 64;
+    std::vector<int4> range((size_t)sim->d.nblk, make_int4(0, 0, 0, 0));
+    int64_t sums = 0;
+    for (int64_t b = 0; b < sim->d.nblk; ++b) {
+        int lo = G, hi = -1;
+        for (int64_t e = L.slice_ptr[b * spb]; e < L.slice_ptr[(b + 1) * spb]; ++e)
+            if (sim->h_grp[e] < G) {
+                lo = std::min<int>(lo, sim->h_grp[e]);
+                hi = std::max<int>(hi, sim->h_grp[e]);
+            }
+        const int count = hi < 0 ? 0 : hi - lo + 1;
+        range[b] = make_int4(hi < 0 ? 0 : lo, count, (int)sums, 0);
+        R.adj_max_groups = std::max(R.adj_max_groups, count);
+        sums += count;
+    }
+    const bool blocks = cronos::adj_block_sums(sim->d, R.adj_max_groups) && sums <= entries;
     std::vector<int32_t> ptr((size_t)G + 1, 0);
-    for (int64_t e = 0; e < entries; ++e)
-        if (sim->h_grp[e] < G) ++ptr[(size_t)sim->h_grp[e] + 1];
+    std::vector<int32_t> idx;
+    auto each = [&](auto&& f) {   // f(group, its sum)
+        if (blocks) {
+            for (const int4& r : range)
+                for (int q = 0; q < r.y; ++q) f(r.x + q, r.z + q);
+        } else {
+            for (int64_t e = 0; e < entries; ++e)
+                if (sim->h_grp[e] < G) f((int)sim->h_grp[e], (int)e);
+        }
+    };
+    each([&](int g, int) { ++ptr[(size_t)g + 1]; });
     for (int32_t g = 0; g < G; ++g) ptr[(size_t)g + 1] += ptr[(size_t)g];
-    std::vector<int32_t> idx((size_t)ptr[(size_t)G]), fill(ptr.begin(), ptr.end() - 1);
-    for (int64_t e = 0; e < entries; ++e)
-        if (sim->h_grp[e] < G) idx[(size_t)fill[sim->h_grp[e]]++] = (int32_t)e;
-    TRY(ensure(&R.grp_entries, idx.size()));
+    idx.resize((size_t)ptr[(size_t)G]);
+    std::vector<int32_t> fill(ptr.begin(), ptr.end() - 1);
+    each([&](int g, int q) { idx[(size_t)fill[g]++] = q; });
+    R.n_sens = (size_t)(blocks ? sums : entries);
+    if (blocks && !R.adj_range) {
+        TRY(ensure(&R.adj_range, range.size()));
+        HIP_TRY(hipMemcpy(R.adj_range, range.data(), range.size() * sizeof(int4), hipMemcpyHostToDevice));
+    }
+    TRY(ensure(&R.grp_sums, idx.size()));
     TRY(ensure(&R.gsum, (size_t)std::max(G, 1)));
-    if (!idx.empty()) HIP_TRY(hipMemcpy(R.grp_entries, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    if (!idx.empty()) HIP_TRY(hipMemcpy(R.grp_sums, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    TRY(ensure(&R.sens, R.n_sens + cronos::kEntryPad));
     TRY(ensure(&R.grp_ptr, ptr.size()));
     HIP_TRY(hipMemcpy(R.grp_ptr, ptr.data(), ptr.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     return CRONOS_OK;
@@ -1690,7 +1726,6 @@ extern "C" cronos_status cronos_rollout(cronos_sim sim, int64_t n_steps, int32_t
         TRY(ensure(&R.vb[q], 3 * n));
         TRY(ensure(&R.xbl[q], 3 * n));
     }
-    TRY(ensure(&R.sens, (size_t)sim->lay.slice_ptr.back()));
     if (sim->actuated && !R.grp_ptr) TRY(build_group_lists(sim));
     // loss weights in the device order (FP32)
     std::vector<float> hw(3 * n);
@@ -1786,7 +1821,7 @@ cronos_status enqueue_reverse_sweep(cronos_sim_t* sim) {
                 nx.xbl = R.xbl[wc ^ 1];
             }
             HIP_TRY(cronos::launch_adj_gather(D, R.seg_x[p] + (size_t)k * n, R.w[wc], R.xbl[wc], R.xb[cur ^ 1], R.sens,
-                                              std::cos(sim->omega * t), std::sin(sim->omega * t), st,
+                                              R.adj_range, R.adj_max_groups, std::cos(sim->omega * t), std::sin(sim->omega * t), st,
                                               sim->actuated ? R.seg_f[p] + (size_t)k * fs : nullptr, sim->p, nx));
             cur ^= 1;
             if (k > 0) wc ^= 1;
@@ -1805,12 +1840,11 @@ extern "C" cronos_status cronos_rollout_backward(cronos_sim sim, double* dphase,
     RolloutBuffers& R = sim->ro;
     if (!R.valid) return fail(CRONOS_EINVAL, "rollout_backward: no rollout recorded");
     const int64_t n = sim->d.n;
-    const int64_t entries = sim->lay.slice_ptr.back();
     hipStream_t st = sim->stream;
     HIP_TRY(hipSetDevice(sim->device));
     HIP_TRY(hipMemcpyAsync(R.xb[0], R.lossw, 3 * n * sizeof(float), hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipMemsetAsync(R.vb[0], 0, 3 * n * sizeof(float), st));
-    HIP_TRY(hipMemsetAsync(R.sens, 0, (size_t)entries * sizeof(double2), st));
+    if (R.sens) HIP_TRY(hipMemsetAsync(R.sens, 0, std::max<size_t>(R.n_sens, 1) * sizeof(double2), st));
     // the reverse sweep flips the adjoint buffers once per step
     const int cur = (int)(R.T & 1);
     // plain launches on the two streams: captured as one HIP graph the same sweep ran its
@@ -1822,7 +1856,7 @@ extern "C" cronos_status cronos_rollout_backward(cronos_sim sim, double* dphase,
     if ((dphase || damp) && G > 0 && sim->actuated) {
         // per group: the sum of its entries' sensitivities, in a fixed order on the device
         std::vector<double> sp(G, 0.0), sq(G, 0.0);
-        HIP_TRY(cronos::launch_adj_group_sums(R.sens, R.grp_ptr, R.grp_entries, G, R.gsum, st));
+        HIP_TRY(cronos::launch_adj_group_sums(R.sens, R.grp_ptr, R.grp_sums, G, R.gsum, st));
         std::vector<double2> hs(G);
         HIP_TRY(hipMemcpyAsync(hs.data(), R.gsum, (size_t)G * sizeof(double2), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));

@@ -42,3 +42,36 @@ def test_lanes_agree(rows, actuated):
             assert np.all(np.isfinite(a)) and a.shape == b.shape
             if a.size:
                 assert np.abs(a - b).max() <= tol * max(np.abs(a).max(), 1e-30)
+
+
+def test_sums_by_workgroup_and_by_entry_agree():
+    """Six groups numbered densely (their sums are held by each workgroup) and spread over 600 numbers (too
+    wide a range for that: one sum per entry) have the same gradient.  Both add the same FP64 terms,
+    under 2^12 of them, in another order: 2^12 * 2^-53 of the terms' sum, which is under 100 times
+    the largest component here."""
+    rng = np.random.default_rng(5)
+    x = rng.uniform(0.0, 1.0, (300, 3))
+    ends = np.array([(i, j) for i in range(300) for j in (i + 1, i + 7, i + 30) if j < 300], np.int32)
+    s = len(ends)
+    groups = np.arange(s) % 7 - 1
+    phase, amp, w = np.linspace(0.1, 3.0, 6), np.linspace(0.1, 0.3, 6), rng.normal(size=x.shape)
+    for lanes in (1, 2, 4):
+        out = []
+        for step in (1, 100):
+            at = np.arange(6) * step
+            sim = CR.cronos_create(x, np.full(300, 0.1), ends, np.full(s, 500.0), np.full(s, 0.5), lanes_per_mass=lanes,
+                                   group=np.where(groups < 0, -1, groups * step).astype(np.int16), n_groups=5 * step + 1,
+                                   dt=1e-4, flags=CR.ALLOW_UNSTABLE)
+            ph, am = np.zeros(5 * step + 1), np.zeros(5 * step + 1)
+            ph[at], am[at] = phase, amp
+            CR.cronos_set_actuation(sim, ph, am, 2.0)
+            loss = CR.cronos_rollout(sim, 4, 2, w)
+            g = CR.cronos_rollout_backward(sim, want_state=True)
+            out.append((loss, g[0][at], g[1][at], g[2], g[3]))
+            rest = np.setdiff1d(np.arange(5 * step + 1), at)
+            assert not g[0][rest].any() and not g[1][rest].any()
+            sim.close()
+        a, b = out
+        assert a[0] == b[0] and np.array_equal(a[3], b[3]) and np.array_equal(a[4], b[4])
+        for p, q in zip(a[1:3], b[1:3]):
+            assert np.abs(p).max() > 0 and np.abs(p - q).max() <= 2.0 ** -41 * 100 * np.abs(p).max()
