@@ -79,7 +79,6 @@ struct DeviceArrays {
     int4* chunks = nullptr;              // (block, first mass, end mass, body)
     int32_t* body_chunk = nullptr;       // [nb+1] chunk offsets of each body
     double* chunk_part = nullptr;        // [n_chunks][kDiagFields]
-    double* body_out = nullptr;          // [nb][kDiagFields]
     float* fout = nullptr;               // [n][3] force output
     int32_t* inv = nullptr;              // [n] caller's mass index -> device's
     // structured-box form (see step_grid_kernel): blocks are aligned 8 x 8 x 8 cubes of a full box
@@ -201,6 +200,6 @@ hipError_t launch_modes_beta(const DeviceArrays& d, ModesBuffers& m, int k, hipS
 // once per device.
 constexpr size_t kModesScratchDoubles = size_t(8) << 20;
 hipError_t modes_scratch(int device, double** ptr);
-hipError_t launch_diagnostics(const DeviceArrays& d, int cur, const StepParams& p, hipStream_t st);
+hipError_t launch_diagnostics(const DeviceArrays& d, int cur, const StepParams& p, double* out, hipStream_t st);
 
 }  // namespace cronos

