@@ -932,6 +932,113 @@ __global__ void __launch_bounds__(1024) step_lanes_kernel(StepArgs a, StepParams
     a.vout[3 * i + 2] = vz;
 }
 
+// One step by explicit entries with four lanes per mass, bitwise the one-lane form's: lane j of a mass
+// evaluates rows j, j + 4, ..., and every lane adds the four lanes' forces in row order (their
+// factors and differences broadcast within the quad by register moves).  The sums cost each lane
+// what they cost one, but they are 3 of some 40 operations a row: on bodies of under one wavefront per
+// SIMD, where a wavefront issues alone, the rest goes four times as fast.
+template <int Q>
+__device__ __forceinline__ float quad_lane(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), Q * 0x55, 0xF, 0xF, true));
+}
+
+constexpr int kQuadPre = 7;   // rows a lane loads up front: 28 of a mass
+
+template <bool ACT, int EX, int N>
+__device__ __forceinline__ void quad_rows(const float4* __restrict__ sx, float4 xi, int slot, float2 c, float f, float& fx,
+                                          float& fy, float& fz) {
+    const float4 xj = sx[slot];
+    float dx, dy, dz;
+    const float fac = hooke_fac<EX>(xi.x, xi.y, xi.z, xj.x, xj.y, xj.z, c.x, ACT ? c.y * f : c.y, dx, dy, dz);
+    auto add = [&](float g, float x, float y, float z) {
+        fx = __builtin_fmaf(g, x, fx);
+        fy = __builtin_fmaf(g, y, fy);
+        fz = __builtin_fmaf(g, z, fz);
+    };
+    add(quad_lane<0>(fac), quad_lane<0>(dx), quad_lane<0>(dy), quad_lane<0>(dz));
+    if (N > 1) add(quad_lane<1>(fac), quad_lane<1>(dx), quad_lane<1>(dy), quad_lane<1>(dz));
+    if (N > 2) add(quad_lane<2>(fac), quad_lane<2>(dx), quad_lane<2>(dy), quad_lane<2>(dz));
+    if (N > 3) add(quad_lane<3>(fac), quad_lane<3>(dx), quad_lane<3>(dy), quad_lane<3>(dz));
+}
+
+template <bool ACT, bool EXACT>
+__global__ void __launch_bounds__(256) step_quads_kernel(StepArgs a, StepParams p) {
+    extern __shared__ float4 sx[];
+    const int b = logical_block(a.nblk);
+    const float safe = ACT ? a.act->safe : p.safe;
+    if (b >= a.nblk) return;
+    const int t = (int)threadIdx.x, nt = (int)blockDim.x;
+    const int m = t >> 2, sub = t & 3, base = b * a.block;
+    const int h0 = a.halo_ptr[b], h1 = a.halo_ptr[b + 1];
+    const int own = a.lane_mass[base + m];
+    const int hj = h0 + t < h1 ? a.halo_idx[h0 + t] : -1;
+    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 xt = a.xin[min(base + min(t, a.block - 1), a.n - 1)], xh = z;
+    const int s = __builtin_amdgcn_readfirstlane((base + m) >> 6);
+    int e0 = 0, w = 0;
+    if (s < a.nslice) {
+        e0 = __builtin_amdgcn_readfirstlane(a.slice_ptr[s]);
+        w = __builtin_amdgcn_readfirstlane((a.slice_ptr[s + 1] - e0) >> 6);
+    }
+    int slot[kQuadPre], g[kQuadPre];
+    float2 c[kQuadPre];
+    auto load = [&](int u, int r) {   // past the end: the last row again (an empty slice: the arrays' padding)
+        const int e = e0 + (m & 63) + max(min(r + sub, w - 1), 0) * 64;
+        slot[u] = a.nbr[e];
+        c[u] = a.kl[e];
+        if (ACT) g[u] = a.grp[e];
+    };
+#pragma unroll
+    for (int u = 0; u < kQuadPre; ++u) load(u, 4 * u);
+    if (hj >= 0) xh = a.xin[hj];
+    const int i = base + own;
+    const bool mine = sub == 0 && i < a.n;
+    float vx = 0.0f, vy = 0.0f, vz = 0.0f;
+    if (mine) {
+        vx = a.vin[3 * i + 0];
+        vy = a.vin[3 * i + 1];
+        vz = a.vin[3 * i + 2];
+    }
+    if (base + t >= a.n) xt = z;
+    if (t < a.block) sx[t] = xt;   // block * 4 threads: one round
+    if (hj >= 0) sx[a.block + t] = xh;
+    for (int h = h0 + t + nt; h < h1; h += nt) sx[a.block + (h - h0)] = a.xin[a.halo_idx[h]];
+    __syncthreads();
+    const float4 xi = sx[own];
+    const int mode = EXACT ? difference_mode(xi, safe) : kPlain;
+    float fx = 0.0f, fy = 0.0f, fz = 0.0f;
+    auto rows = [&](auto ex, int u, int left) {   // left: rows from this lane group's first on, uniform
+        constexpr int EX = decltype(ex)::value;
+        const float f = ACT ? a.factor[g[u]] : 1.0f;
+        switch (min(left, 4)) {
+        case 1: quad_rows<ACT, EX, 1>(sx, xi, slot[u], c[u], f, fx, fy, fz); break;
+        case 2: quad_rows<ACT, EX, 2>(sx, xi, slot[u], c[u], f, fx, fy, fz); break;
+        case 3: quad_rows<ACT, EX, 3>(sx, xi, slot[u], c[u], f, fx, fy, fz); break;
+        case 4: quad_rows<ACT, EX, 4>(sx, xi, slot[u], c[u], f, fx, fy, fz); break;
+        }
+    };
+    auto walk = [&](auto ex) {
+#pragma unroll
+        for (int u = 0; u < kQuadPre; ++u)
+            if (4 * u < w) rows(ex, u, w - 4 * u);
+        for (int r = 4 * kQuadPre; r < w; r += 4) {
+            load(0, r);
+            rows(ex, 0, w - r);
+        }
+    };
+    if (mode == kPlain) walk(std::integral_constant<int, kPlain>{});
+    else if (mode == kExactZ) walk(std::integral_constant<int, kExactZ>{});
+    else walk(std::integral_constant<int, kExactAll>{});
+    if (!mine) return;
+    float4 xo;
+    integrate(p, p.dtv, xi, fx, fy, fz, a.fext ? a.fext + 3 * i : nullptr, vx, vy, vz, xo,
+              a.vstar_out ? a.vstar_out + 3 * i : nullptr);
+    a.xout[i] = xo;
+    a.vout[3 * i + 0] = vx;
+    a.vout[3 * i + 1] = vy;
+    a.vout[3 * i + 2] = vz;
+}
+
 // Persistent form: a fixed grid (a multiple of 8 workgroups) walks the blocks; workgroup w runs
 // on XCD w % 8 and takes that XCD's contiguous eighth of the blocks in strides.
 template <bool ACT, bool EXACT, int BATCH, int MODE, bool STAGE = false>
@@ -1811,6 +1918,12 @@ inline int grid_for(int64_t nblk) { return (int)(((nblk + 7) / 8) * 8); }
 
 constexpr int kAdjStagedFactors = 4096;
 
+// Explicit bodies of 64-mass workgroups up to this size take four lanes per mass.  One lane against four:
+// 1,000 masses 5.35 / 4.50 us a step, 4,320 5.2 / 4.3, 12,711 7.95 / 6.72, 18,000 5.31 / 5.20, 24,000
+// 5.67 / 5.68, 48,400 5.74 / 6.17 (above some 16,000 masses the SIMDs hold several wavefronts, and the
+// sums that every lane repeats are no longer free); workgroups of 256 masses, 1,000: 5.04 / 7.69.
+constexpr int64_t kQuadMasses = 16384;
+
 // LDS that a workgroup may take for kAdjBlockSums: what a launch may have without asking for more, and two
 // workgroups a CU still fit.  Four lanes on 64 masses: up to 25 groups a block (the quadruped's 16 at most).
 constexpr size_t kAdjBlockLds = 64 * 1024;
@@ -1899,6 +2012,13 @@ hipError_t launch_step_io(const DeviceArrays& d, const float4* xin, const float*
             else if (nar) ex ? go(step_lanes_kernel<false, true, 4, true>) : go(step_lanes_kernel<false, false, 4, true>);
             else ex ? go(step_lanes_kernel<false, true, 4, false>) : go(step_lanes_kernel<false, false, 4, false>);
         }
+        return hipGetLastError();
+    }
+    if (mode == kExplicit && d.persistent_groups <= 0 && d.block == 64 && d.n <= kQuadMasses) {
+        const dim3 g((unsigned)grid_for(d.nblk)), th((unsigned)(4 * d.block));
+        auto go = [&](auto k) { hipLaunchKernelGGL(k, g, th, lds, st, a, p); };
+        if (d.grp) p.exact ? go(step_quads_kernel<true, true>) : go(step_quads_kernel<true, false>);
+        else p.exact ? go(step_quads_kernel<false, true>) : go(step_quads_kernel<false, false>);
         return hipGetLastError();
     }
     const bool persistent = d.persistent_groups > 0;
