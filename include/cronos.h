@@ -349,7 +349,7 @@ cronos_status cronos_natural_frequencies(cronos_sim sim, int32_t n_modes, int32_
    memory).  The workspace is looked up on the first call on a device.  Every call on one GPU
    shares that workspace and overwrites it: calls that overlap on one GPU (from several
    threads or streams) race and must be serialised by the caller.  EINVAL when
-   80 n + 16 max_iter bytes (n masses, plus alignment) exceed the workspace, as for
+   80 n + 16 max_iter bytes (n masses, plus alignment and a few sums per workgroup) exceed the workspace, as for
    cronos_natural_frequencies otherwise. */
 cronos_status cronos_natural_frequencies_noalloc(cronos_sim sim, int32_t n_modes, int32_t max_iter, double tol,
                                                  uint64_t seed, double* omega, int32_t* n_found,
@@ -407,7 +407,7 @@ cronos_status cronos_launch_config(cronos_sim sim, int32_t* block_masses, int32_
  * buffers into the other set, HIP events; the state is unchanged); *plain_step_us receives the
  * mean of the last 8 (0 where nothing was timed: CRONOS_NO_GRAPH, the default stream, the
  * resident form).  *graphs receives 1 when step calls launch HIP graphs — of 2^j steps, j < 8,
- * both buffer parities captured at creation and after cronos_set_actuation, a call's step count
+ * both buffer parities captured once, at creation, a call's step count
  * decomposed into powers of two from the largest down — and 0 for plain launches, which is the
  * choice where *plain_step_us is 12 us or more (the device then trails the host; a graph launch
  * adds tens of microseconds before its first kernel) unless CRONOS_GRAPH is set.  *staged_io

@@ -199,6 +199,8 @@ hipError_t launch_modes_beta(const DeviceArrays& d, ModesBuffers& m, int k, hipS
 // ends.  modes_scratch returns its address on `device` (which must be current), looked up
 // once per device.
 constexpr size_t kModesScratchDoubles = size_t(8) << 20;
+// Beyond those, room for the partial sums of norms and their scalars, which a request need not count.
+constexpr size_t kModesScratchExtra = 1024;
 hipError_t modes_scratch(int device, double** ptr);
 hipError_t launch_diagnostics(const DeviceArrays& d, int cur, const StepParams& p, double* out, hipStream_t st);
 

@@ -26,7 +26,7 @@
 
 // Workspace of cronos_natural_frequencies_noalloc (each GPU holds its own copy).  Host code
 // never uses this name as an address: modes_scratch looks the device address up.
-static __device__ __align__(256) double scratch[cronos::kModesScratchDoubles];
+static __device__ __align__(256) double scratch[cronos::kModesScratchDoubles + cronos::kModesScratchExtra];
 
 namespace cronos {
 namespace {

@@ -1535,19 +1535,25 @@ extern "C" cronos_status cronos_natural_frequencies_noalloc(cronos_sim sim, int3
     HIP_TRY(hipSetDevice(sim->device));
     double* base = nullptr;
     HIP_TRY(cronos::modes_scratch(sim->device, &base));
-    // carve the fixed workspace: every buffer starts on a 256-byte boundary
+    // carve the fixed workspace: every buffer starts on a 256-byte boundary.  A request counts the vectors,
+    // the coefficients and a partial sum per workgroup and per 256 masses.
+    auto padded = [](int64_t count) { return (std::max<int64_t>(count, 1) + 31) / 32 * 32; };
+    const int64_t need = padded(n) + 3 * padded(3 * n) + padded(sim->d.nblk) + padded((n + 255) / 256) +
+                         2 * padded(max_iter);
+    if (need > (int64_t)cronos::kModesScratchDoubles)
+        return fail(CRONOS_EINVAL,
+                    "natural_frequencies_noalloc: %lld masses and max_iter %d need %lld doubles of workspace; the "
+                    "fixed workspace holds %zu",
+                    (long long)n, max_iter, (long long)need, cronos::kModesScratchDoubles);
     const int64_t counts[9] = {n, 3 * n, 3 * n, 3 * n, cronos::modes_apply_parts(sim->d), cronos::kModesNormParts,
                                max_iter, max_iter, 2};
     int64_t off[9], used = 0;
     for (int b = 0; b < 9; ++b) {
         off[b] = used;
-        used += (std::max<int64_t>(counts[b], 1) + 31) / 32 * 32;
+        used += padded(counts[b]);
     }
-    if (used > (int64_t)cronos::kModesScratchDoubles)
-        return fail(CRONOS_EINVAL,
-                    "natural_frequencies_noalloc: %lld masses and max_iter %d need %lld doubles of workspace; the "
-                    "fixed workspace holds %zu",
-                    (long long)n, max_iter, (long long)used, cronos::kModesScratchDoubles);
+    if (used > (int64_t)(cronos::kModesScratchDoubles + cronos::kModesScratchExtra))
+        return fail(CRONOS_EINVAL, "natural_frequencies_noalloc: workspace layout of %lld doubles", (long long)used);
     cronos::ModesBuffers m;
     m.ism = base + off[0];
     m.q[0] = base + off[1];
