@@ -156,9 +156,9 @@ constexpr int kPart = EX == kExactAll && BATCH > 2 ? BATCH / 2 : BATCH;
 // uniform across the wavefront), BATCH rows at a time: each batch is loaded while the one before
 // it is worked on, and the first before the workgroup's positions are staged, since entries depend
 // on nothing in LDS.  A step waits on memory more than it computes, and a slice's five to ten
-// batches were one full latency each when loaded as they were needed (655,000 masses of the
-// 64-robot population: 13.2 -> 11.4 us; the cantilever by 16-bit entries 18.3 -> 17.1, by 32-bit ones
-// 19.7 -> 18.3; the quadruped with one lane per mass 7.7 -> 6.8).
+// batches were one full latency each when loaded as they were needed: a population of 64 robots
+// (337,000 masses) 13.2 -> 11.4 us a step; the cantilever by 16-bit entries 18.3 -> 17.1, by 32-bit
+// ones 19.7 -> 18.3; the quadruped with one lane per mass 7.7 -> 6.8.
 // The springs are added in row order whatever BATCH is.
 template <class Rows, int BATCH>
 struct RowWalk {
@@ -218,8 +218,8 @@ struct RowWalk {
 // Sum of the spring forces on this lane's mass over its slice entries.  The slice (and so the
 // trip count) is uniform across the wavefront; entries are fetched in batches of BATCH so
 // that several loads are in flight before the first is consumed.
-// (Loading a batch ahead as RowWalk does, three registers a row here, lost: 640,000 masses 30.8 -> 31.5 us,
-// the quadruped's bodies 7.9 -> 8.7 us.)
+// (Loading a batch ahead as RowWalk does, three registers a row here, lost: the cantilever's 640,000 masses
+// 30.8 -> 31.5 us, the quadruped 7.9 -> 8.7.)
 template <bool ACT, int EX, int BATCH>
 __device__ __forceinline__ void gather(const float4* __restrict__ sx, float4 xi, int s, int nslice,
                                        const int32_t* __restrict__ slice_ptr,
