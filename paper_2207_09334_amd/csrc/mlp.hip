@@ -725,14 +725,13 @@ struct cronos_mlp_t {
     bf16* dzt[3] = {};                 // [sizes[l+1]][max_rows]
     float* part_w = nullptr;           // [splits][n_params] split-K partials of the weight gradients
     int grad_splits = 1;               // partials Adam adds (1: the gradient is in grad)
-    double* part = nullptr;            // loss partials
-    int loss_parts = 0;                // how many the last forward with the loss left
+    double* part = nullptr;            // loss partials of one minibatch: [loss_parts(max_rows)]
     // training data
     float* data_x = nullptr;
     float* data_t = nullptr;
     int* idx = nullptr;
     long data_rows = 0;
-    double* epoch_part = nullptr;      // loss partials of the last epoch's minibatches
+    double* epoch_part = nullptr;      // loss partials of the last epoch's minibatches, one after the other
     size_t epoch_part_cap = 0;
 };
 
@@ -772,16 +771,30 @@ hipError_t launch_forward(hipStream_t st, GemmArgs g) {
     return hipGetLastError();
 }
 
-// The output layer's product; loss_parts: the loss partials it leaves.
-hipError_t launch_output(hipStream_t st, GemmArgs g, int* loss_parts) {
-    if (g.n_real > 16) {
-        prepare(g, 1);
-        *loss_parts = g.nbx * g.nby;
-        return gemm<kLinear>(st, g);
+// Output layers of at most this many columns take thin_linear_kernel.
+constexpr int kThinColumns = 16;
+
+// Loss partials that the output layer's product leaves for `rows` rows of n_out columns: one per
+// wavefront of the narrow kernel, else one per tile.  Not falling in either argument.
+size_t loss_parts(int n_out, int rows) {
+    const int padded = (rows + 63) / 64 * 64;
+    if (n_out <= kThinColumns) return (size_t)padded / 16;
+    return (size_t)(padded / kTile) * (size_t)((pad_width(n_out) + kTile - 1) / kTile);
+}
+
+// The output layer's product; with the loss, into g.loss_part, which has room for `room` partials.
+cronos_status launch_output(hipStream_t st, GemmArgs g, size_t room) {
+    const bool thin = g.n_real <= kThinColumns;
+    prepare(g, 1);
+    const size_t parts = thin ? (size_t)g.M / 16 : (size_t)g.nbx * (size_t)g.nby;
+    if (g.T && parts > room) return fail(CRONOS_EINVAL, "mlp: %zu loss partials, room for %zu", parts, room);
+    if (thin) {
+        hipLaunchKernelGGL(thin_linear_kernel, dim3(g.M / 16), dim3(64), 0, st, g);
+        HIP_TRY(hipGetLastError());
+    } else {
+        HIP_TRY(gemm<kLinear>(st, g));
     }
-    *loss_parts = g.M / 16;
-    hipLaunchKernelGGL(thin_linear_kernel, dim3(g.M / 16), dim3(64), 0, st, g);
-    return hipGetLastError();
+    return CRONOS_OK;
 }
 
 template <int E1, int BK1, int E2>
@@ -826,8 +839,8 @@ void free_mlp(cronos_mlp_t* q) {
 // Forward over `rows` (<= max_rows, padded to 64) rows already in q->x; with_loss: the output
 // product's epilogue also forms the loss partials and dY from the targets in q->t, and the hidden
 // layers keep what the backward products read (the activation's slopes, transposed activations).
-// loss_part: where the loss partials go (q->loss_parts of them).
-cronos_status forward_dev(cronos_mlp_t* q, int rows, bool with_loss, double* loss_part) {
+// loss_part: where the loss partials go (loss_parts of them), with room for loss_room.
+cronos_status forward_dev(cronos_mlp_t* q, int rows, bool with_loss, double* loss_part, size_t loss_room) {
     const int P = (rows + 63) / 64 * 64;
     const long R = q->max_rows;
     const bf16* in = q->x;
@@ -872,8 +885,7 @@ cronos_status forward_dev(cronos_mlp_t* q, int rows, bool with_loss, double* los
         g.loss_part = loss_part;
         g.rows = rows;
     }
-    HIP_TRY(launch_output(q->stream, g, &q->loss_parts));
-    return CRONOS_OK;
+    return launch_output(q->stream, g, loss_room);
 }
 
 // Loss and gradients for `rows` rows whose inputs are in q->x / q->xt and targets in q->t.
@@ -971,14 +983,14 @@ cronos_status adam_dev(cronos_mlp_t* q, double lr, double b1, double b2, double 
 }
 
 // The loss of `rows` rows from its partials (host copies).
-double loss_of(const cronos_mlp_t* q, const double* parts, int count, int rows) {
+double loss_of(const cronos_mlp_t* q, const double* parts, size_t count, int rows) {
     double s = 0.0;
-    for (int k = 0; k < count; ++k) s += parts[k];
+    for (size_t k = 0; k < count; ++k) s += parts[k];
     return s / ((double)rows * q->sizes[4]);
 }
 
 double loss_from_parts(cronos_mlp_t* q, int rows, cronos_status* st) {
-    const int nb = q->loss_parts;
+    const size_t nb = loss_parts(q->sizes[4], rows);
     std::vector<double> h(nb);
     *st = CRONOS_OK;
     if (hipMemcpyAsync(h.data(), q->part, nb * sizeof(double), hipMemcpyDeviceToHost, q->stream) != hipSuccess ||
@@ -1060,7 +1072,7 @@ extern "C" cronos_status cronos_mlp_create(const int32_t* sizes, const double* p
         HIP_TRY(dmalloc(&q->t, R * sizes[4]));
         HIP_TRY(dmalloc(&q->dy, R * q->wp[4]));
         HIP_TRY(dmalloc(&q->dyt, sizes[4] * R));
-        HIP_TRY(dmalloc(&q->part, (R * q->wp[4] + 255) / 256));
+        HIP_TRY(dmalloc(&q->part, loss_parts(sizes[4], q->max_rows)));
         // split-K partials of the weight gradients at max_rows rows, laid out like the parameters
         const int splits = (int)((R + kSplitRows - 1) / kSplitRows);
         if (splits > 1) HIP_TRY(dmalloc(&q->part_w, (size_t)splits * n));
@@ -1119,7 +1131,7 @@ extern "C" cronos_status cronos_mlp_forward(cronos_mlp q, const float* x, int64_
         const int r = (int)std::min<int64_t>(q->max_rows, rows - r0);
         cronos_status st = upload_rows(q, x + r0 * q->sizes[0], nullptr, r);
         if (st != CRONOS_OK) return st;
-        st = forward_dev(q, r, false, nullptr);
+        st = forward_dev(q, r, false, nullptr, 0);
         if (st != CRONOS_OK) return st;
         HIP_TRY(hipMemcpyAsync(y + r0 * n_out, q->y, (size_t)r * n_out * sizeof(float), hipMemcpyDeviceToHost, q->stream));
         HIP_TRY(hipStreamSynchronize(q->stream));
@@ -1133,7 +1145,7 @@ extern "C" cronos_status cronos_mlp_loss_grad(cronos_mlp q, const float* x, cons
     if (!q || !x || !t || rows < 1 || rows > q->max_rows) return fail(CRONOS_EINVAL, "mlp_loss_grad: bad arguments");
     HIP_TRY(hipSetDevice(q->device));
     cronos_status st = upload_rows(q, x, t, rows);
-    if (st == CRONOS_OK) st = forward_dev(q, rows, true, q->part);
+    if (st == CRONOS_OK) st = forward_dev(q, rows, true, q->part, loss_parts(q->sizes[4], q->max_rows));
     if (st == CRONOS_OK) st = backward_dev(q, rows, true);
     if (st != CRONOS_OK) return st;
     const double l = loss_from_parts(q, rows, &st);
@@ -1183,8 +1195,8 @@ extern "C" cronos_status cronos_mlp_train(cronos_mlp q, const float* x, const fl
     HIP_TRY(hipMemcpyAsync(q->data_t, t, (size_t)rows * n_out * sizeof(float), hipMemcpyHostToDevice, q->stream));
     // learning rate: cosine from lr to lr_final over all minibatch steps (constant if equal)
     const int64_t per_epoch = (rows + batch - 1) / batch, last = std::max<int64_t>(1, per_epoch * epochs - 1);
-    // loss partials of the last epoch, read back once at its end (at most one per 16 padded rows)
-    const size_t parts_cap = (size_t)per_epoch * (size_t)((std::min<int64_t>(batch, rows) + 63) / 64 * 4);
+    // loss partials of the last epoch, read back once at its end
+    const size_t parts_cap = (size_t)per_epoch * loss_parts(n_out, (int)std::min<int64_t>(batch, rows));
     if (q->epoch_part_cap < parts_cap) {
         if (q->epoch_part) (void)hipFree(q->epoch_part);
         q->epoch_part = nullptr;
@@ -1207,20 +1219,17 @@ extern "C" cronos_status cronos_mlp_train(cronos_mlp q, const float* x, const fl
     for (int e = 0; e < epochs; ++e) {
         const bool final_epoch = e == epochs - 1;
         HIP_TRY(hipMemcpyAsync(q->idx, perm[e & 1].data(), rows * sizeof(int), hipMemcpyHostToDevice, q->stream));
-        std::vector<int> counts;   // loss partials of each of the last epoch's minibatches
-        size_t parts = 0;
+        size_t parts = 0;   // loss partials of the last epoch's minibatches so far
         for (int64_t b0 = 0; b0 < rows; b0 += batch) {
             const int r = (int)std::min<int64_t>(batch, rows - b0);
             cronos_status st = gather_rows(q, q->data_x, q->data_t, q->idx + b0, r, true);
-            if (st == CRONOS_OK) st = forward_dev(q, r, true, final_epoch ? q->epoch_part + parts : q->part);
+            if (st == CRONOS_OK) st = final_epoch ? forward_dev(q, r, true, q->epoch_part + parts, q->epoch_part_cap - parts)
+                                               : forward_dev(q, r, true, q->part, loss_parts(n_out, q->max_rows));
             if (st == CRONOS_OK) st = backward_dev(q, r, false);
             const double lr_t = lr_final + 0.5 * (lr - lr_final) * (1.0 + std::cos(M_PI * (double)step++ / (double)last));
             if (st == CRONOS_OK) st = adam_dev(q, lr_t, 0.9, 0.999, 1e-8);
             if (st != CRONOS_OK) return st;
-            if (final_epoch) {
-                counts.push_back(q->loss_parts);
-                parts += (size_t)q->loss_parts;
-            }
+            if (final_epoch) parts += loss_parts(n_out, r);
         }
         if (!final_epoch) {
             draw_order(e + 1);
@@ -1234,8 +1243,9 @@ extern "C" cronos_status cronos_mlp_train(cronos_mlp q, const float* x, const fl
         size_t at = 0;
         for (int64_t b = 0; b < per_epoch; ++b) {
             const int r = (int)std::min<int64_t>(batch, rows - b * batch);
-            sum += loss_of(q, h.data() + at, counts[b], r) * r;
-            at += (size_t)counts[b];
+            const size_t count = loss_parts(n_out, r);
+            sum += loss_of(q, h.data() + at, count, r) * r;
+            at += count;
         }
         if (epoch_loss) *epoch_loss = sum / (double)rows;
     }
