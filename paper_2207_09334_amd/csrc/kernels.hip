@@ -2211,6 +2211,8 @@ hipError_t launch_actuation_steps(const DeviceArrays& d, unsigned long long cycl
 
 namespace {
 
+// LDS of a reverse step whose workgroups sum up to `groups` groups each (0: none of its own), a row
+// more than that for the springs that count towards none of them.
 size_t adj_lds_bytes(const DeviceArrays& d, int groups) {
     const size_t threads = (size_t)d.block * (d.lanes == 2 || d.lanes == 4 ? d.lanes : 1);
     return 2 * (size_t)d.lds_slots * sizeof(float4) + (groups ? (size_t)(groups + 1) * ((threads + 16) * sizeof(double) + sizeof(float)) : 0);
@@ -2237,7 +2239,8 @@ hipError_t launch_adj_gather(const DeviceArrays& d, const float4* x, const float
         hipLaunchKernelGGL(k, g, th, lds, st, a, p, next);
     };
 #define CRONOS_ADJ(M) go(adj_gather_kernel<M>, adj_gather_lanes_kernel<M, 2>, adj_gather_lanes_kernel<M, 4>)
-    if (!d.grp) CRONOS_ADJ(kAdjPassive);
+    // a body with groups of which no spring is a member has nothing to sum, and factors of 1 only
+    if (!d.grp || (range && max_groups == 0)) CRONOS_ADJ(kAdjPassive);
     else if (range) CRONOS_ADJ(kAdjBlockSums);
     else CRONOS_ADJ(kAdjEntrySums);
 #undef CRONOS_ADJ
