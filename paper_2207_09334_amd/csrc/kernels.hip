@@ -972,6 +972,9 @@ __global__ void __launch_bounds__(1024) step_lanes_kernel(StepArgs a, StepParams
 // factors and differences broadcast within the quad by register moves).  The sums cost each lane
 // what they cost one, but they are 3 of some 40 operations a row: on bodies of under one wavefront per
 // SIMD, where a wavefront issues alone, the rest goes four times as fast.
+// A workgroup is one slice of 64 masses (the host's rule), and each of its four wavefronts chooses the
+// difference for the slice, from all 64 positions, as the one lane-per-mass wavefront does: chosen for
+// its own 16 masses, springs of many rest lengths' stretch got other bits beside a plane.
 template <int Q>
 __device__ __forceinline__ float quad_lane(float v) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), Q * 0x55, 0xF, 0xF, true));
@@ -1040,7 +1043,7 @@ __global__ void __launch_bounds__(256) step_quads_kernel(StepArgs a, StepParams 
     for (int h = h0 + t + nt; h < h1; h += nt) sx[a.block + (h - h0)] = a.xin[a.halo_idx[h]];
     __syncthreads();
     const float4 xi = sx[own];
-    const int mode = EXACT ? difference_mode(xi, safe) : kPlain;
+    const int mode = EXACT ? difference_mode(sx[t & 63], safe) : kPlain;
     float fx = 0.0f, fy = 0.0f, fz = 0.0f;
     auto rows = [&](auto ex, int u, int left) {   // left: rows from this lane group's first on, uniform
         constexpr int EX = decltype(ex)::value;
