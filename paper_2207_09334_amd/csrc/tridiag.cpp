@@ -49,6 +49,12 @@ void gershgorin(const double* a, const double* b, int64_t k, double* lo, double*
     *hi = h;
 }
 
+// (l + h) / 2, also where the sum is beyond the largest double.
+static double middle(double l, double h) {
+    const double s = l + h;
+    return std::isinf(s) ? 0.5 * l + 0.5 * h : 0.5 * s;
+}
+
 // The `count` smallest eigenvalues of T, ascending, by section of [lo, hi] down to one ulp: up to
 // kShifts of them at a time, each pass over T placing kShifts / m points inside each of m intervals.
 void tridiag_smallest(const double* a, const double* b2, int64_t k, int64_t count, double lo, double hi, double tiny,
@@ -65,9 +71,11 @@ void tridiag_smallest(const double* a, const double* b2, int64_t k, int64_t coun
         for (int it = 0; it < 200; ++it) {
             bool open = false;
             for (int j = 0; j < m; ++j) {
-                const double mid = 0.5 * (l[j] + h[j]);
+                const double mid = middle(l[j], h[j]);
                 open = open || (mid > l[j] && mid < h[j]);   // else the interval is at one ulp
-                for (int p = 0; p < per; ++p) x[j * per + p] = l[j] + (h[j] - l[j]) * ((double)(p + 1) / (per + 1));
+                const double width = h[j] - l[j];   // infinite beyond the largest double: halved until it is not
+                for (int p = 0; p < per; ++p)
+                    x[j * per + p] = std::isinf(width) ? mid : l[j] + width * ((double)(p + 1) / (per + 1));
             }
             if (!open) break;
             sturm_counts(a, b2, k, x, tiny, below);
@@ -81,7 +89,7 @@ void tridiag_smallest(const double* a, const double* b2, int64_t k, int64_t coun
                 }
             }
         }
-        for (int j = 0; j < m; ++j) theta[j0 + j] = 0.5 * (l[j] + h[j]);
+        for (int j = 0; j < m; ++j) theta[j0 + j] = middle(l[j], h[j]);
     }
 }
 
