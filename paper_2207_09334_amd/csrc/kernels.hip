@@ -774,7 +774,7 @@ __global__ void __launch_bounds__(1024) step_kernel(StepArgs a, StepParams p) {
 // 3% of the VALU's issue slots), so each lane loads its entries before the workgroup's barrier,
 // beside the halo's index -> position chain, and reads all its neighbours from LDS before the
 // first spring's arithmetic: 5.4 -> 4.8 us per step (two rows at a time after the barrier: a
-// memory, an LDS and an arithmetic latency for each pair).
+// memory, an LDS and an arithmetic latency for each pair).  EARLY: chosen by lanes_early.
 constexpr int kLaneGroup = 8;   // rows whose LDS reads are in flight together
 // rows of a lane held in registers: all of a voxel node's 26 (4 lanes: 7, 2 lanes: 13)
 template <int LPM>
@@ -796,6 +796,7 @@ struct LaneRows {
         const int r = ok ? k * LPM + sub : k > 0 ? (k - 1) * LPM + sub : 0;
         return NARROW ? (uint32_t)narrow[e + r * 64] : packed[e + r * 64];
     }
+    template <bool EARLY>
     __device__ __forceinline__ void load(int s, int lane, int sub, int nslice, const int32_t* __restrict__ slice_ptr) {
         s = __builtin_amdgcn_readfirstlane(s);
         e = w = count = 0;
@@ -804,7 +805,7 @@ struct LaneRows {
         w = __builtin_amdgcn_readfirstlane((slice_ptr[s + 1] - e0) >> 6);
         e = e0 + lane;
         count = (w + LPM - 1) / LPM;
-        if (count == 0) return;
+        if (!EARLY || count == 0) return;
         bool ok;
 #pragma unroll
         for (int u = 0; u < kLanePre<LPM>; ++u) q[u] = row(min(u, count - 1), sub, ok);   // stays inside the slice
@@ -864,10 +865,47 @@ __device__ __forceinline__ void lane_group(int count, uint32_t tbase, const floa
     }
 }
 
+// A lane's rows two at a time, each pair loaded when it is needed.
 template <bool ACT, int EX, int LPM, bool NARROW>
-__device__ __forceinline__ void gather_lanes(uint32_t tbase, const float* __restrict__ sf, float4 xi, int sub, int tb,
-                                             const LaneRows<LPM, NARROW>& rows, float& fx, float& fy, float& fz) {
-    fx = fy = fz = 0.0f;
+__device__ __forceinline__ void lane_pairs(uint32_t tbase, const float* __restrict__ sf, float4 xi, int sub, int tb,
+                                           const LaneRows<LPM, NARROW>& rows, float& fx, float& fy, float& fz) {
+    const uint32_t tmask = (1u << tb) - 1u;
+    auto one = [&](uint32_t q) {
+        uint32_t xa, ca, gi = 0;
+        if (NARROW) {
+            xa = (q >> tb) << 4;
+            ca = ((q & tmask) << 4) | tbase;
+        } else {
+            decode_entry<ACT>(q, tbase, xa, ca, gi);
+        }
+        const float4 xj = lds_f4(xa);
+        const float4 c = lds_f4(ca);
+        const float g = ACT ? sf[gi] : 1.0f;
+        float dx, dy, dz;
+        const float fac = hooke_fac_tab<ACT, EX>(xi, xj, c, g, dx, dy, dz);
+        fx = __builtin_fmaf(fac, dx, fx);
+        fy = __builtin_fmaf(fac, dy, fy);
+        fz = __builtin_fmaf(fac, dz, fz);
+    };
+    constexpr int B = 2;
+    for (int k = 0; k < rows.count; k += B) {
+        uint32_t q[B];
+        bool ok[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const int r = (k + u) * LPM + sub, e = rows.e + r * 64;
+            ok[u] = r < rows.w;
+            q[u] = ok[u] ? (NARROW ? (uint32_t)rows.narrow[e] : rows.packed[e]) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (ok[u]) one(q[u]);
+    }
+}
+
+template <bool ACT, int EX, int LPM, bool NARROW>
+__device__ __forceinline__ void lane_early(uint32_t tbase, const float* __restrict__ sf, float4 xi, int sub, int tb,
+                                           const LaneRows<LPM, NARROW>& rows, float& fx, float& fy, float& fz) {
     const bool ok_last = (rows.count - 1) * LPM + sub < rows.w;
     auto ok = [&](int end) { return end < rows.count || ok_last; };   // of a group that ends before row `end`
     const int n0 = min(rows.count, kLaneGroup);
@@ -885,6 +923,14 @@ __device__ __forceinline__ void gather_lanes(uint32_t tbase, const float* __rest
         const int n = min(rows.count - k, 4);
         lane_group<ACT, EX, NARROW, 0>(n, tbase, sf, xi, tb, q, ok(k + n), fx, fy, fz);
     }
+}
+
+template <bool ACT, int EX, int LPM, bool NARROW, bool EARLY>
+__device__ __forceinline__ void gather_lanes(uint32_t tbase, const float* __restrict__ sf, float4 xi, int sub, int tb,
+                                             const LaneRows<LPM, NARROW>& rows, float& fx, float& fy, float& fz) {
+    fx = fy = fz = 0.0f;
+    if (EARLY) lane_early<ACT, EX, LPM, NARROW>(tbase, sf, xi, sub, tb, rows, fx, fy, fz);
+    else lane_pairs<ACT, EX, LPM, NARROW>(tbase, sf, xi, sub, tb, rows, fx, fy, fz);
 #pragma unroll
     for (int o = 1; o < LPM; o <<= 1) {
         fx += __shfl_xor(fx, o, 64);
@@ -896,7 +942,7 @@ __device__ __forceinline__ void gather_lanes(uint32_t tbase, const float* __rest
 // One step with LPM lanes per mass: a workgroup of block * LPM threads stages its block's
 // positions and halo, thread t serves mass lane t / LPM; the first lane of each mass
 // integrates.  Compact table forms (32- or 16-bit entries), one workgroup per block.
-template <bool ACT, bool EXACT, int LPM, bool NARROW>
+template <bool ACT, bool EXACT, int LPM, bool NARROW, bool EARLY>
 __global__ void __launch_bounds__(1024) step_lanes_kernel(StepArgs a, StepParams p) {
     extern __shared__ float4 sx[];
     // the arguments that the first loads need, fetched together (one scalar-cache latency, not
@@ -921,7 +967,7 @@ __global__ void __launch_bounds__(1024) step_lanes_kernel(StepArgs a, StepParams
     LaneRows<LPM, NARROW> rows;
     rows.packed = a.packed;
     rows.narrow = a.narrow;
-    rows.load((base + m) >> 6, m & 63, sub, a.nslice, a.slice_ptr);
+    rows.template load<EARLY>((base + m) >> 6, m & 63, sub, a.nslice, a.slice_ptr);
     const uint32_t tbase = table_base(a.lds_slots);
     float4* st = reinterpret_cast<float4*>(reinterpret_cast<char*>(sx) + tbase);
     float* sf = reinterpret_cast<float*>(st + a.n_table);
@@ -952,11 +998,11 @@ __global__ void __launch_bounds__(1024) step_lanes_kernel(StepArgs a, StepParams
     float fx, fy, fz;
     const int mode = EXACT ? difference_mode(xi, safe) : kPlain;
     if (mode == kPlain)
-        gather_lanes<ACT, kPlain, LPM, NARROW>(tbase, sf, xi, sub, a.narrow_tb, rows, fx, fy, fz);
+        gather_lanes<ACT, kPlain, LPM, NARROW, EARLY>(tbase, sf, xi, sub, a.narrow_tb, rows, fx, fy, fz);
     else if (mode == kExactZ)
-        gather_lanes<ACT, kExactZ, LPM, NARROW>(tbase, sf, xi, sub, a.narrow_tb, rows, fx, fy, fz);
+        gather_lanes<ACT, kExactZ, LPM, NARROW, EARLY>(tbase, sf, xi, sub, a.narrow_tb, rows, fx, fy, fz);
     else
-        gather_lanes<ACT, kExactAll, LPM, NARROW>(tbase, sf, xi, sub, a.narrow_tb, rows, fx, fy, fz);
+        gather_lanes<ACT, kExactAll, LPM, NARROW, EARLY>(tbase, sf, xi, sub, a.narrow_tb, rows, fx, fy, fz);
     if (!mine) return;
     float4 xo;
     integrate(p, p.dtv, xi, fx, fy, fz, a.fext ? a.fext + 3 * i : nullptr, vx, vy, vz, xo,
@@ -1976,6 +2022,18 @@ constexpr int kAdjStagedFactors = 4096;
 // sums that every lane repeats are no longer free); workgroups of 256 masses, 1,000: 5.04 / 7.69.
 constexpr int64_t kQuadMasses = 16384;
 
+// Several lanes per mass with their entries loaded up front, and every LDS read of eight rows before the first
+// spring (lane_early): 64-110 registers against 27-52, and up to a row more than a slice has.  That pays where
+// wavefronts are alone on their SIMDs (all of them together at most one for each of the 1024, in workgroups
+// of at most four) and each lane has several rows; else rows go in pairs (lane_pairs), with the same sums.
+// Pairs / up front, us a step, 26 rows a mass: 4 lanes in 64-mass workgroups 1,000 masses 3.87 / 3.49, 12,000
+// 4.05 / 3.64, 24,000 4.22 / 4.37, 120,000 7.65 / 8.62; 2 lanes 24,000 5.50 / 5.19, 60,000 5.98 / 6.00;
+// workgroups of 512 threads 12,000 4.16 / 4.40, of 1024 threads 4.79 / 5.30 (4 lanes), 6.17 / 7.25 (2).  Fewer
+// rows (4 lanes, 64-mass workgroups, 12,000 masses): 14 rows 3.46 / 3.44, 8 rows 3.08 / 3.36, 2 rows 2.89 / 3.25.
+bool lanes_early(const DeviceArrays& d) {
+    return d.block * d.lanes <= 256 && d.n * d.lanes <= 64 * 1024 && d.mean_rows >= 5.0f * (float)d.lanes;
+}
+
 // LDS that a workgroup may take for kAdjBlockSums: what a launch may have without asking for more, and two
 // workgroups a CU still fit.  Four lanes on 64 masses: up to 25 groups a block (the quadruped's 16 at most).
 constexpr size_t kAdjBlockLds = 64 * 1024;
@@ -1994,8 +2052,8 @@ hipError_t step_static_lds(size_t* bytes) {
                         (const void*)step_persistent<false, true, 4, kTable>, (const void*)step_kernel<true, true, 4, kSplit>,
                         (const void*)step_persistent<true, false, 8, kSplit>,
                         (const void*)step_kernel<false, true, 4, kNarrow>,
-                        (const void*)step_lanes_kernel<true, true, 4, false>,
-                        (const void*)step_lanes_kernel<false, true, 2, true>,
+                        (const void*)step_lanes_kernel<true, true, 4, false, true>,
+                        (const void*)step_lanes_kernel<false, true, 2, true, false>,
                         (const void*)step_resident<false, true, 4, true, true>, (const void*)step_resident<true, true, 4, false, false>};
     *bytes = 0;
     for (const void* k : ks) {
@@ -2055,15 +2113,13 @@ hipError_t launch_step_io(const DeviceArrays& d, const float4* xin, const float*
         const bool act = d.grp != nullptr, ex = p.exact != 0, nar = mode == kNarrow && !act;
         const dim3 g((unsigned)grid_for(d.nblk)), th((unsigned)(d.block * d.lanes));
         auto go = [&](auto k) { hipLaunchKernelGGL(k, g, th, lds, st, a, p); };
-        if (d.lanes == 2) {
-            if (act) ex ? go(step_lanes_kernel<true, true, 2, false>) : go(step_lanes_kernel<true, false, 2, false>);
-            else if (nar) ex ? go(step_lanes_kernel<false, true, 2, true>) : go(step_lanes_kernel<false, false, 2, true>);
-            else ex ? go(step_lanes_kernel<false, true, 2, false>) : go(step_lanes_kernel<false, false, 2, false>);
-        } else {
-            if (act) ex ? go(step_lanes_kernel<true, true, 4, false>) : go(step_lanes_kernel<true, false, 4, false>);
-            else if (nar) ex ? go(step_lanes_kernel<false, true, 4, true>) : go(step_lanes_kernel<false, false, 4, true>);
-            else ex ? go(step_lanes_kernel<false, true, 4, false>) : go(step_lanes_kernel<false, false, 4, false>);
-        }
+#define CRONOS_GO_L(A, L, N, Y) (ex ? go(step_lanes_kernel<A, true, L, N, Y>) : go(step_lanes_kernel<A, false, L, N, Y>))
+#define CRONOS_GO_LN(L, Y) (act ? CRONOS_GO_L(true, L, false, Y) : nar ? CRONOS_GO_L(false, L, true, Y) : CRONOS_GO_L(false, L, false, Y))
+        const bool early = lanes_early(d);
+        if (d.lanes == 2) early ? CRONOS_GO_LN(2, true) : CRONOS_GO_LN(2, false);
+        else early ? CRONOS_GO_LN(4, true) : CRONOS_GO_LN(4, false);
+#undef CRONOS_GO_LN
+#undef CRONOS_GO_L
         return hipGetLastError();
     }
     if (mode == kExplicit && d.persistent_groups <= 0 && d.block == 64 && d.n <= kQuadMasses) {

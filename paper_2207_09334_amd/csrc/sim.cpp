@@ -1021,6 +1021,7 @@ extern "C" cronos_status cronos_create(const cronos_desc* d, cronos_sim* out) {
     D.block = L.block;
     D.nblk = L.nblk;
     D.nslice = L.nslice;
+    D.mean_rows = (float)((double)entries / (64.0 * (double)L.nslice));
     D.lds_slots = L.block + L.max_halo;
     D.nb = sim->nb;
     D.batch = batch;
