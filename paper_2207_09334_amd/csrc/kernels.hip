@@ -2020,7 +2020,12 @@ constexpr int kAdjStagedFactors = 4096;
 // 1,000 masses 5.35 / 4.50 us a step, 4,320 5.2 / 4.3, 12,711 7.95 / 6.72, 18,000 5.31 / 5.20, 24,000
 // 5.67 / 5.68, 48,400 5.74 / 6.17 (above some 16,000 masses the SIMDs hold several wavefronts, and the
 // sums that every lane repeats are no longer free); workgroups of 256 masses, 1,000: 5.04 / 7.69.
+// Fewer than six entry rows a mass are not worth it (300 masses, one lane against four: no springs 1.87 / 2.34,
+// 2 rows 2.60 / 2.75, 4 rows 2.85 / 2.78, 8 rows 3.28 / 3.05, 26 rows 5.16 / 4.40).
 constexpr int64_t kQuadMasses = 16384;
+constexpr float kQuadRows = 6.0f;
+
+bool quads(const DeviceArrays& d) { return d.block == 64 && d.n <= kQuadMasses && d.mean_rows >= kQuadRows; }
 
 // Several lanes per mass with their entries loaded up front, and every LDS read of eight rows before the first
 // spring (lane_early): 64-110 registers against 27-52, and up to a row more than a slice has.  That pays where
@@ -2122,7 +2127,7 @@ hipError_t launch_step_io(const DeviceArrays& d, const float4* xin, const float*
 #undef CRONOS_GO_L
         return hipGetLastError();
     }
-    if (mode == kExplicit && d.persistent_groups <= 0 && d.block == 64 && d.n <= kQuadMasses) {
+    if (mode == kExplicit && d.persistent_groups <= 0 && quads(d)) {
         const dim3 g((unsigned)grid_for(d.nblk)), th((unsigned)(4 * d.block));
         auto go = [&](auto k) { hipLaunchKernelGGL(k, g, th, lds, st, a, p); };
         if (d.grp) p.exact ? go(step_quads_kernel<true, true>) : go(step_quads_kernel<true, false>);
