@@ -241,7 +241,8 @@ typedef struct {
                                      (with 4 lanes per mass; not with CRONOS_NO_TABLE,
                                      CRONOS_SPLIT or CRONOS_RESIDENT), and 256 otherwise       */
     int32_t batch;                /* incidence entries each lane keeps in flight: 2, 4 or 8;
-                                     0 = tuned or 4                                           */
+                                     0 = tuned or 4 (2 runs as 4 except in the split form and
+                                     with actuated explicit entries; the sums are the same)   */
     int32_t persistent;           /* 1 = one persistent launch per step (a resident grid walks
                                      the workgroup blocks); 0 = tuned or one workgroup per block;
                                      -1 = force one workgroup per block                       */

@@ -2025,6 +2025,14 @@ constexpr int kAdjStagedFactors = 4096;
 constexpr int64_t kQuadMasses = 16384;
 constexpr float kQuadRows = 6.0f;
 
+// Entries that a one-lane step keeps in flight.  Two at a time are left to the forms that gain by them: compact
+// entries are loaded a batch ahead, and a batch of two is then too short to hide anything (26 rows a mass, two
+// against four: 1,000 masses 6.05 / 4.83 us, 400,000 16.45 / 14.56); passive explicit entries run four
+// either way (5.58 / 4.92 and 21.5 / 21.6).  The springs are added in row order whatever it is.
+int step_batch(const DeviceArrays& d, int mode) {
+    return d.batch == 2 && mode != kSplit && !(mode == kExplicit && d.grp) ? 4 : d.batch;
+}
+
 bool quads(const DeviceArrays& d) { return d.block == 64 && d.n <= kQuadMasses && d.mean_rows >= kQuadRows; }
 
 // Several lanes per mass with their entries loaded up front, and every LDS read of eight rows before the first
@@ -2150,18 +2158,19 @@ hipError_t launch_step_io(const DeviceArrays& d, const float4* xin, const float*
      : mode == kTable  ? CRONOS_GO(A, E, B, kTable)                                                  \
                        : CRONOS_GO(A, E, B, kExplicit))
     const bool act = d.grp != nullptr, ex = p.exact != 0;
+    const int batch = step_batch(d, mode);
     if (d.stage_io && act && mode == kTable) {
 #define CRONOS_GO_S(E, B) go(step_kernel<true, E, B, kTable, true>, step_persistent<true, E, B, kTable, true>)
-        if (d.batch == 8) ex ? CRONOS_GO_S(true, 8) : CRONOS_GO_S(false, 8);
-        else if (d.batch == 2) ex ? CRONOS_GO_S(true, 2) : CRONOS_GO_S(false, 2);
+        if (batch == 8) ex ? CRONOS_GO_S(true, 8) : CRONOS_GO_S(false, 8);
         else ex ? CRONOS_GO_S(true, 4) : CRONOS_GO_S(false, 4);
 #undef CRONOS_GO_S
-    } else if (d.batch == 8) {
+    } else if (batch == 8) {
         if (act) ex ? CRONOS_GO_M(true, true, 8) : CRONOS_GO_M(true, false, 8);
         else ex ? CRONOS_GO_M(false, true, 8) : CRONOS_GO_M(false, false, 8);
-    } else if (d.batch == 2) {
-        if (act) ex ? CRONOS_GO_M(true, true, 2) : CRONOS_GO_M(true, false, 2);
-        else ex ? CRONOS_GO_M(false, true, 2) : CRONOS_GO_M(false, false, 2);
+    } else if (batch == 2) {   // see step_batch
+        if (mode == kSplit && !act) ex ? CRONOS_GO(false, true, 2, kSplit) : CRONOS_GO(false, false, 2, kSplit);
+        else if (mode == kSplit) ex ? CRONOS_GO(true, true, 2, kSplit) : CRONOS_GO(true, false, 2, kSplit);
+        else ex ? CRONOS_GO(true, true, 2, kExplicit) : CRONOS_GO(true, false, 2, kExplicit);
     } else {
         if (act) ex ? CRONOS_GO_M(true, true, 4) : CRONOS_GO_M(true, false, 4);
         else ex ? CRONOS_GO_M(false, true, 4) : CRONOS_GO_M(false, false, 4);
