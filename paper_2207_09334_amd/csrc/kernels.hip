@@ -619,7 +619,7 @@ __device__ __forceinline__ void integrate(const StepParams& p, float dtv, float4
 // damping, symplectic Euler, fixed masses.
 template <bool ACT, bool EXACT, int BATCH, int MODE, bool STAGE = false>
 __device__ __forceinline__ void step_block(float4* __restrict__ sx, const StepArgs& a, const StepParams& p, int b,
-                                           float u, float safe) {
+                                           float u) {
     constexpr bool TABLE = MODE != kExplicit;
     const int t = (int)threadIdx.x, base = b * a.block;
     const uint32_t tbase = table_base(a.lds_slots);
@@ -630,10 +630,10 @@ __device__ __forceinline__ void step_block(float4* __restrict__ sx, const StepAr
     // lane's mass, the first halo index, positions, the first batch of entries, the table's
     // first part, then what hangs on those
     const int own = a.lane_mass[base + t];
+    float4 xt = make_float4(0.f, 0.f, 0.f, 0.f), xh = xt, tab = xt;
+    if (base + t < a.n) xt = a.xin[base + t];   // before the halo's, which first waits for halo_ptr
     const int h0 = a.halo_ptr[b], h1 = a.halo_ptr[b + 1];
     const int hj = h0 + t < h1 ? a.halo_idx[h0 + t] : -1;
-    float4 xt = make_float4(0.f, 0.f, 0.f, 0.f), xh = xt, tab = xt;
-    if (base + t < a.n) xt = a.xin[base + t];
     if (TABLE && t < a.n_table) tab = a.table[t];
     const int2 bg = TABLE && ACT ? a.blk_groups[b] : make_int2(0, 0);
     const int s = (base + t) >> 6;
@@ -667,6 +667,7 @@ __device__ __forceinline__ void step_block(float4* __restrict__ sx, const StepAr
     sx[t] = xt;
     if (hj >= 0) sx[a.block + t] = xh;
     for (int h = h0 + t + a.block; h < h1; h += a.block) sx[a.block + (h - h0)] = a.xin[a.halo_idx[h]];
+    const float safe = ACT ? a.act->safe : p.safe;   // here, so that no scalar load above is waited for with it
     __syncthreads();
     const float4 xi = sx[own];
     float fx, fy, fz;
@@ -759,9 +760,8 @@ __global__ void __launch_bounds__(1024) step_kernel(StepArgs a, StepParams p) {
     extern __shared__ float4 sx[];
     constexpr bool FUSABLE = ACT && MODE != kExplicit;
     const int b = logical_block(a.nblk);
-    const float safe = ACT ? a.act->safe : p.safe;
     const float u = FUSABLE && a.fuse ? advance_step(a) : 0.0f;
-    if (b < a.nblk) step_block<ACT, EXACT, BATCH, MODE, STAGE>(sx, a, p, b, u, safe);
+    if (b < a.nblk) step_block<ACT, EXACT, BATCH, MODE, STAGE>(sx, a, p, b, u);
 }
 
 // Several lanes per mass (LPM = 2 or 4; compact table forms): lane j of a mass's group walks its
@@ -1132,12 +1132,11 @@ __global__ void __launch_bounds__(1024) step_persistent(StepArgs a, StepParams p
     const int xcd = (int)(blockIdx.x & 7u);
     const int stride = (int)(gridDim.x >> 3);
     constexpr bool FUSABLE = ACT && MODE != kExplicit;
-    const float safe = ACT ? a.act->safe : p.safe;
     const float u = FUSABLE && a.fuse ? advance_step(a) : 0.0f;
     for (int j = (int)(blockIdx.x >> 3); j < per; j += stride) {
         const int b = xcd * per + j;
         if (b >= a.nblk) break;
-        step_block<ACT, EXACT, BATCH, MODE, STAGE>(sx, a, p, b, u, safe);
+        step_block<ACT, EXACT, BATCH, MODE, STAGE>(sx, a, p, b, u);
         __syncthreads();  // LDS is restaged for the next block
     }
 }
