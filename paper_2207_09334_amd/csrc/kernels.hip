@@ -412,13 +412,20 @@ __device__ __forceinline__ void spring_pass(const float4* __restrict__ sx, uint3
     if (threadIdx.x == 0) sfac[n_sp] = 0.0f;  // the factor of the padding entries
     for (int j0 = __builtin_amdgcn_readfirstlane(w0); j0 < n_sp; j0 += BATCH * block) {
         uint32_t r[BATCH];
+        int gi[BATCH];
         float g[BATCH];
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) {  // lanes past the end re-read the last record
             const int j = min(j0 + u * block + lane, n_sp - 1);
             r[u] = rec[j];
-            if (ACT) g[u] = sf[rgrp[j]];
+            if (ACT) gi[u] = rgrp[j];
         }
+        // every load is issued before the first of them is waited for (left to itself the compiler may wait
+        // for each group index in turn)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u)
+            if (ACT) g[u] = sf[gi[u]];
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) {
             const int j = j0 + u * block + lane;
@@ -2027,9 +2034,10 @@ constexpr float kQuadRows = 6.0f;
 // Entries that a one-lane step keeps in flight.  Two at a time are left to the forms that gain by them: compact
 // entries are loaded a batch ahead, and a batch of two is then too short to hide anything (26 rows a mass, two
 // against four: 1,000 masses 6.05 / 4.83 us, 400,000 16.45 / 14.56); passive explicit entries run four
-// either way (5.58 / 4.92 and 21.5 / 21.6).  The springs are added in row order whatever it is.
+// either way (5.58 / 4.92 and 21.5 / 21.6), and so do passive split ones (28.7 /
+// 25.9).  The springs are added in row order whatever it is.
 int step_batch(const DeviceArrays& d, int mode) {
-    return d.batch == 2 && mode != kSplit && !(mode == kExplicit && d.grp) ? 4 : d.batch;
+    return d.batch == 2 && !(d.grp && (mode == kSplit || mode == kExplicit)) ? 4 : d.batch;
 }
 
 bool quads(const DeviceArrays& d) { return d.block == 64 && d.n <= kQuadMasses && d.mean_rows >= kQuadRows; }
@@ -2167,8 +2175,7 @@ hipError_t launch_step_io(const DeviceArrays& d, const float4* xin, const float*
         if (act) ex ? CRONOS_GO_M(true, true, 8) : CRONOS_GO_M(true, false, 8);
         else ex ? CRONOS_GO_M(false, true, 8) : CRONOS_GO_M(false, false, 8);
     } else if (batch == 2) {   // see step_batch
-        if (mode == kSplit && !act) ex ? CRONOS_GO(false, true, 2, kSplit) : CRONOS_GO(false, false, 2, kSplit);
-        else if (mode == kSplit) ex ? CRONOS_GO(true, true, 2, kSplit) : CRONOS_GO(true, false, 2, kSplit);
+        if (mode == kSplit) ex ? CRONOS_GO(true, true, 2, kSplit) : CRONOS_GO(true, false, 2, kSplit);
         else ex ? CRONOS_GO(true, true, 2, kExplicit) : CRONOS_GO(true, false, 2, kExplicit);
     } else {
         if (act) ex ? CRONOS_GO_M(true, true, 4) : CRONOS_GO_M(true, false, 4);
