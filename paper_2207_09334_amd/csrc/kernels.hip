@@ -2031,6 +2031,8 @@ constexpr int kAdjStagedFactors = 4096;
 constexpr int64_t kQuadMasses = 16384;
 constexpr float kQuadRows = 6.0f;
 
+int step_mode(const DeviceArrays& d) { return d.sp_rec ? kSplit : d.narrow ? kNarrow : d.packed ? kTable : kExplicit; }
+
 // Entries that a one-lane step keeps in flight.  Two at a time are left to the forms that gain by them: compact
 // entries are loaded a batch ahead, and a batch of two is then too short to hide anything (26 rows a mass, two
 // against four: 1,000 masses 6.05 / 4.83 us, 400,000 16.45 / 14.56); passive explicit entries run four
@@ -2122,7 +2124,7 @@ hipError_t launch_step_io(const DeviceArrays& d, const float4* xin, const float*
         else hipLaunchKernelGGL(step_grid_kernel<false>, grid, th, 0, st, g, p);
         return hipGetLastError();
     }
-    const int mode = d.sp_rec ? kSplit : d.narrow ? kNarrow : d.packed ? kTable : kExplicit;
+    const int mode = step_mode(d);
     if (fuse && !fused_actuation(d)) return hipErrorInvalidValue;
     StepArgs a{xin, vin, xout, vout, d.slice_ptr, d.nbr, d.kl, d.grp, d.halo_ptr, d.halo_idx,
                d.lane_mass, factor ? factor : d.factor, d.fext, vstar, d.packed, d.narrow, d.table, d.blk_groups, d.sp_rec, d.sp_grp,
@@ -2215,13 +2217,27 @@ hipError_t persistent_grid(const DeviceArrays& d, int exact, int* grid) {
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
-    const void* k;
-    if (d.sp_rec)
-        k = d.grp ? (exact ? (const void*)step_persistent<true, true, 4, kSplit> : (const void*)step_persistent<true, false, 4, kSplit>)
-                  : (exact ? (const void*)step_persistent<false, true, 4, kSplit> : (const void*)step_persistent<false, false, 4, kSplit>);
-    else
-        k = d.grp ? (exact ? (const void*)step_persistent<true, true, 4, kTable> : (const void*)step_persistent<true, false, 4, kTable>)
-                  : (exact ? (const void*)step_persistent<false, true, 4, kTable> : (const void*)step_persistent<false, false, 4, kTable>);
+    // the very kernel that will run: a grid of more workgroups than the device holds at once takes two rounds
+    const void* k = nullptr;
+    const int mode = step_mode(d), batch = step_batch(d, mode);
+    const bool act = d.grp != nullptr;
+    auto is = [&](const void* kernel) { k = kernel; };
+#define CRONOS_K(A, E, B, M) (const void*)step_persistent<A, E, B, M>
+#define CRONOS_K_M(A, E, B)                                                                                       \
+    is(mode == kSplit ? CRONOS_K(A, E, B, kSplit) : mode == kNarrow ? CRONOS_K(A, E, B, (A ? kTable : kNarrow))   \
+       : mode == kTable ? CRONOS_K(A, E, B, kTable) : CRONOS_K(A, E, B, kExplicit))
+#define CRONOS_K_E(A, B) (exact ? CRONOS_K_M(A, true, B) : CRONOS_K_M(A, false, B))
+    if (batch == 2) {   // actuated split and explicit forms only
+        if (mode == kSplit) is(exact ? CRONOS_K(true, true, 2, kSplit) : CRONOS_K(true, false, 2, kSplit));
+        else is(exact ? CRONOS_K(true, true, 2, kExplicit) : CRONOS_K(true, false, 2, kExplicit));
+    } else if (batch == 8) {
+        act ? CRONOS_K_E(true, 8) : CRONOS_K_E(false, 8);
+    } else {
+        act ? CRONOS_K_E(true, 4) : CRONOS_K_E(false, 4);
+    }
+#undef CRONOS_K_E
+#undef CRONOS_K_M
+#undef CRONOS_K
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, d.block, step_launch_lds_bytes(d));
     if (e != hipSuccess) return e;
     int g = std::max(1, per_cu) * cus;

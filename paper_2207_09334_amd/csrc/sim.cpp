@@ -1961,6 +1961,7 @@ extern "C" cronos_status cronos_autotune(const cronos_desc* d, int32_t n_steps, 
             const int bt = cfg[0], pers = cfg[1], ln = cfg[2];
             {
                 sim->d.batch = bt;
+                if (pers && cronos::persistent_grid(sim->d, sim->p.exact, &pgrid) != hipSuccess) continue;
                 sim->d.persistent_groups = pers ? pgrid : 0;
                 sim->d.lanes = ln;
                 sim->use_graph = false;
