@@ -2315,7 +2315,21 @@ size_t adj_lds_bytes(const DeviceArrays& d, int groups) {
 
 }  // namespace
 
-bool adj_block_sums(const DeviceArrays& d, int max_groups) { return adj_lds_bytes(d, max_groups) <= kAdjBlockLds; }
+// Sums per workgroup pay where they save more than they cost.  They save a read and a write of 16 bytes per
+// entry, which is the more the less of them the caches hold; they cost each thread two LDS operations per group
+// of the workgroup's range, and LDS that other workgroups could use.  Per entry / per workgroup, us a
+// reversed step with the step recomputed beside it: 4 lanes on 64 masses, 16 groups, 26 rows a mass, 1,000 masses
+// 14.5 / 13.6, 12,000 16.4 / 14.4, 50,000 28.9 / 21.8; 14 rows 12.0 / 12.5, 13.3 / 12.7, 21.9 / 19.2; 4
+// rows 10.2 / 11.3, 10.9 / 11.2, 15.3 / 14.1; 24 groups, 14 rows 12.6 / 13.7, 13.2 / 13.6, 20.8 / 21.7; one lane,
+// 40 groups in 64-mass workgroups, 8 rows 13.0 / 17.3, 14.8 / 18.0, 17.4 / 19.7.
+// (No group at all: the passive form, which sums nothing.)
+bool adj_block_sums(const DeviceArrays& d, int max_groups) {
+    if (max_groups == 0) return true;
+    if (adj_lds_bytes(d, max_groups) > kAdjBlockLds) return false;
+    const float groups = (float)max_groups, threads = (float)(d.block * d.lanes);
+    if (d.n < 8192) return d.mean_rows >= 20.0f && groups <= d.mean_rows && 16.0f * groups <= 3.0f * threads;
+    return groups <= (d.n < 32768 ? 1.0f : 2.0f) * d.mean_rows;
+}
 
 hipError_t launch_adj_gather(const DeviceArrays& d, const float4* x, const float4* w, const float* xbl, float* xb0,
                              double2* sens, const int4* range, int max_groups, double cos_t, double sin_t, hipStream_t st,
