@@ -249,7 +249,10 @@ typedef struct {
     int32_t lanes_per_mass;       /* lanes sharing each mass's incidence list: 1, 2 or 4
                                      (workgroups of block_masses * lanes threads, at most 1024;
                                      compact table forms with one workgroup per block only,
-                                     else 1); 0 = tuned, or 4 for a system under 131,072
+                                     else 1: explicit entries of small bodies in 64-mass
+                                     workgroups are evaluated by four lanes per mass whatever
+                                     is given, but summed in row order, bit for bit as by
+                                     one); 0 = tuned, or 4 for a system under 131,072
                                      masses when block_masses is 0 (see there), or 1.  More
                                      than one lane per mass
                                      groups each mass's force sum differently (equal to
@@ -382,7 +385,8 @@ cronos_status cronos_stream_bandwidth(int32_t device, int64_t bytes, int32_t rep
 cronos_status cronos_info(cronos_sim sim, int64_t* n_masses, int64_t* n_springs, int32_t* n_bodies,
                           int32_t* block_masses, int64_t* step);
 /* Launch configuration in use: masses per workgroup, batch, persistent workgroups (0 = one
- * per block), the form of the step's incidence data (CRONOS_FORM_*) and the lanes per mass.
+ * per block), the form of the step's incidence data (CRONOS_FORM_*) and the lanes per mass (whose
+ * partial sums are added up; 1 for explicit entries, however many lanes evaluate them).
  * Any output may be NULL. */
 #define CRONOS_FORM_EXPLICIT 0  /* (slot, k, L0) per entry, every spring evaluated at both ends  */
 #define CRONOS_FORM_TABLE    1  /* 32-bit entries indexing the table of distinct (k, L0) pairs    */
@@ -431,7 +435,7 @@ typedef struct {
  * once per workgroup size in {64, 128, 256, 512, 1024} and times n_steps steps (after 3 warm-up
  * steps, HIP events on its stream) for every batch in {2, 4, 8} and both launch forms with
  * one lane per mass, and for 2 and 4 lanes per mass (table forms, where the workgroup of
- * size x lanes threads fits); the
+ * size x lanes threads fits; where batches run the same kernel, the first of the equals may be any); the
  * fastest configuration is returned and cached for the process under the key (GPU
  * architecture, floor(log2 N), floor(log2 S), actuated, contact), and appended to the file
  * named by the environment variable CRONOS_TUNE_CACHE if set (read back at the first

@@ -51,7 +51,8 @@ enum : int { kPlain = 0, kExactZ = 1, kExactAll = 2 };
 constexpr double kLengthFloor = 1e-37;
 
 // e^2 + kLengthFloor in one instruction: left to itself the compiler copies the constant into the
-// accumulator of a two-address multiply-add first (two more instructions per spring).
+// accumulator of a two-address multiply-add first (two more instructions per spring).  A loop around it
+// is not unrolled by the compiler, which may not copy such an instruction.
 __device__ __forceinline__ double square_above_floor(double e) {
     double s;
     asm("v_fma_f64 %0, %1, %1, %2" : "=v"(s) : "v"(e), "s"(kLengthFloor));
@@ -1240,7 +1241,9 @@ forces_kernel(const float4* __restrict__ xin, const float* __restrict__ mass, co
     const int own = stage_positions(sx, xin, halo_ptr, halo_idx, lane_mass, b, base, n, block);
     const float4 xi = sx[own];
     float fx, fy, fz;
-    // the same choice of difference as the step, so this is the force the step integrates
+    // the choice of difference of the steps that run one lane per mass (and of the explicit ones that run four), so
+    // this is the force such a step integrates; several lanes per mass choose for 32 or 16 masses at a time, which
+    // tells for springs of more than twice their rest length beside a coordinate plane only
     const int mode = p.exact ? difference_mode(xi, p.safe) : kPlain;
     const int s = (base + (int)threadIdx.x) >> 6;
     if (mode == kPlain) gather<ACT, kPlain, 4>(sx, xi, s, nslice, slice_ptr, nbr, kl, grp, factor, fx, fy, fz);
