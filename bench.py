@@ -407,7 +407,7 @@ def mlp_bench(args) -> dict:
     X = rng.normal(size=(args.mlp_rows, sizes[0])).astype(np.float32)
     T = np.tanh(X[:, :3] + 0.1 * X[:, 3:6] * X[:, 6:9]).astype(np.float32)
     batch = 1024
-    net = CR.cronos_mlp_create(W.mlp_init(4, sizes), max_rows=batch)
+    net = CR.cronos_mlp_create(W.mlp_init(4, sizes), sizes=sizes, max_rows=batch)
     CR.cronos_mlp_train(net, X[:batch * 4], T[:batch * 4], batch=batch, epochs=1, lr=1e-3, seed=1)   # warm-up
     torch.cuda.synchronize()
     t0 = time.perf_counter()

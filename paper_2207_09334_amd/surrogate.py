@@ -89,7 +89,7 @@ class Surrogate:
         Xn = self.xs.apply(X)
         self.lo, self.hi = Xn.min(axis=0), Xn.max(axis=0)
         sizes = (X.shape[1], width, width, width, D.shape[1])
-        self.net = CR.cronos_mlp_create(W.mlp_init(seed, sizes), max_rows=max_rows)
+        self.net = CR.cronos_mlp_create(W.mlp_init(seed, sizes), sizes=sizes, max_rows=max_rows)
         self.n_params = sum(sizes[l] * sizes[l + 1] + sizes[l + 1] for l in range(4))
         t0 = time.perf_counter()
         self.train_loss = CR.cronos_mlp_train(self.net, Xn.astype(np.float32), self.ds.apply(D).astype(np.float32),
