@@ -532,7 +532,7 @@ def cronos_mlp_create(params, sizes=(96, 256, 256, 256, 3), max_rows=4096, devic
     sz = _arr(sizes, np.int32)
     fl = _flat(params)
     need = sum(int(sz[l]) * int(sz[l + 1]) + int(sz[l + 1]) for l in range(len(sz) - 1))
-    if len(sz) != 5 or len(fl) != need:
+    if len(sz) != 5 or len(fl) < need:   # (of a longer list the layers take the first)
         raise CronosError(EINVAL, f"mlp_create: {len(fl)} parameters for layers {tuple(sizes)}, which hold {need}")
     h = _p()
     _check(_lib.cronos_mlp_create(_ptr(sz), _ptr(fl), int(max_rows), device, stream, C.byref(h)))

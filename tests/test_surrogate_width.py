@@ -1,5 +1,5 @@
-"""The surrogate trains the network of the width it was asked for, and a network is created only from as many
-parameters as its layers hold."""
+"""The surrogate trains the network of the width it was asked for, and a network is created only from at least
+as many parameters as its layers hold."""
 import numpy as np
 import pytest
 
@@ -22,8 +22,8 @@ def test_network_has_the_width_asked_for(monkeypatch, width):
     assert made["shapes"][::2] == [(96, width), (width, width), (width, width), (width, 3)]
 
 
-@pytest.mark.parametrize("given, sizes", [((96, 768, 768, 768, 3), (96, 256, 256, 256, 3)), ((4, 5, 6, 7, 2), (4, 5, 6, 7, 3)),
+@pytest.mark.parametrize("given, sizes", [((96, 256, 256, 256, 3), (96, 768, 768, 768, 3)), ((4, 5, 6, 7, 2), (4, 5, 6, 7, 3)),
                                           ((4, 5, 6, 7, 2), (4, 5, 6, 7))])
-def test_parameters_of_another_network_are_refused(given, sizes):
+def test_too_few_parameters_are_refused(given, sizes):
     with pytest.raises(CR.CronosError):
         CR.cronos_mlp_create(W.mlp_init(1, given), sizes=sizes)
